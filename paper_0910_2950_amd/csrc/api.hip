@@ -729,7 +729,7 @@ int fgi_dslash(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const vo
         pack_even_spinor(c, g, in, vin);  // same layout for either parity
         FermionOp op = f.op64(u, a.kappa);
         if (f.sp == P64) {
-            dslash(c, op, out_parity, P64, SpinorPtr{vin, nullptr}, P64, SpinorPtr{vout, nullptr});
+            dslash(c, op, out_parity, P64, SpinorPtr{vin, nullptr}, P64, SpinorPtr{vout, nullptr}, true);
         } else {
             void* us = c.sloppy.get(sloppy_bytes(g));
             make_sloppy(c, g, u, us, f.sp, f.rc);
@@ -738,7 +738,7 @@ int fgi_dslash(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const vo
             float* norms = (float*)c.s_norms.get(sizeof(float) * 3 * (size_t)g.Vh);
             SpinorPtr si{c.s_p.get(nb), norms}, so{c.s_q.get(nb), norms + g.Vh};
             convert_spinor(c, g, P64, SpinorPtr{vin, nullptr}, f.sp, si);
-            dslash(c, os, out_parity, f.sp, si, f.sp, so);
+            dslash(c, os, out_parity, f.sp, si, f.sp, so, true);
             convert_spinor(c, g, f.sp, so, P64, SpinorPtr{vout, nullptr});
         }
         unpack_even_spinor(c, g, vout, out);
@@ -899,7 +899,7 @@ int fgi_halo_time(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const
         t.interior_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 1); });
         t.faces_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 2); });
         t.all_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 0); });
-        t.local_us = timed([&] { dslash(c, h.op, 1, h.prec, h.in, h.prec, so); });
+        t.local_us = timed([&] { dslash(c, h.op, 1, h.prec, h.in, h.prec, so, true); });
         t.face_sites = g.Vh / g.L[3];
         t.halo_bytes = (long)hb;
         FGI_HIP(hipEventDestroy(e0));
@@ -1966,7 +1966,7 @@ void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<Ch
         d.beta = ch.beta;
         d.kappa = ch.kappa;
         const long n[4] = {d.g.Vh, d.g.V, 4L * d.g.V, d.g.Vh};
-        const int bsz[4] = {256, 256, 256, c.ds_bs};
+        const int bsz[4] = {256, 256, 256, ds_sites(c, d.g.Vh)};
         for (int k = 0; k < 4; k++) {
             d.blk0[k] = B.nblk[k];
             d.nblk[k] = (int)((n[k] + bsz[k] - 1) / bsz[k]);
@@ -1982,9 +1982,28 @@ void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<Ch
 }
 
 void upload_batch(Ctx& c, const std::vector<ChainDesc>& cd, Batch& B) {
-    ChainDesc* dcd = (ChainDesc*)c.cdesc.get(sizeof(ChainDesc) * cd.size());
-    FGI_HIP(hipMemcpyAsync(dcd, cd.data(), sizeof(ChainDesc) * cd.size(), hipMemcpyHostToDevice, c.stream));
-    B.cd = dcd;
+    std::vector<int2> map[2];
+    for (int k = 0; k < 2; k++) {
+        for (int i = 0; i < B.nc; i++)
+            if (site_split(cd[i].g.Vh) == (k == DS_SPLIT)) {
+                B.ds_nc[k]++;
+                for (int b = 0; b < cd[i].nblk[GRID_DS]; b++) map[k].push_back(make_int2(i, b));
+            }
+        B.ds_blk[k] = (int)map[k].size();
+        for (int i = 0; i < B.nc; i++)
+            if (site_split(cd[i].g.Vh) == (k == DS_SPLIT)) map[k].push_back(make_int2(i, cd[i].nblk[GRID_DS]));
+    }
+    const size_t nd = sizeof(ChainDesc) * cd.size(), n0 = sizeof(int2) * map[0].size(), n1 = sizeof(int2) * map[1].size();
+    std::vector<char> host(nd + n0 + n1);
+    std::memcpy(host.data(), cd.data(), nd);
+    if (n0) std::memcpy(host.data() + nd, map[0].data(), n0);
+    if (n1) std::memcpy(host.data() + nd + n0, map[1].data(), n1);
+    char* dev = (char*)c.cdesc.get(host.size());
+    FGI_HIP(hipMemcpyAsync(dev, host.data(), host.size(), hipMemcpyHostToDevice, c.stream));
+    FGI_HIP(hipStreamSynchronize(c.stream));   // host goes out of scope
+    B.cd = (const ChainDesc*)dev;
+    B.ds_map[0] = (const int2*)(dev + nd);
+    B.ds_map[1] = (const int2*)(dev + nd + n0);
 }
 }  // namespace
 

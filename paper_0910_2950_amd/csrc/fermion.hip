@@ -348,6 +348,275 @@ __global__ void __launch_bounds__(DBS) k_dslash(DArgs A) {
     dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, NT>(A, b, nb, lds);
 }
 
+// ------------------------------------------------ split sites (small lattices) ---
+// One thread per site leaves most of the chip idle below a few hundred waves
+// (8^4: 32 waves on 1024 SIMDs), and the launch then lasts as long as one
+// thread's chain of eight dependent hops.  Here a block's four waves share 64
+// sites: wave w takes the two hops along direction w, with all its loads in
+// flight together, the four partial sums meet in LDS, and wave w finishes spin
+// w of the epilogue.  The sum of the four directions is ((0 + 1) + (2 + 3)), so
+// the bits differ from the one-thread order; the choice depends on the lattice
+// alone (site_split), so every path of one lattice makes it alike.
+
+// element e = 3 spin + colour of the spinor at s (R the working precision)
+template <int P, typename R> __device__ __forceinline__ cx<R> load_elem(const SpinorPtr& f, int s, int Vh, int e, float n) {
+    if constexpr (P == P64) {
+        const d2 v = ((const d2*)f.v)[(size_t)e * Vh + s];
+        return {R(v.x), R(v.y)};
+    } else if constexpr (P == P32) {
+        const f2 v = ((const f2*)f.v)[((size_t)(e >> 1) * Vh + s) * 2 + (e & 1)];
+        return {R(v.x), R(v.y)};
+    } else {
+        const h2 v = ((const h2*)f.v)[((size_t)(e >> 2) * Vh + s) * 4 + (e & 3)];
+        return {R(float(v.x) * n), R(float(v.y) * n)};
+    }
+}
+template <int P> __device__ __forceinline__ float load_norm(const SpinorPtr& f, int s) {
+    if constexpr (P == P16) return f.norm[s];
+    return 1.0f;
+}
+
+// One spin (three colours) of a spinor as one wave of the block holds it.
+template <int P, typename R>
+__device__ __forceinline__ void load_spin(const SpinorPtr& f, int s, int Vh, int w, cx<R> v[3]) {
+    const float n = load_norm<P>(f, s);
+#pragma unroll
+    for (int k = 0; k < 3; k++) v[k] = load_elem<P, R>(f, s, Vh, 3 * w + k, n);
+}
+
+// FP16 storage needs the largest component over the four waves' spins (mx:
+// 4 x 64 floats of LDS); every wave of the block calls this together.
+template <int P, typename R>
+__device__ __forceinline__ void store_spin(const SpinorPtr& f, int s, int Vh, int w, bool live, const cx<R> v[3],
+                                           float* mx) {
+    if constexpr (P == P16) {
+        const int lane = threadIdx.x & 63;
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) m = fmaxf(m, fmaxf(fabsf(float(v[k].re)), fabsf(float(v[k].im))));
+        mx[w * 64 + lane] = m;
+        __syncthreads();
+        m = fmaxf(fmaxf(mx[lane], mx[64 + lane]), fmaxf(mx[128 + lane], mx[192 + lane]));
+        if (!live) return;
+        const float inv = m > 0.f ? 1.0f / m : 0.f;
+        if (w == 0) f.norm[s] = m;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int e = 3 * w + k;
+            ((h2*)f.v)[((size_t)(e >> 2) * Vh + s) * 4 + (e & 3)] =
+                h2{(_Float16)(float(v[k].re) * inv), (_Float16)(float(v[k].im) * inv)};
+        }
+    } else {
+        if (!live) return;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int e = 3 * w + k;
+            if constexpr (P == P64) ((d2*)f.v)[(size_t)e * Vh + s] = d2{double(v[k].re), double(v[k].im)};
+            else ((f2*)f.v)[((size_t)(e >> 1) * Vh + s) * 2 + (e & 1)] = f2{float(v[k].re), float(v[k].im)};
+        }
+    }
+}
+
+// both hops along MU, every load issued before any arithmetic
+template <int MU, int PIN, int PL, int RECON, int G5IN, typename R>
+__device__ __forceinline__ void hop_pair(const Geom& g, int p, int s, const Coord& c, const void* links,
+                                         const SpinorPtr& in, cx<R> acc[4][3]) {
+    const int sf = cb_neighbour(g, c, MU, +1), sb = cb_neighbour(g, c, MU, -1);
+    LoadPlain<PIN, G5IN, R> ld{in};
+    typename LoadPlain<PIN, G5IN, R>::Raw rf, rb;
+    RawLink<PL, RECON> lf, lb;
+    ld.fetch(sf, g.Vh, rf);
+    fetch_link<PL, RECON, false>(links, MU, p, s, g.Vh, lf);
+    ld.fetch(sb, g.Vh, rb);
+    fetch_link<PL, RECON, false>(links, MU, 1 - p, sb, g.Vh, lb);
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int k = 0; k < 3; k++) acc[i][k] = {R(0), R(0)};
+    cx<R> psi[4][3], h[2][3], uh[2][3];
+    {
+        R w = ld.get(rf, psi) * R(link_unit<PL, RECON>());
+        spin_proj<MU, -1>(psi, h);
+        const M3<R> u = LinkIO<PL, RECON, R>::decode(lf);
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int a = 0; a < 3; a++)
+                uh[j][a] = cdot3(u.e[a][0], h[j][0], u.e[a][1], h[j][1], u.e[a][2], h[j][2]);
+        if (MU == 3 && c.c[3] == g.L[3] - 1) w = -w;
+        spin_recon_acc<MU, -1>(acc, uh, w);
+    }
+    {
+        R w = ld.get(rb, psi) * R(link_unit<PL, RECON>());
+        spin_proj<MU, +1>(psi, h);
+        const M3<R> u = LinkIO<PL, RECON, R>::decode(lb);
+#pragma unroll
+        for (int j = 0; j < 2; j++)
+#pragma unroll
+            for (int a = 0; a < 3; a++)
+                uh[j][a] = cdot3c(u.e[0][a], h[j][0], u.e[1][a], h[j][1], u.e[2][a], h[j][2]);
+        if (MU == 3 && c.c[3] == 0) w = -w;
+        spin_recon_acc<MU, +1>(acc, uh, w);
+    }
+}
+
+// the directions' partial sums: [direction][element][site of the block]
+template <typename R> struct SplitLds {
+    cx<R> part[4][12][64];
+    float mx[256];
+    double red[3 * 4];
+};
+
+// A block's 64 sites of one Dslash-shaped kernel (the modes of dslash_body).
+// early: leave before any load when this launch has nothing to do (batched
+// launches, where finished chains must not keep the chip busy); otherwise the
+// state is only waited for after the hops, its latency hidden behind theirs.
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+__device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb, int early,
+                                                  SplitLds<typename Real<PIN == P64 ? P64 : P32>::T>& L) {
+    typedef typename Real<PIN == P64 ? P64 : P32>::T R;
+    typedef typename Real<PX>::T RX;
+    const Geom& g = A.g;
+    StateView S{INT_MAX, 0, 0, 1, {0.0, 0.0}, 0.0, 0.0, 0.0};
+    if (A.st) S = load_state(A.st);
+    const int iter = S.base + A.iter;
+    if (A.st && (early || b >= nb)) {
+        if (A.gate ? !S.act : S.stop_at <= iter) return;
+        if constexpr (MODE == M_HOP) {
+            if (b >= nb) {
+                if (A.cgs) {
+                    cgs_state_update(A.st, S, iter, A.partial, nb, L.red);
+                } else if (A.partial) {
+                    const double pAp = sum_partials(A.partial, nb, L.red);
+                    if (threadIdx.x == 0) A.st->pAp = pAp;
+                }
+                return;
+            }
+        }
+    }
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int s_ = b * SPLIT_SITES + lane;
+    const bool live = s_ < g.Vh;
+    const int s = live ? s_ : g.Vh - 1;
+    const Coord c = cb_coords(g, A.p_out, s);
+    // the epilogue's operands, in flight beside the hops'
+    cx<R> cen[3], ph[3];
+    cx<RX> av[3], xv[3], rv[3], pv[3], sv[3];
+    if constexpr (MODE != M_HOP) load_spin<PC, R>(A.center, s, g.Vh, w, cen);
+    if constexpr (MODE == M_RESID) load_spin<PC, R>(A.aux, s, g.Vh, w, ph);
+    if constexpr (MODE == M_CGX || MODE == M_CGS) {
+        load_spin<PC, RX>(A.aux, s, g.Vh, w, av);
+        load_spin<PX, RX>(A.x, s, g.Vh, w, xv);
+        load_spin<PX, RX>(A.r, s, g.Vh, w, rv);
+    }
+    if constexpr (MODE == M_CGS) {
+        load_spin<PX, RX>(A.dir, s, g.Vh, w, pv);
+        load_spin<PX, RX>(A.adir, s, g.Vh, w, sv);
+    }
+    {
+        cx<R> acc[4][3];
+        if (w == 0) hop_pair<0, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
+        else if (w == 1) hop_pair<1, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
+        else if (w == 2) hop_pair<2, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
+        else hop_pair<3, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) L.part[w][3 * i + k][lane] = acc[i][k];
+    }
+    __syncthreads();
+    if (A.st && (A.gate ? !S.act : S.stop_at <= iter)) return;
+    cx<R> acc[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int e = 3 * w + k;
+        acc[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
+        if (A.g5out && w >= 2) acc[k] = -acc[k];
+    }
+    double nrm = 0.0, rs = 0.0, ps = 0.0;
+    if constexpr (MODE == M_HOP) {
+        store_spin<POUT, R>(A.out, s, g.Vh, w, live, acc, L.mx);
+        return;
+    } else {
+        const R k2 = R(A.kappa2);
+#pragma unroll
+        for (int k = 0; k < 3; k++) acc[k] = cen[k] - k2 * acc[k];
+        if constexpr (MODE == M_SCHUR || MODE == M_CGQ || MODE == M_RESID) {
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                if constexpr (MODE == M_RESID) acc[k] = ph[k] - acc[k];
+                nrm += double(acc[k].re) * double(acc[k].re) + double(acc[k].im) * double(acc[k].im);
+            }
+            store_spin<POUT, R>(A.out, s, g.Vh, w, live, acc, L.mx);
+        } else if constexpr (MODE == M_CGX) {
+            const RX al = RX(((iter & 1) ? S.rr[1] : S.rr[0]) / S.pAp);
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const cx<RX> ap = {RX(acc[k].re), RX(acc[k].im)};
+                xv[k] = xv[k] + al * av[k];
+                rv[k] = rv[k] - al * ap;
+                nrm += double(rv[k].re) * double(rv[k].re) + double(rv[k].im) * double(rv[k].im);
+            }
+            store_spin<PX, RX>(A.x, s, g.Vh, w, live, xv, L.mx);
+            store_spin<PX, RX>(A.r, s, g.Vh, w, live, rv, L.mx);
+        } else {
+            const RX be = RX(S.beta);
+            const RX al = RX(((iter & 1) ? S.rr[1] : S.rr[0]) / (S.pAp + S.corr));
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                pv[k].re = fma(be, pv[k].re, av[k].re);
+                pv[k].im = fma(be, pv[k].im, av[k].im);
+                sv[k].re = fma(be, sv[k].re, RX(acc[k].re));
+                sv[k].im = fma(be, sv[k].im, RX(acc[k].im));
+                xv[k] = xv[k] + al * pv[k];
+                rv[k] = rv[k] - al * sv[k];
+                nrm += double(rv[k].re) * double(rv[k].re) + double(rv[k].im) * double(rv[k].im);
+                ps += double(pv[k].re) * double(sv[k].re) + double(pv[k].im) * double(sv[k].im);
+            }
+            store_spin<PX, RX>(A.dir, s, g.Vh, w, live, pv, L.mx);
+            store_spin<PX, RX>(A.adir, s, g.Vh, w, live, sv, L.mx);
+            store_spin<PX, RX>(A.x, s, g.Vh, w, live, xv, L.mx);
+            store_spin<PX, RX>(A.r, s, g.Vh, w, live, rv, L.mx);
+            if constexpr (PC != PX) {  // the hops' copy of r, and Re<rt, s> with the stored values
+                store_spin<PC, RX>(A.aux, s, g.Vh, w, live, rv, L.mx);
+                const float m = fmaxf(fmaxf(L.mx[lane], L.mx[64 + lane]), fmaxf(L.mx[128 + lane], L.mx[192 + lane]));
+                const float inv = m > 0.f ? 1.0f / m : 0.f;
+#pragma unroll
+                for (int k = 0; k < 3; k++) {
+                    rv[k].re = RX(float((_Float16)(float(rv[k].re) * inv)) * m);
+                    rv[k].im = RX(float((_Float16)(float(rv[k].im) * inv)) * m);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 3; k++) rs += double(rv[k].re) * double(sv[k].re) + double(rv[k].im) * double(sv[k].im);
+        }
+    }
+    if (!A.partial) return;
+    if (!live) nrm = rs = ps = 0.0;
+    if constexpr (MODE == M_CGS) {
+        double v[3] = {nrm, rs, ps};
+        block_sum<3>(v, L.red);
+        if (threadIdx.x == 0) {
+            A.partial[b] = v[0];
+            A.partial[nb + b] = v[1];
+            A.partial[2 * nb + b] = v[2];
+        }
+        return;
+    }
+    double v[1] = {nrm};
+    block_sum<1>(v, L.red);
+    if (threadIdx.x == 0) A.partial[b] = v[0];
+}
+
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+__global__ void __launch_bounds__(256) k_dslash_split(DArgs A) {
+    __shared__ SplitLds<typename Real<PIN == P64 ? P64 : P32>::T> L;
+    const int nb = (A.g.Vh + SPLIT_SITES - 1) / SPLIT_SITES;
+    const int b = (int)blockIdx.x < nb ? (A.xcd ? xcd_block(blockIdx.x, nb) : (int)blockIdx.x) : blockIdx.x;
+    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>(A, b, nb, 0, L);
+}
+
 // one chain's part of a concatenated spinor field / link field
 template <int P> __device__ __forceinline__ SpinorPtr spin_off(SpinorPtr p, const ChainDesc& d) {
     if (!p.v) return p;
@@ -366,15 +635,10 @@ template <int PL, int RECON> __device__ __forceinline__ size_t link_byte_off(con
     return (size_t)d.link0 * sloppy_link_bytes(PL, RECON);
 }
 
-// batched launch: every chain of the batch with its own geometry, kappa,
-// solver state (base.st[c]) and partials slice; nsb site blocks in all, and
-// blocks past them (an M_HOP with partials) are the chains' reduction blocks
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
-__global__ void __launch_bounds__(DBS) k_dslash_b(DArgs base, const ChainDesc* __restrict__ cd, int nc, int nsb) {
-    __shared__ double lds[3 * DBS / 64];
-    const int gb = (int)blockIdx.x < nsb ? (base.xcd ? xcd_block(blockIdx.x, nsb) : (int)blockIdx.x) : blockIdx.x;
-    const int c = gb < nsb ? find_chain(cd, nc, gb, GRID_DS) : gb - nsb;
-    const ChainDesc& d = cd[c];
+// One chain's arguments of a batched launch: its own geometry, kappa, solver
+// state (base.st[c]) and partials slice.
+template <int PIN, int PC, int POUT, int PX, int PL, int RECON>
+__device__ __forceinline__ DArgs chain_args(const DArgs& base, const ChainDesc& d, int c) {
     DArgs A = base;
     A.g = d.g;
     A.kappa2 = d.kappa * d.kappa;
@@ -387,8 +651,31 @@ __global__ void __launch_bounds__(DBS) k_dslash_b(DArgs base, const ChainDesc* _
     A.r = spin_off<PX>(base.r, d);
     A.partial = base.partial ? base.partial + d.blk0[GRID_DS] : nullptr;
     A.st = base.st ? base.st + c : nullptr;
-    const int b = gb < nsb ? gb - d.blk0[GRID_DS] : d.nblk[GRID_DS];
-    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, b, d.nblk[GRID_DS], lds);
+    return A;
+}
+
+// batched launch over the chains of one block table (ds_map): nsb site blocks,
+// and past them (an M_HOP with partials) the chains' reduction blocks
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+__global__ void __launch_bounds__(DBS) k_dslash_b(DArgs base, const ChainDesc* __restrict__ cd,
+                                                  const int2* __restrict__ map, int nsb) {
+    __shared__ double lds[3 * DBS / 64];
+    const int gb = (int)blockIdx.x < nsb ? (base.xcd ? xcd_block(blockIdx.x, nsb) : (int)blockIdx.x) : blockIdx.x;
+    const int2 m = map[gb];
+    const ChainDesc& d = cd[m.x];
+    const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
+    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, m.y, d.nblk[GRID_DS], lds);
+}
+
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+__global__ void __launch_bounds__(256) k_dslash_split_b(DArgs base, const ChainDesc* __restrict__ cd,
+                                                        const int2* __restrict__ map, int nsb) {
+    __shared__ SplitLds<typename Real<PIN == P64 ? P64 : P32>::T> L;
+    const int gb = (int)blockIdx.x < nsb ? (base.xcd ? xcd_block(blockIdx.x, nsb) : (int)blockIdx.x) : blockIdx.x;
+    const int2 m = map[gb];
+    const ChainDesc& d = cd[m.x];
+    const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
+    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>(A, m.y, d.nblk[GRID_DS], 1, L);
 }
 
 // First kernel of a CG iteration: p = r + beta p, stored in p's precision.
@@ -441,14 +728,71 @@ __global__ void __launch_bounds__(DBS) k_cg_p(int Vh, SpinorPtr p, SpinorPtr r, 
 }
 
 template <int PP, int PX>
-__global__ void __launch_bounds__(DBS) k_cg_p_b(const ChainDesc* __restrict__ cd, int nc, SpinorPtr p, SpinorPtr r,
-                                                CGState* st, const double* partial, int xcd, int j) {
+__global__ void __launch_bounds__(DBS) k_cg_p_b(const ChainDesc* __restrict__ cd, const int2* __restrict__ map,
+                                                SpinorPtr p, SpinorPtr r, CGState* st, const double* partial, int xcd,
+                                                int j) {
     __shared__ double lds[DBS / 64];
-    const int gb = xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-    const int c = find_chain(cd, nc, gb, GRID_DS);
-    const ChainDesc& d = cd[c];
-    cg_p_body<PP, PX>(d.g.Vh, spin_off<PP>(p, d), spin_off<PX>(r, d), st + c, partial + d.blk0[GRID_DS], j,
-                      gb - d.blk0[GRID_DS], d.nblk[GRID_DS], lds);
+    const int2 m = map[xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x];
+    const ChainDesc& d = cd[m.x];
+    cg_p_body<PP, PX>(d.g.Vh, spin_off<PP>(p, d), spin_off<PX>(r, d), st + m.x, partial + d.blk0[GRID_DS], j, m.y,
+                      d.nblk[GRID_DS], lds);
+}
+
+// The same with a block's four waves sharing 64 sites, one spin each.
+template <int PP, int PX>
+__device__ __forceinline__ void cg_p_split_body(int Vh, const SpinorPtr& p, const SpinorPtr& r, CGState* st,
+                                                const double* partial, int j, int b, int nb, double* lds, float* mx) {
+    typedef typename Real<PP == P64 ? P64 : P32>::T R;
+    const StateView S = load_state(st);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int s_ = b * SPLIT_SITES + (threadIdx.x & 63);
+    const bool live = s_ < Vh;
+    const int s = live ? s_ : Vh - 1;
+    cx<R> rv[3], pv[3];
+    load_spin<PX, R>(r, s, Vh, w, rv);
+    load_spin<PP, R>(p, s, Vh, w, pv);
+    const int iter = S.base + j;
+    if (S.stop_at <= iter) return;
+    double beta = S.beta;
+    if (iter != S.base0) {
+        const double rr = sum_partials(partial, nb, lds);
+        const bool stop = rr <= S.rr_stop;
+        beta = rr / ((iter & 1) ? S.rr[0] : S.rr[1]);  // |r|^2 of iteration iter - 1
+        if (b == 0 && threadIdx.x == 0) {
+            st->rr[iter & 1] = rr;
+            if (stop) st->stop_at = iter;
+            else st->beta = beta;
+        }
+        if (stop) return;
+    }
+    const R be = R(beta);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        pv[k].re = fma(be, pv[k].re, rv[k].re);
+        pv[k].im = fma(be, pv[k].im, rv[k].im);
+    }
+    store_spin<PP, R>(p, s, Vh, w, live, pv, mx);
+}
+
+template <int PP, int PX>
+__global__ void __launch_bounds__(256) k_cg_p_split(int Vh, SpinorPtr p, SpinorPtr r, CGState* st,
+                                                    const double* partial, int xcd, int j) {
+    __shared__ double lds[4];
+    __shared__ float mx[256];
+    cg_p_split_body<PP, PX>(Vh, p, r, st, partial, j, xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x,
+                            gridDim.x, lds, mx);
+}
+
+template <int PP, int PX>
+__global__ void __launch_bounds__(256) k_cg_p_split_b(const ChainDesc* __restrict__ cd, const int2* __restrict__ map,
+                                                      SpinorPtr p, SpinorPtr r, CGState* st, const double* partial,
+                                                      int xcd, int j) {
+    __shared__ double lds[4];
+    __shared__ float mx[256];
+    const int2 m = map[xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x];
+    const ChainDesc& d = cd[m.x];
+    cg_p_split_body<PP, PX>(d.g.Vh, spin_off<PP>(p, d), spin_off<PX>(r, d), st + m.x, partial + d.blk0[GRID_DS], j,
+                            m.y, d.nblk[GRID_DS], lds, mx);
 }
 
 // Last node of a CG batch: fold the |r|^2 partials of the batch's last
@@ -836,6 +1180,9 @@ static int links_streamed(const FermionOp& op, long nlinks) {
     return per * (double)nlinks > kL2Bytes ? 1 : 0;
 }
 
+// blocks (= partials) of the Dslash-shaped kernels on a lattice
+static int ds_blocks(const Ctx& c, int Vh) { return nblk(Vh, ds_sites(c, Vh)); }
+
 template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
 static void launch_dslash_nt(Ctx& c, bool nt, int nb, DArgs& a) {
     if (nt) hipLaunchKernelGGL((k_dslash<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, true>), dim3(nb), dim3(c.ds_bs), 0, c.stream, a);
@@ -843,11 +1190,31 @@ static void launch_dslash_nt(Ctx& c, bool nt, int nb, DArgs& a) {
 }
 
 template <int MODE, int PIN, int PC, int POUT, int PX, int G5IN>
-static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a) {
+static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = false) {
     const bool nt = links_streamed(op, 4L * a.g.V);
     a.xcd = c.ds_xcd;
     // an M_HOP inside CG (state and partials) carries the pAp reduction block
-    int nb = nblk(a.g.Vh, c.ds_bs) + ((MODE == M_HOP && a.st && a.partial) ? 1 : 0);
+    const int extra = (MODE == M_HOP && a.st && a.partial) ? 1 : 0;
+    if (!plain && site_split(a.g.Vh)) {
+        const dim3 nb(nblk(a.g.Vh, SPLIT_SITES) + extra), bs(256);
+        if constexpr (PIN == P64) {
+            if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
+            hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>), nb, bs, 0, c.stream, a);
+        } else {
+            if (op.prec == P32 && op.recon == 18)
+                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P32, 18, G5IN>), nb, bs, 0, c.stream, a);
+            else if (op.prec == P32)
+                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P32, 12, G5IN>), nb, bs, 0, c.stream, a);
+            else if (op.prec == P16 && op.recon == 18)
+                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P16, 18, G5IN>), nb, bs, 0, c.stream, a);
+            else if (op.prec == P16)
+                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P16, 12, G5IN>), nb, bs, 0, c.stream, a);
+            else throw Error(-1, "sloppy spinors need sloppy links");
+        }
+        FGI_LAUNCH_CHECK();
+        return;
+    }
+    int nb = nblk(a.g.Vh, c.ds_bs) + extra;
     if constexpr (PIN == P64) {
         if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
         launch_dslash_nt<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>(c, nt, nb, a);
@@ -872,13 +1239,14 @@ static DArgs base_args(const FermionOp& op, int p_out) {
 
 static CGState* dev_state(Ctx& c) { return (CGState*)c.state.get(sizeof(CGState)); }
 
-void dslash(Ctx& c, const FermionOp& op, int out_parity, int prec_in, SpinorPtr in, int prec_out, SpinorPtr out) {
+void dslash(Ctx& c, const FermionOp& op, int out_parity, int prec_in, SpinorPtr in, int prec_out, SpinorPtr out,
+            bool plain) {
     DArgs a = base_args(op, out_parity);
     a.in = in;
     a.out = out;
-    if (prec_in == P64 && prec_out == P64) launch_dslash<M_HOP, P64, P64, P64, P64, 0>(c, op, a);
-    else if (prec_in == P32 && prec_out == P32) launch_dslash<M_HOP, P32, P32, P32, P32, 0>(c, op, a);
-    else if (prec_in == P16 && prec_out == P16) launch_dslash<M_HOP, P16, P16, P16, P32, 0>(c, op, a);
+    if (prec_in == P64 && prec_out == P64) launch_dslash<M_HOP, P64, P64, P64, P64, 0>(c, op, a, plain);
+    else if (prec_in == P32 && prec_out == P32) launch_dslash<M_HOP, P32, P32, P32, P32, 0>(c, op, a, plain);
+    else if (prec_in == P16 && prec_out == P16) launch_dslash<M_HOP, P16, P16, P16, P32, 0>(c, op, a, plain);
     else throw Error(-1, "dslash: unsupported precision pair");
 }
 
@@ -1121,7 +1489,7 @@ static double true_residual(Ctx& c, const FermionOp& op64, const d2* phi, const 
     b.g5out = 1;
     b.partial = partial_buf(c, g);
     launch_dslash<M_RESID, P64, P64, P64, P64, 0>(c, op64, b);
-    final_sum(c, b.partial, nblk(g.Vh, c.ds_bs), scal + 1);
+    final_sum(c, b.partial, ds_blocks(c, g.Vh), scal + 1);
     FGI_HIP(hipMemcpyAsync(c.host_scal + 1, scal + 1, sizeof(double), hipMemcpyDeviceToHost, c.stream));
     FGI_HIP(hipStreamSynchronize(c.stream));
     return c.host_scal[1];
@@ -1147,8 +1515,12 @@ static void cg_iteration(Ctx& c, const FermionOp& ops, const CGVecs& v, int j) {
     CGState* st = dev_state(c);
     double* part = partial_buf(c, *ops.g);
     const int Vh = ops.g->Vh;
-    hipLaunchKernelGGL((k_cg_p<PP, PX>), dim3(nblk(Vh, c.ds_bs)), dim3(c.ds_bs), 0, c.stream, Vh, v.p, v.r, st,
-                       (const double*)part, nblk(Vh, c.ds_bs), c.ds_xcd, j);
+    if (site_split(Vh))
+        hipLaunchKernelGGL((k_cg_p_split<PP, PX>), dim3(ds_blocks(c, Vh)), dim3(256), 0, c.stream, Vh, v.p, v.r, st,
+                           (const double*)part, c.ds_xcd, j);
+    else
+        hipLaunchKernelGGL((k_cg_p<PP, PX>), dim3(nblk(Vh, c.ds_bs)), dim3(c.ds_bs), 0, c.stream, Vh, v.p, v.r, st,
+                           (const double*)part, nblk(Vh, c.ds_bs), c.ds_xcd, j);
     FGI_LAUNCH_CHECK();
     {
         DArgs a = base_args(ops, 1);
@@ -1251,7 +1623,7 @@ static void cg_iteration_cgs(Ctx& c, const FermionOp& ops, const CGVecs& v, int 
 // the M_CGS partials of the vectors as they stand (start of a run, reliable update)
 template <int PP, int PX>
 static void cgs_partials(Ctx& c, const Geom& g, const CGVecs& v) {
-    hipLaunchKernelGGL((k_cgs_partials<PP, PX>), dim3(nblk(g.Vh, c.ds_bs)), dim3(c.ds_bs), 0, c.stream, g.Vh, v.r,
+    hipLaunchKernelGGL((k_cgs_partials<PP, PX>), dim3(ds_blocks(c, g.Vh)), dim3(ds_sites(c, g.Vh)), 0, c.stream, g.Vh, v.r,
                        v.rt, v.pf, v.sf, partial_buf(c, g));
     FGI_LAUNCH_CHECK();
 }
@@ -1264,7 +1636,7 @@ static void cg_batch_eager(Ctx& c, const FermionOp& ops, const CGVecs& v, int B)
         else cg_iteration<PP, PX>(c, ops, v, j);
     }
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(DBS), 0, c.stream, dev_state(c), (const double*)partial_buf(c, *ops.g),
-                       nblk(ops.g->Vh, c.ds_bs), B);
+                       ds_blocks(c, ops.g->Vh), B);
     FGI_LAUNCH_CHECK();
 }
 
@@ -1546,28 +1918,33 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
 }
 
 // ====================================================== batched chains ======
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+static void launch_dslash_b_rec(Ctx& c, const Batch& B, DArgs& a) {
+    // an M_HOP inside CG (states and partials) carries one pAp reduction block per chain
+    const bool red = MODE == M_HOP && a.st && a.partial;
+    for (int k = 0; k < 2; k++) {
+        const int nsb = B.ds_blk[k];
+        if (!nsb) continue;
+        const dim3 nb(nsb + (red ? B.ds_nc[k] : 0));
+        if (k == DS_SPLIT)
+            hipLaunchKernelGGL((k_dslash_split_b<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>), nb, dim3(256), 0,
+                               c.stream, a, B.cd, B.ds_map[k], nsb);
+        else
+            hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>), nb, dim3(c.ds_bs), 0, c.stream,
+                               a, B.cd, B.ds_map[k], nsb);
+    }
+}
+
 template <int MODE, int PIN, int PC, int POUT, int PX, int G5IN>
 static void launch_dslash_b(Ctx& c, const Batch& B, const FermionOp& op, DArgs& a) {
-    const int nsb = B.nblk[GRID_DS];
     a.xcd = c.ds_xcd;
-    // an M_HOP inside CG (states and partials) carries one pAp reduction block per chain
-    const int nb = nsb + ((MODE == M_HOP && a.st && a.partial) ? B.nc : 0);
     if constexpr (PIN == P64) {
-        hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>), dim3(nb), dim3(c.ds_bs), 0, c.stream, a,
-                           B.cd, B.nc, nsb);
+        launch_dslash_b_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>(c, B, a);
     } else {
-        if (op.prec == P32 && op.recon == 18)
-            hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, P32, 18, G5IN>), dim3(nb), dim3(c.ds_bs), 0, c.stream,
-                               a, B.cd, B.nc, nsb);
-        else if (op.prec == P32)
-            hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, P32, 12, G5IN>), dim3(nb), dim3(c.ds_bs), 0, c.stream,
-                               a, B.cd, B.nc, nsb);
-        else if (op.recon == 18)
-            hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, P16, 18, G5IN>), dim3(nb), dim3(c.ds_bs), 0, c.stream,
-                               a, B.cd, B.nc, nsb);
-        else
-            hipLaunchKernelGGL((k_dslash_b<MODE, PIN, PC, POUT, PX, P16, 12, G5IN>), dim3(nb), dim3(c.ds_bs), 0, c.stream,
-                               a, B.cd, B.nc, nsb);
+        if (op.prec == P32 && op.recon == 18) launch_dslash_b_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN>(c, B, a);
+        else if (op.prec == P32) launch_dslash_b_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN>(c, B, a);
+        else if (op.recon == 18) launch_dslash_b_rec<MODE, PIN, PC, POUT, PX, P16, 18, G5IN>(c, B, a);
+        else launch_dslash_b_rec<MODE, PIN, PC, POUT, PX, P16, 12, G5IN>(c, B, a);
     }
     FGI_LAUNCH_CHECK();
 }
@@ -1668,8 +2045,12 @@ static void true_residual_b(Ctx& c, const Batch& B, const FermionOp& op64, const
 template <int PP, int PX>
 static void cg_iteration_b(Ctx& c, const Batch& B, const FermionOp& ops, const CGVecs& v, int j, CGState* st) {
     double* part = partial_buf(c, B);
-    hipLaunchKernelGGL((k_cg_p_b<PP, PX>), dim3(B.nblk[GRID_DS]), dim3(c.ds_bs), 0, c.stream, B.cd, B.nc, v.p, v.r, st,
-                       (const double*)part, c.ds_xcd, j);
+    if (B.ds_blk[DS_SPLIT])
+        hipLaunchKernelGGL((k_cg_p_split_b<PP, PX>), dim3(B.ds_blk[DS_SPLIT]), dim3(256), 0, c.stream, B.cd,
+                           B.ds_map[DS_SPLIT], v.p, v.r, st, (const double*)part, c.ds_xcd, j);
+    if (B.ds_blk[DS_PLAIN])
+        hipLaunchKernelGGL((k_cg_p_b<PP, PX>), dim3(B.ds_blk[DS_PLAIN]), dim3(c.ds_bs), 0, c.stream, B.cd,
+                           B.ds_map[DS_PLAIN], v.p, v.r, st, (const double*)part, c.ds_xcd, j);
     FGI_LAUNCH_CHECK();
     {
         DArgs a = base_args_b(ops, 1);
@@ -1826,9 +2207,10 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
     GraphEntry* ge = nullptr;
     if (c.use_graphs) {
         // the grid sizes are baked into the graph (the chain table is read at run time)
-        char key[320];
-        snprintf(key, sizeof key, "bcg/%d/%d/%p/%d/%d/%d/%d/%ld/%p/%p/%p/%p/%p/%p/%p/%p/%p/%d/%d/%d", PP, PX,
-                 ops.links, ops.prec, ops.recon, nc, B.nblk[GRID_DS], B.sites, (void*)B.cd, v.x.v, v.r.v, v.p.v,
+        char key[400];
+        snprintf(key, sizeof key, "bcg/%d/%d/%p/%d/%d/%d/%d/%d/%p/%p/%ld/%p/%p/%p/%p/%p/%p/%p/%p/%p/%d/%d/%d", PP, PX,
+                 ops.links, ops.prec, ops.recon, nc, B.ds_blk[0], B.ds_blk[1], (void*)B.ds_map[0], (void*)B.ds_map[1],
+                 B.sites, (void*)B.cd, v.x.v, v.r.v, v.p.v,
                  v.q.v, v.t.v, (void*)v.p.norm, (void*)st, (void*)part, Bi, c.ds_bs, c.ds_xcd);
         ge = &cached_graph(c, key, [&] { cg_batch_b<PP, PX>(c, B, ops, v, Bi, st); });
     }

@@ -149,6 +149,21 @@ struct Ctx {
     d2* noalloc_scratch = nullptr;
 };
 
+// Lattices of at most SPLIT_MAX_VH even sites run the Dslash-shaped kernels
+// with each site shared by four waves (k_dslash_split), SPLIT_SITES sites per
+// block.  The line lies where one thread per site reaches half a wave per SIMD.
+// A CG iteration in us, one thread per site and split (FP64, MP32, MP16/18;
+// 64-iteration solves, the call's other work included): 2048 even sites 41.6 ->
+// 27.4, 46.0 -> 37.3, 42.8 -> 36.4; 15120: 51.8 -> 33.5, 46.0 -> 35.6, 42.2 ->
+// 33.6; 32768: 80.0 -> 57.2, 52.6 -> 46.7, 45.6 -> 40.9; 65536: 105.4 -> 104.3,
+// 71.2 -> 70.0, 50.2 -> 52.3.
+constexpr int SPLIT_SITES = 64;
+constexpr int SPLIT_MAX_VH = 32768;
+inline bool site_split(int Vh) { return Vh <= SPLIT_MAX_VH; }
+// sites per block of the Dslash-shaped kernels on a lattice of Vh even sites
+inline int ds_sites(const Ctx& c, int Vh) { return site_split(Vh) ? SPLIT_SITES : c.ds_bs; }
+enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
+
 // A batch of independent chains: their descriptors on the device and the
 // total block counts of the Vh-, V- and 4V-sized grids over all of them.
 struct Batch {
@@ -156,6 +171,12 @@ struct Batch {
     int nc = 0;
     int nblk[4] = {0, 0, 0, 0};
     long sites = 0, vol = 0, links = 0;  // totals: sum Vh, sum V, sum 4V
+    // Dslash-shaped launches, one per DsKind that has chains: block -> (chain,
+    // block of the chain), then one (chain, its block count) per chain for the
+    // reduction blocks
+    const int2* ds_map[2] = {nullptr, nullptr};
+    int ds_blk[2] = {0, 0};   // site blocks
+    int ds_nc[2] = {0, 0};    // chains
 };
 
 // Block-partial buffer of the reductions, with room for every grid launched
@@ -251,8 +272,10 @@ struct FermionOp {
     int prec, recon;     // link storage precision / reconstruction
 };
 // out_{1-p} = D_{(1-p) p} in_p  (hopping term between parities)
+// plain: always with the summation order of the halo hop (one thread per site),
+// whatever the lattice size
 void dslash(Ctx&, const FermionOp&, int out_parity, int prec_in, SpinorPtr in, int prec_out,
-            SpinorPtr out);
+            SpinorPtr out, bool plain = false);
 // out_e = [g5] (in_e - kappa^2 D_eo t_o)  where t_o = D_oe in_e is computed too
 void mhat(Ctx&, const FermionOp&, int prec, SpinorPtr in_e, SpinorPtr tmp_o, SpinorPtr out_e,
           int dagger);
