@@ -146,7 +146,7 @@ enum Mode {
     M_SCHUR = 1,  // out = center - kappa^2 [g5] acc          [|out|^2 partials]
     M_CGQ = 2,    // CG: q = p - kappa^2 acc (center p), |q|^2 partials (pAp)
     M_CGX = 3,    // CG: Ap = q - kappa^2 g5 acc; x += alpha p; r -= alpha Ap; |r|^2 partials
-    M_RESID = 4,  // r = aux - (center - kappa^2 g5 acc), |r|^2 partials
+    M_RESID = 4,  // r = aux - (center - kappa^2 g5 acc), |r|^2 partials; x = 0 when given
     M_CGS = 5     // CG, Chronopoulos-Gear form: w = q - kappa^2 g5 acc; p = rt + beta p;
                   // s = w + beta s; x += alpha p; r -= alpha s; the hops' copy rt of r;
                   // |r|^2, Re<rt, s>, Re<p, s> partials
@@ -263,6 +263,13 @@ __device__ __forceinline__ void dslash_body(const DArgs& A, int b, int nb, doubl
                         nrm += double(acc[i][k].re) * double(acc[i][k].re) + double(acc[i][k].im) * double(acc[i][k].im);
                     }
                 SpinorIO<POUT, R>::store(A.out, s, g.Vh, acc);
+                if (A.x.v) {
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+#pragma unroll
+                        for (int k = 0; k < 3; k++) acc[i][k] = {R(0), R(0)};
+                    SpinorIO<POUT, R>::store(A.x, s, g.Vh, acc);
+                }
             } else if (MODE == M_CGX) {
                 typedef typename Real<PX>::T RX;
                 const RX al = RX(((iter & 1) ? S.rr[1] : S.rr[0]) / S.pAp);
@@ -549,6 +556,11 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
                 nrm += double(acc[k].re) * double(acc[k].re) + double(acc[k].im) * double(acc[k].im);
             }
             store_spin<POUT, R>(A.out, s, g.Vh, w, live, acc, L.mx);
+            if (MODE == M_RESID && A.x.v) {
+#pragma unroll
+                for (int k = 0; k < 3; k++) acc[k] = {R(0), R(0)};
+                store_spin<POUT, R>(A.x, s, g.Vh, w, live, acc, L.mx);
+            }
         } else if constexpr (MODE == M_CGX) {
             const RX al = RX(((iter & 1) ? S.rr[1] : S.rr[0]) / S.pAp);
 #pragma unroll
@@ -812,9 +824,57 @@ __device__ __forceinline__ void advance_body(CGState* st, const double* partial,
     if (threadIdx.x == 0) st->base = it;
 }
 
-__global__ void __launch_bounds__(DBS) k_advance(CGState* st, const double* partial, int nb, int n) {
+// seen: the pinned host copy of the state that the host reads when it polls
+__global__ void __launch_bounds__(DBS) k_advance(CGState* st, const double* partial, int nb, int n, CGState* seen) {
     __shared__ double lds[DBS / 64];
     advance_body(st, partial, nb, n, lds);
+    if (threadIdx.x == 0) *seen = *st;
+}
+
+// The scalars of a solve that the host does not have to wait for: tolerances
+// in, |phi|^2 and the last true residual out (pinned host memory).
+struct CGRun {
+    double tol2, ru2;      // tol^2, ru_delta^2 (0: the inner run goes straight to the target)
+    const double* bb;      // |phi|^2 on the device
+    double* seen;          // host: [0] |phi|^2, [1] |r|^2 of the last true residual
+};
+__device__ __forceinline__ double inner_stop(const CGRun& C, double rr, double target) {
+    const double s = C.ru2 * rr;
+    return C.ru2 > 0.0 && s > target ? s : target;
+}
+
+// First state of a run: rr0 = |phi|^2, or (part) the |r|^2 of a starting point.
+// A zero phi or a starting point within the target leaves a finished run.
+__global__ void __launch_bounds__(DBS) k_cg_start(CGState* st, CGRun C, const double* part, int nb) {
+    __shared__ double lds[DBS / 64];
+    const double rr0 = part ? sum_partials(part, nb, lds) : *C.bb;
+    if (threadIdx.x) return;
+    const double target = C.tol2 * *C.bb;
+    CGState h{};
+    h.rr[0] = rr0;
+    h.rr[1] = rr0;   // the CG form's first beta divides by it (p = s = 0 there, so its value does not matter)
+    h.rr_stop = inner_stop(C, rr0, target);
+    const bool there = *C.bb == 0.0 || (part && rr0 <= target) || !isfinite(rr0);
+    h.stop_at = there ? 0 : INT_MAX;
+    *st = h;
+    C.seen[0] = *C.bb;
+    C.seen[1] = rr0;
+}
+
+// After a true residual at iteration kend: the run continues from it like a
+// start that keeps the direction, or is finished.
+__global__ void __launch_bounds__(DBS) k_cg_restart(CGState* st, CGRun C, const double* part, int nb, int kend) {
+    __shared__ double lds[DBS / 64];
+    const double rr = sum_partials(part, nb, lds);
+    if (threadIdx.x) return;
+    const double target = C.tol2 * *C.bb;
+    st->beta = rr / st->rr[(kend - 1) & 1];
+    st->rr[kend & 1] = rr;
+    st->rr_stop = inner_stop(C, rr, target);
+    st->stop_at = rr <= target || !isfinite(rr) ? 0 : INT_MAX;
+    st->base = kend;
+    st->base0 = kend;
+    C.seen[1] = rr;
 }
 
 // one block per chain
@@ -885,9 +945,6 @@ __global__ void __launch_bounds__(DBS) k_cgs_partials(int Vh, SpinorPtr r, Spino
     }
 }
 
-__global__ void k_set_state(CGState* st, CGState v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *st = v;
-}
 
 __global__ void k_zero(size_t n, double* p) {
     size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1457,25 +1514,23 @@ void hop_oe_g5_p32(Ctx& c, const FermionOp& op32, void* in_e, void* out_o) {
 }
 
 // ---------------------------------------------------------------- CG ------
-static double norm2_sync(Ctx& c, const Geom& g, const d2* v) {
+// |v|^2 into the device scalar out
+static void norm2(Ctx& c, const Geom& g, const d2* v, double* out) {
     double* part = partial_buf(c, g);
-    double* scal = (double*)c.scal.get(sizeof(double) * 64);
     int nb = nblk(g.Vh, DBS);
     hipLaunchKernelGGL(k_norm2_partials, dim3(nb), dim3(DBS), 0, c.stream, g.Vh, v, part);
     FGI_LAUNCH_CHECK();
-    final_sum(c, part, nb, scal);
-    FGI_HIP(hipMemcpyAsync(c.host_scal, scal, sizeof(double), hipMemcpyDeviceToHost, c.stream));
-    FGI_HIP(hipStreamSynchronize(c.stream));
-    return c.host_scal[0];
+    final_sum(c, part, nb, out);
 }
 
-// r64 = phi - Mhat^+ Mhat X (FP64), returns |r64|^2
-static double true_residual(Ctx& c, const FermionOp& op64, const d2* phi, const d2* X, d2* r64) {
+// r = phi - Mhat^+ Mhat X in FP64, stored in r's precision PR, and its |r|^2
+// partials (returns their number); x0: a vector of the same precision to clear
+template <int PR>
+static int true_residual(Ctx& c, const FermionOp& op64, const d2* phi, const d2* X, SpinorPtr r, SpinorPtr x0) {
     const Geom& g = *op64.g;
     size_t n = sizeof(d2) * 12 * (size_t)g.Vh;
     d2* t = (d2*)c.tmp_o.get(n);
     d2* q = (d2*)c.cg_q.get(n);
-    double* scal = (double*)c.scal.get(sizeof(double) * 64);
     mhat(c, op64, P64, sp(X), sp(t), sp(q), 0);  // q = Mhat X
     DArgs a = base_args(op64, 1);                // t = D_oe g5 q
     a.in = sp(q);
@@ -1485,14 +1540,12 @@ static double true_residual(Ctx& c, const FermionOp& op64, const d2* phi, const 
     b.in = sp(t);
     b.center = sp(q);
     b.aux = sp(phi);
-    b.out = sp(r64);
+    b.out = r;
+    b.x = x0;
     b.g5out = 1;
     b.partial = partial_buf(c, g);
-    launch_dslash<M_RESID, P64, P64, P64, P64, 0>(c, op64, b);
-    final_sum(c, b.partial, ds_blocks(c, g.Vh), scal + 1);
-    FGI_HIP(hipMemcpyAsync(c.host_scal + 1, scal + 1, sizeof(double), hipMemcpyDeviceToHost, c.stream));
-    FGI_HIP(hipStreamSynchronize(c.stream));
-    return c.host_scal[1];
+    launch_dslash<M_RESID, P64, P64, PR, P64, 0>(c, op64, b);
+    return ds_blocks(c, g.Vh);
 }
 
 struct CGVecs {
@@ -1636,7 +1689,7 @@ static void cg_batch_eager(Ctx& c, const FermionOp& ops, const CGVecs& v, int B)
         else cg_iteration<PP, PX>(c, ops, v, j);
     }
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(DBS), 0, c.stream, dev_state(c), (const double*)partial_buf(c, *ops.g),
-                       ds_blocks(c, ops.g->Vh), B);
+                       ds_blocks(c, ops.g->Vh), B, c.host_state);
     FGI_LAUNCH_CHECK();
 }
 
@@ -1769,23 +1822,21 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     const Geom& g = *op64.g;
     const size_t n64 = sizeof(d2) * 12 * (size_t)g.Vh;
     CGResult res{0, 0, 0.0, 0};
-    double bb = norm2_sync(c, g, phi);
-    if (!guess || bb == 0.0) zero_spinor(c, g, X, P64);
-    if (bb == 0.0) {
-        res.converged = 1;
-        return res;
-    }
-    const double target = tol * tol * bb;
+    CGState* st = dev_state(c);
+    double* scal = (double*)c.scal.get(sizeof(double) * 64);
+    norm2(c, g, phi, scal);
+    const CGRun run{tol * tol, PX == P64 ? 0.0 : c.ru_delta * c.ru_delta, scal, c.host_scal};
     d2* r64 = (d2*)c.cg_r.get(n64);
-    double rr0 = bb;  // |r|^2 of the starting point
+    auto start = [&](const double* part, int nb) {
+        hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(DBS), 0, c.stream, st, run, part, nb);
+        FGI_LAUNCH_CHECK();
+    };
     if (guess) {
-        rr0 = true_residual(c, op64, phi, X, r64);
-        if (!std::isfinite(rr0)) throw Error(-4, "CG: non-finite residual of the starting point");
-        if (rr0 <= target) {
-            res.converged = 1;
-            res.rel_resid = std::sqrt(rr0 / bb);
-            return res;
-        }
+        const int nb = true_residual<P64>(c, op64, phi, X, sp(r64), SpinorPtr{});
+        start(partial_buf(c, g), nb);
+    } else {
+        zero_spinor(c, g, X, P64);
+        start(nullptr, 0);
     }
     const d2* r_start = guess ? r64 : phi;
     CGVecs v{};   // every field null until set: the graph key reads them all
@@ -1826,69 +1877,86 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
         }
         cgs_partials<PP, PX>(c, g, v);
     }
-    CGState* st = dev_state(c);
-    CGState h{};
-    h.rr[0] = rr0;
-    h.rr[1] = rr0;   // the CG form's first beta divides by it (p = s = 0 there, so its value does not matter)
-    h.rr_stop = (PX == P64) ? target : std::max(c.ru_delta * c.ru_delta * rr0, target);
-    h.beta = 0.0;
-    h.stop_at = INT_MAX;
-    h.base = 0;
-    h.base0 = 0;
-    hipLaunchKernelGGL(k_set_state, dim3(1), dim3(64), 0, c.stream, st, h);
-    FGI_LAUNCH_CHECK();
     const bool prof = c.profile && (c.profile_prec < 0 || c.profile_prec == PP);
     const int B = c.cg_batch;
     GraphEntry* ge = nullptr;
     if (c.use_graphs)
         ge = &cached_graph(c, graph_key<PP, PX>("cg", c, ops, v, B), [&] { cg_batch_eager<PP, PX>(c, ops, v, B); });
-    int k = 0;  // iteration index of the next batch
+    // The host launches as many iterations as the decay of |r|^2 so far says the
+    // inner run still needs, then waits once for the state that k_advance leaves
+    // in pinned memory; a run whose end is not the solve's goes on from its true
+    // residual without the host (k_cg_restart).  Fixed batches of 8 left a third
+    // of the launches empty where a run takes ten iterations, and each run
+    // waited twice.  The iterates do not depend on the counts.
+    int k = 0, base0 = 0;   // iterations launched so far; start of the current inner run
+    int kcap = B * ((maxiter + B - 1) / B);   // where an unfinished run is cut off: whole batches from base0
+    int n = std::min(std::min(B, 8), kcap);
+    double rr_first = 0.0;
     for (;;) {
-        if (ge) FGI_HIP(hipGraphLaunch(ge->exec, c.stream));
-        else cg_batch_eager<PP, PX>(c, ops, v, B);
-        FGI_HIP(hipMemcpyAsync(c.host_state, st, sizeof(CGState), hipMemcpyDeviceToHost, c.stream));
+        for (int left = n; left > 0;) {
+            const int m = std::min(left, B);
+            if (ge && m == B) FGI_HIP(hipGraphLaunch(ge->exec, c.stream));
+            else cg_batch_eager<PP, PX>(c, ops, v, m);
+            left -= m;
+        }
         FGI_HIP(hipStreamSynchronize(c.stream));
         const CGState hs = *c.host_state;
-        const int kend = hs.stop_at <= k + B ? hs.stop_at : k + B;
-        bool inner_done = hs.stop_at <= kend;
-        if (inner_done || kend >= maxiter) {
+        const double bb = c.host_scal[0], rr_true = c.host_scal[1], target = tol * tol * bb;
+        if (!std::isfinite(rr_true))
+            throw Error(-4, guess && !base0 ? "CG: non-finite residual of the starting point" : "CG: non-finite residual");
+        if (bb == 0.0) {   // phi = 0: the solution is 0, whatever the start
+            if (guess) zero_spinor(c, g, X, P64);
+            res.converged = 1;
+            return res;
+        }
+        if ((guess || base0) && rr_true <= target) {   // the last true residual was there already
+            res.converged = 1;
+            res.rel_resid = std::sqrt(rr_true / bb);
+            if (!base0) return res;
+            res.reliable_updates--;
+            break;
+        }
+        if (rr_first == 0.0) rr_first = rr_true;
+        const int kend = hs.stop_at <= k + n ? hs.stop_at : k + n;
+        const bool inner_done = hs.stop_at <= kend;
+        k = kend;
+        const double now = hs.rr[kend & 1];
+        double stop = hs.rr_stop;
+        if (inner_done || kend >= kcap) {
             if (PX != P64) {
                 hipLaunchKernelGGL((k_add_to64<PX>), dim3(nblk(g.Vh, DBS)), dim3(DBS), 0, c.stream, g.Vh, v.x, sp(X));
                 FGI_LAUNCH_CHECK();
             }
-            double rr = true_residual(c, op64, phi, X, r64);
-            res.iters = kend;
-            res.rel_resid = std::sqrt(rr / bb);
-            if (!std::isfinite(rr)) throw Error(-4, "CG: non-finite residual");
-            if (rr <= target) {
-                res.converged = 1;
-                break;
-            }
-            if (kend >= maxiter) break;
             // reliable update: continue from the true residual, keep the direction
-            res.reliable_updates++;
-            if (PX != P64) {
-                convert<P64, PX>(c, g, sp(r64), v.r);
-                zero_spinor(c, g, v.x.v, P32);
+            const int nb = true_residual<PX>(c, op64, phi, X, v.r, PX == P64 ? SpinorPtr{} : v.x);
+            hipLaunchKernelGGL(k_cg_restart, dim3(1), dim3(DBS), 0, c.stream, st, run,
+                               (const double*)partial_buf(c, g), nb, kend);
+            FGI_LAUNCH_CHECK();
+            res.iters = kend;
+            if (stop <= target || kend >= maxiter) {   // the solve should end here: look before launching more
+                FGI_HIP(hipStreamSynchronize(c.stream));
+                const double rr = c.host_scal[1];
+                res.rel_resid = std::sqrt(rr / bb);
+                if (!std::isfinite(rr)) throw Error(-4, "CG: non-finite residual");
+                if (rr <= target) {
+                    res.converged = 1;
+                    break;
+                }
+                if (kend >= maxiter) break;
             }
+            res.reliable_updates++;
             if (cgs) {  // the hops' copy of the new r, s = A p afresh, and the partials
                 if constexpr (PP != PX) convert<PX, PP>(c, g, v.r, v.rt);
                 cgs_refresh_s<PP, PX>(c, ops, v);
                 cgs_partials<PP, PX>(c, g, v);
             }
-            CGState u = hs;
-            u.beta = rr / hs.rr[(kend - 1) & 1];
-            u.rr[kend & 1] = rr;
-            u.stop_at = INT_MAX;
-            u.base = kend;
-            u.base0 = kend;
-            u.rr_stop = (PX == P64) ? target : std::max(c.ru_delta * c.ru_delta * rr, target);
-            hipLaunchKernelGGL(k_set_state, dim3(1), dim3(64), 0, c.stream, st, u);
-            FGI_LAUNCH_CHECK();
-            k = kend;
-        } else {
-            k = kend;
+            base0 = kend;
+            kcap = kend + B * ((maxiter - kend + B - 1) / B);
+            stop = std::max(run.ru2 * now, target);
         }
+        const double need = std::log(stop / now) / (std::log(now / rr_first) / kend);
+        n = !(need > 0.0) || need > 1e6 ? B : need > 12.0 ? (int)std::min(0.9 * need, 64.0) : (int)std::ceil(need);
+        n = std::min(n, kcap - k);
     }
     if (prof) {
         // live sample of the bare hop: N back-to-back launches between two events
