@@ -447,8 +447,7 @@ int fgi_destroy(fgi_ctx* ctx) {
                           &c.force3, &c.chain_U, &c.stout_lev, &c.stout_F, &c.stout_ga, &c.stout_gb,
                           &c.stout_part, &c.stout_M, &c.stout_sloppy, &c.hs_dchi, &c.hs_xo, &c.hs_yo,
                           &c.hs_dxo, &c.hs_dyo, &c.hs_zero, &c.hs_t1, &c.cl_sig, &c.cl_blk, &c.cl_blk2,
-                          &c.cl_blk32, &c.cl_s32, &c.cl_fh,
-                          &c.cl_ld, &c.cl_to, &c.cl_te, &c.cl_ue, &c.cl_r, &c.cl_p, &c.cl_ap, &c.cl_t,
+                          &c.cl_blk32, &c.cl_fh, &c.cl_ld, &c.cl_to,
                           &c.cl_ye, &c.cl_xo, &c.cl_yo, &c.br_jp, &c.br_jf, &c.br_jj, &c.halo_a, &c.halo_b};
         for (DevBuf* b : bufs) b->release();
         for (hipEvent_t e : c.ev_pool) hipEventDestroy(e);

@@ -252,40 +252,6 @@ __global__ void __launch_bounds__(CBS) k_clover_blocks(Geom g, const double* __r
     ld[(size_t)b * g.V + t] = logdet;
 }
 
-// out = g5^go (A (g5^gi in) - k2 u) at the Vh sites of one parity (u may be
-// null); in-place (out == in) is allowed
-__global__ void __launch_bounds__(CBS) k_clover_apply(int Vh, int V, int poff, const d2* __restrict__ blk,
-                                                      const d2* in, const d2* __restrict__ u, double k2, int gi,
-                                                      int go, d2* out) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= Vh) return;
-    const size_t site = (size_t)poff + s;
-    cx<double> v[12];
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        const d2 w = in[(size_t)k * Vh + s];
-        v[k] = (gi && k >= 6) ? cx<double>{-w.x, -w.y} : cx<double>{w.x, w.y};
-    }
-#pragma unroll
-    for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int r = 0; r < 6; r++) {
-            cx<double> acc = {0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < 6; c++) {
-                const d2 e = blk[(size_t)(b * 36 + r * 6 + c) * V + site];
-                acc = acc + cx<double>{e.x, e.y} * v[b * 6 + c];
-            }
-            const int k = b * 6 + r;
-            if (u) {
-                const d2 w = u[(size_t)k * Vh + s];
-                acc = acc - k2 * cx<double>{w.x, w.y};
-            }
-            if (go && k >= 6) acc = -acc;
-            out[(size_t)k * Vh + s] = d2{acc.re, acc.im};
-        }
-}
-
 // Colour matrices Kt_q(x) = (K - K^+) / 8, K = i (cw Z + cd Z') per site and
 // plane, with
 //   Z_{ba}  = sum_{s,t} sigma_{st} X_{t b} conj(Y_{s a})        (pseudofermion part, weight cw by parity)
@@ -460,199 +426,10 @@ double host_scalar(Ctx& c, const double* dev, int slot) {
     return c.host_scal[slot];
 }
 
-// Re <a, b> over the 12 Vh complex components of two even spinors
-double dot_re(Ctx& c, const Geom& g, const d2* a, const d2* b, int slot) {
-    double* part = partial_buf(c, g);
-    double* scal = (double*)c.scal.get(sizeof(double) * 64);
-    const int nb = dot_partials(c, 24L * g.Vh, (const double*)a, (const double*)b, part);
-    final_sum(c, part, nb, scal + slot);
-    return host_scalar(c, scal + slot, slot);
-}
-
-// ---- CG scalars on the device: st[0] = |r|^2, st[1] = alpha, st[2] = beta.
-// Reductions sum per-block partials in a fixed order in one block.
-__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int n) {
-    __shared__ double sh[CBS];
-    double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += CBS) v += part[i];
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = CBS / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    return sh[0];
-}
-
-// mode 0: st[0] = sum (|r|^2 of a restart); 1: alpha = st[0] / sum (<p, A p>);
-// 2: beta = sum / st[0], st[0] = sum (|r|^2 of the new residual)
-__global__ void __launch_bounds__(CBS) k_cl_scalar(const double* __restrict__ part, int n, int mode,
-                                                   double* __restrict__ st) {
-    const double v = sum_partials(part, n);
-    if (threadIdx.x != 0) return;
-    if (mode == 0) {
-        st[0] = v;
-    } else if (mode == 1) {
-        st[1] = st[0] / v;
-    } else {
-        st[2] = v / st[0];
-        st[0] = v;
-    }
-}
-
-// x += alpha p, r -= alpha A p; partial[b] = sum over the block of |r|^2
-__global__ void __launch_bounds__(CBS) k_cl_xr(int Vh, const double* __restrict__ st, const d2* __restrict__ p,
-                                               const d2* __restrict__ ap, d2* __restrict__ x, d2* __restrict__ r,
-                                               double* __restrict__ part) {
-    __shared__ double sh[CBS];
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
-    if (s < Vh) {
-        const double a = st[1];
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            const size_t i = (size_t)k * Vh + s;
-            const d2 pv = p[i], qv = ap[i];
-            d2 xv = x[i], rv = r[i];
-            xv.x += a * pv.x;
-            xv.y += a * pv.y;
-            rv.x -= a * qv.x;
-            rv.y -= a * qv.y;
-            x[i] = xv;
-            r[i] = rv;
-            acc += rv.x * rv.x + rv.y * rv.y;
-        }
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = CBS / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-// p = r + beta p
-__global__ void __launch_bounds__(CBS) k_cl_p(int Vh, const double* __restrict__ st, const d2* __restrict__ r,
-                                              d2* __restrict__ p) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= Vh) return;
-    const double b = st[2];
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        const size_t i = (size_t)k * Vh + s;
-        const d2 rv = r[i], pv = p[i];
-        p[i] = d2{rv.x + b * pv.x, rv.y + b * pv.y};
-    }
-}
-
-// ---- FP32 inner solver of the mixed-precision clover CG.  FP32 spinors are
-// [6][Vh] float4 (component k in the x,y or z,w half of float4 k / 2), the
-// blocks [72][V] float2 in the FP64 blocks' order.
+// FP32 copy of the blocks, [72][V] float2 in the same order
 __global__ void __launch_bounds__(CBS) k_blk_to_f32(size_t n, const d2* __restrict__ a, f2* __restrict__ b) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) b[t] = f2{(float)a[t].x, (float)a[t].y};
-}
-
-__device__ __forceinline__ cx<float> ld32(const float* __restrict__ v, int Vh, int s, int k) {
-    const size_t o = 4 * ((size_t)(k >> 1) * Vh + s) + 2 * (k & 1);
-    return {v[o], v[o + 1]};
-}
-__device__ __forceinline__ void st32(float* __restrict__ v, int Vh, int s, int k, cx<float> z) {
-    const size_t o = 4 * ((size_t)(k >> 1) * Vh + s) + 2 * (k & 1);
-    v[o] = z.re;
-    v[o + 1] = z.im;
-}
-
-// out = g5^go (A (g5^gi in) - k2 u), FP32 storage and arithmetic
-__global__ void __launch_bounds__(CBS) k_clover_apply32(int Vh, int V, int poff, const f2* __restrict__ blk,
-                                                        const float* in, const float* __restrict__ u, float k2,
-                                                        int gi, int go, float* out) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= Vh) return;
-    const size_t site = (size_t)poff + s;
-    cx<float> v[12];
-#pragma unroll
-    for (int k = 0; k < 12; k++) {
-        const cx<float> w = ld32(in, Vh, s, k);
-        v[k] = (gi && k >= 6) ? cx<float>{-w.re, -w.im} : w;
-    }
-#pragma unroll
-    for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int r = 0; r < 6; r++) {
-            cx<float> acc = {0.0f, 0.0f};
-#pragma unroll
-            for (int c = 0; c < 6; c++) {
-                const f2 e = blk[(size_t)(b * 36 + r * 6 + c) * V + site];
-                acc = acc + cx<float>{e.x, e.y} * v[b * 6 + c];
-            }
-            const int k = b * 6 + r;
-            if (u) acc = acc - k2 * ld32(u, Vh, s, k);
-            if (go && k >= 6) acc = -acc;
-            st32(out, Vh, s, k, acc);
-        }
-}
-
-// partial[b] = sum over the block of Re <a, b> (FP32 vectors, FP64 sums)
-__global__ void __launch_bounds__(CBS) k_dot32(int Vh, const float* __restrict__ a, const float* __restrict__ b,
-                                               double* __restrict__ part) {
-    __shared__ double sh[CBS];
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
-    if (s < Vh)
-#pragma unroll
-        for (int k = 0; k < 24; k++) {
-            const size_t o = (size_t)(k >> 2) * Vh * 4 + 4 * (size_t)s + (k & 3);
-            acc += (double)a[o] * (double)b[o];
-        }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = CBS / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-// x += alpha p, r -= alpha A p (FP32); partial[b] = block sum of |r|^2
-__global__ void __launch_bounds__(CBS) k_cl_xr32(int Vh, const double* __restrict__ st, const float* __restrict__ p,
-                                                 const float* __restrict__ ap, float* __restrict__ x,
-                                                 float* __restrict__ r, double* __restrict__ part) {
-    __shared__ double sh[CBS];
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
-    if (s < Vh) {
-        const float a = (float)st[1];
-#pragma unroll
-        for (int k = 0; k < 24; k++) {
-            const size_t o = (size_t)(k >> 2) * Vh * 4 + 4 * (size_t)s + (k & 3);
-            x[o] += a * p[o];
-            const float rv = r[o] - a * ap[o];
-            r[o] = rv;
-            acc += (double)rv * (double)rv;
-        }
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int w = CBS / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-// p = r + beta p (FP32)
-__global__ void __launch_bounds__(CBS) k_cl_p32(int Vh, const double* __restrict__ st, const float* __restrict__ r,
-                                                float* __restrict__ p) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= Vh) return;
-    const float b = (float)st[2];
-#pragma unroll
-    for (int k = 0; k < 24; k++) {
-        const size_t o = (size_t)(k >> 2) * Vh * 4 + 4 * (size_t)s + (k & 3);
-        p[o] = r[o] + b * p[o];
-    }
 }
 
 }  // namespace
@@ -682,220 +459,49 @@ void clover_unpack(Ctx& c, const Geom& g, const d2* blk, void* out) {
     FGI_LAUNCH_CHECK();
 }
 
-void clover_apply(Ctx& c, const Geom& g, const d2* blk, int parity, const d2* in, const d2* u, double k2, int g5in,
-                  int g5out, d2* out) {
-    hipLaunchKernelGGL(k_clover_apply, dim3(nb_of(g.Vh)), dim3(CBS), 0, c.stream, g.Vh, g.V, parity * g.Vh, blk, in,
-                       u, k2, g5in, g5out, out);
-    FGI_LAUNCH_CHECK();
+static FermionOp with_blocks(const FermionOp& op, const void* blk) {
+    FermionOp o = op;
+    o.blk = blk;
+    return o;
 }
 
 // out_e = Mhat in_e = A_ee in_e - kappa^2 D_eo A_oo^-1 D_oe in_e, or with
-// dagger g5 Mhat g5 in_e (the g5 on the input folded into the first hop and
-// into the A_ee product, the one on the output into that product's store)
+// dagger g5 Mhat g5 in_e (A commutes with g5): two launches, the block products
+// inside the Dslash-shaped kernels
 void clover_mhat(Ctx& c, const FermionOp& op, const d2* blk, const d2* in_e, d2* out_e, int dagger) {
-    const Geom& g = *op.g;
-    d2* to = (d2*)c.cl_to.get(spinor_bytes(g));
-    if (dagger) hop_oe_g5(c, op, in_e, to);
-    else dslash(c, op, 1, P64, SpinorPtr{(void*)in_e, nullptr}, P64, SpinorPtr{to, nullptr});
-    clover_apply(c, g, blk, 1, to, nullptr, 0.0, 0, 0, to);
-    d2* ue = (d2*)c.cl_ue.get(spinor_bytes(g));
-    dslash(c, op, 0, P64, SpinorPtr{to, nullptr}, P64, SpinorPtr{ue, nullptr});
-    clover_apply(c, g, blk, 0, in_e, ue, op.kappa * op.kappa, dagger, dagger, out_e);
+    d2* to = (d2*)c.cl_to.get(spinor_bytes(*op.g));
+    mhat(c, with_blocks(op, blk), P64, SpinorPtr{(void*)in_e, nullptr}, SpinorPtr{to, nullptr},
+         SpinorPtr{out_e, nullptr}, dagger);
 }
 
-// CG on Mhat^+ Mhat with the clover Mhat, FP64.  The recurrence scalars stay
-// on the device (k_cl_scalar); the host reads |r|^2 once per batch of
-// CL_BATCH iterations.  Stopping rule as in the fused solver: once the
-// recursive residual has passed tol |phi|, the true residual is formed and
-// decides; if it has not passed, CG restarts from it.  A batch may run a few
-// iterations past the point where the recursive residual first passed.
-constexpr int CL_BATCH = 8;
-
+// CG on Mhat^+ Mhat with the clover Mhat: the Wilson operator's solver on the
+// clover kernels (five launches per iteration; the separate products, dot
+// products and scalar kernels of a solver of its own took twelve)
 CGResult clover_cg(Ctx& c, const FermionOp& op, const d2* blk, const d2* phi, d2* x, double tol, int maxiter,
                    bool guess) {
-    const Geom& g = *op.g;
-    const size_t nb = spinor_bytes(g);
-    d2* r = (d2*)c.cl_r.get(nb);
-    d2* p = (d2*)c.cl_p.get(nb);
-    d2* ap = (d2*)c.cl_ap.get(nb);
-    d2* t = (d2*)c.cl_t.get(nb);
-    double* part = partial_buf(c, g);
-    const long ndot = 24L * g.Vh;
-    double* part2 = part + (ndot + 255) / 256 + 64;   // after the dot partials
-    double* scal = (double*)c.scal.get(sizeof(double) * 64);
-    double* st = scal + 56;                           // rr, alpha, beta
-    const int nbv = nb_of(g.Vh);
-    auto normal = [&](const d2* in, d2* out) {
-        clover_mhat(c, op, blk, in, t, 0);
-        clover_mhat(c, op, blk, t, out, 1);
-    };
-    auto true_residual = [&]() {
-        normal(x, ap);
-        spinor_lincomb(c, g, 1.0, phi, -1.0, ap, 0, r);
-    };
-    auto set_rr = [&]() {   // st[0] = |r|^2, returned to the host
-        const int n = dot_partials(c, ndot, (const double*)r, (const double*)r, part);
-        hipLaunchKernelGGL(k_cl_scalar, dim3(1), dim3(CBS), 0, c.stream, (const double*)part, n, 0, st);
-        FGI_LAUNCH_CHECK();
-        return host_scalar(c, st, 56);
-    };
-    CGResult res{};
-    const double bb = dot_re(c, g, phi, phi, 49);
-    const double target = tol * tol * bb;
-    if (guess) {
-        true_residual();
-    } else {
-        spinor_lincomb(c, g, 0.0, phi, 0.0, phi, 0, x);
-        FGI_HIP(hipMemcpyAsync(r, phi, nb, hipMemcpyDeviceToDevice, c.stream));
-    }
-    FGI_HIP(hipMemcpyAsync(p, r, nb, hipMemcpyDeviceToDevice, c.stream));
-    double rr = set_rr();
-    int it = 0;
-    bool conv = bb == 0.0 || rr <= target;
-    while (!conv && it < maxiter) {
-        const int nbatch = std::min(CL_BATCH, maxiter - it);
-        for (int k = 0; k < nbatch; k++) {
-            normal(p, ap);
-            const int n1 = dot_partials(c, ndot, (const double*)p, (const double*)ap, part);
-            hipLaunchKernelGGL(k_cl_scalar, dim3(1), dim3(CBS), 0, c.stream, (const double*)part, n1, 1, st);
-            hipLaunchKernelGGL(k_cl_xr, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, (const double*)st, (const d2*)p,
-                               (const d2*)ap, x, r, part2);
-            hipLaunchKernelGGL(k_cl_scalar, dim3(1), dim3(CBS), 0, c.stream, (const double*)part2, nbv, 2, st);
-            hipLaunchKernelGGL(k_cl_p, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, (const double*)st, (const d2*)r, p);
-            FGI_LAUNCH_CHECK();
-        }
-        it += nbatch;
-        rr = host_scalar(c, st, 56);
-        if (!(rr > target)) {   // passed (or not a number: the true residual decides)
-            true_residual();
-            rr = set_rr();
-            if (rr <= target) {
-                conv = true;
-                break;
-            }
-            FGI_HIP(hipMemcpyAsync(p, r, nb, hipMemcpyDeviceToDevice, c.stream));
-            res.reliable_updates++;
-        }
-    }
-    res.iters = it;
-    res.converged = conv ? 1 : 0;
-    res.rel_resid = bb > 0.0 ? std::sqrt(rr / bb) : 0.0;
-    return res;
+    const FermionOp o = with_blocks(op, blk);
+    return cg_solve(c, o, o, P64, phi, x, tol, maxiter, guess);
 }
 
-// Mixed precision: defect correction around an FP32 CG.  Each outer step forms
-// the FP64 true residual r = phi - A x, solves A e = r in FP32 (FP32 links of
-// op32, FP32 blocks, device scalars, |r32|^2 read every CL_BATCH iterations)
-// until its residual has dropped by CL_INNER or below what the outer target
-// needs, and adds e to x in FP64.  The FP64 true residual decides convergence,
-// so the solution meets tol exactly as the FP64 solver's does.
-constexpr double CL_INNER = 1e-5;
-
+// Mixed precision: FP32 inner iterations on the FP32 links of op32 and an FP32
+// copy of the blocks, FP64 reliable updates, so the solution meets tol exactly
+// as the FP64 solver's does.  Where the FP32 iteration is not finite (a
+// right-hand side beyond the FP32 range, a broken recursion) FP64 takes over
+// from the start.
 CGResult clover_cg_mp(Ctx& c, const FermionOp& op, const FermionOp& op32, const d2* blk, const d2* phi, d2* x,
                       double tol, int maxiter, bool guess) {
-    const Geom& g = *op.g;
-    const size_t nb = spinor_bytes(g), nb32 = nb / 2;
-    d2* r = (d2*)c.cl_r.get(nb);
-    d2* ap = (d2*)c.cl_ap.get(nb);
-    d2* t = (d2*)c.cl_t.get(nb);
-    f2* blk32 = (f2*)c.cl_blk32.get(sizeof(f2) * 72 * (size_t)g.V);
-    float* s32 = (float*)c.cl_s32.get(nb32 * 7);
-    float *r32 = s32, *p32 = s32 + nb32 / 4, *q32 = s32 + 2 * (nb32 / 4), *e32 = s32 + 3 * (nb32 / 4);
-    float *t32 = s32 + 4 * (nb32 / 4), *to32 = s32 + 5 * (nb32 / 4), *ue32 = s32 + 6 * (nb32 / 4);
-    double* part = partial_buf(c, g);
-    double* part2 = part + nb_of(g.Vh) + 64;
-    double* scal = (double*)c.scal.get(sizeof(double) * 64);
-    double* st = scal + 56;
-    const int nbv = nb_of(g.Vh);
-    {
-        const size_t n = 72 * (size_t)g.V;
-        hipLaunchKernelGGL(k_blk_to_f32, dim3((unsigned)((n + CBS - 1) / CBS)), dim3(CBS), 0, c.stream, n, blk, blk32);
-        FGI_LAUNCH_CHECK();
+    const size_t n = 72 * (size_t)op.g->V;
+    f2* blk32 = (f2*)c.cl_blk32.get(sizeof(f2) * n);
+    hipLaunchKernelGGL(k_blk_to_f32, dim3((unsigned)((n + CBS - 1) / CBS)), dim3(CBS), 0, c.stream, n, blk, blk32);
+    FGI_LAUNCH_CHECK();
+    try {
+        return cg_solve(c, with_blocks(op, blk), with_blocks(op32, blk32), P32, phi, x, tol, maxiter, guess);
+    } catch (const Error& e) {
+        if (e.code != -4) throw;
     }
-    const float k2 = (float)(op.kappa * op.kappa);
-    auto mhat32 = [&](float* in, float* out, int dagger) {
-        if (dagger) hop_oe_g5_p32(c, op32, in, to32);
-        else dslash(c, op32, 1, P32, SpinorPtr{in, nullptr}, P32, SpinorPtr{to32, nullptr});
-        hipLaunchKernelGGL(k_clover_apply32, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, g.V, g.Vh,
-                           (const f2*)blk32, (const float*)to32, (const float*)nullptr, 0.0f, 0, 0, to32);
-        dslash(c, op32, 0, P32, SpinorPtr{to32, nullptr}, P32, SpinorPtr{ue32, nullptr});
-        hipLaunchKernelGGL(k_clover_apply32, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, g.V, 0, (const f2*)blk32,
-                           (const float*)in, (const float*)ue32, k2, dagger, dagger, out);
-        FGI_LAUNCH_CHECK();
-    };
-    auto normal64 = [&](const d2* in, d2* out) {
-        clover_mhat(c, op, blk, in, t, 0);
-        clover_mhat(c, op, blk, t, out, 1);
-    };
-    auto dot32 = [&](const float* a, const float* b, int mode) {
-        hipLaunchKernelGGL(k_dot32, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, a, b, part);
-        hipLaunchKernelGGL(k_cl_scalar, dim3(1), dim3(CBS), 0, c.stream, (const double*)part, nbv, mode, st);
-        FGI_LAUNCH_CHECK();
-    };
-    CGResult res{};
-    const double bb = dot_re(c, g, phi, phi, 49);
-    const double target = tol * tol * bb;
-    if (!guess) spinor_lincomb(c, g, 0.0, phi, 0.0, phi, 0, x);
-    int it = 0;
-    bool conv = bb == 0.0;
-    double rr = bb;
-    while (!conv) {
-        normal64(x, ap);
-        spinor_lincomb(c, g, 1.0, phi, -1.0, ap, 0, r);
-        rr = dot_re(c, g, r, r, 50);
-        if (rr <= target) {
-            conv = true;
-            break;
-        }
-        if (it >= maxiter) break;
-        if (it > 0) res.reliable_updates++;
-        // inner FP32 solve of A e = r from e = 0
-        convert_spinor(c, g, P64, SpinorPtr{r, nullptr}, P32, SpinorPtr{r32, nullptr});
-        FGI_HIP(hipMemcpyAsync(p32, r32, nb32, hipMemcpyDeviceToDevice, c.stream));
-        FGI_HIP(hipMemsetAsync(e32, 0, nb32, c.stream));
-        dot32(r32, r32, 0);
-        const double rr0 = host_scalar(c, st, 56);
-        const double inner = std::max(CL_INNER * CL_INNER * rr0, 0.25 * target);
-        double rri = rr0;
-        const int before = it;
-        bool inner_finite = std::isfinite(rr0);
-        while (inner_finite && rri > inner && it < maxiter) {
-            const int nbatch = std::min(CL_BATCH, maxiter - it);
-            for (int k = 0; k < nbatch; k++) {
-                mhat32(p32, t32, 0);
-                mhat32(t32, q32, 1);
-                dot32(p32, q32, 1);
-                hipLaunchKernelGGL(k_cl_xr32, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, (const double*)st,
-                                   (const float*)p32, (const float*)q32, e32, r32, part2);
-                hipLaunchKernelGGL(k_cl_scalar, dim3(1), dim3(CBS), 0, c.stream, (const double*)part2, nbv, 2, st);
-                hipLaunchKernelGGL(k_cl_p32, dim3(nbv), dim3(CBS), 0, c.stream, g.Vh, (const double*)st,
-                                   (const float*)r32, p32);
-                FGI_LAUNCH_CHECK();
-            }
-            it += nbatch;
-            rri = host_scalar(c, st, 56);
-            inner_finite = std::isfinite(rri);
-        }
-        if (!inner_finite) {
-            // the FP32 residual is not finite (the recursion broke down, or the
-            // residual does not fit FP32): its correction is discarded and the
-            // FP64 solver continues from the current x
-            const CGResult r64 = clover_cg(c, op, blk, phi, x, tol, std::max(maxiter - it, 0), true);
-            res.iters = it + r64.iters;
-            res.converged = r64.converged;
-            res.rel_resid = r64.rel_resid;
-            res.reliable_updates += r64.reliable_updates + 1;
-            return res;
-        }
-        if (it == before) break;   // no FP32 progress possible: report the FP64 residual
-        // x += e
-        convert_spinor(c, g, P32, SpinorPtr{e32, nullptr}, P64, SpinorPtr{ap, nullptr});
-        spinor_lincomb(c, g, 1.0, x, 1.0, ap, 0, x);
-    }
-    res.iters = it;
-    res.converged = conv ? 1 : 0;
-    res.rel_resid = bb > 0.0 ? std::sqrt(rr / bb) : 0.0;
-    return res;
+    CGResult r = clover_cg(c, op, blk, phi, x, tol, maxiter, false);
+    r.reliable_updates++;
+    return r;
 }
 
 // F += coef * (pf_scale F_pf + det_scale F_det) with F_pf the force of
@@ -921,14 +527,11 @@ void clover_force(Ctx& c, const FermionOp& op, double csw, const d2* blk, const 
         ye = (d2*)c.cl_ye.get(nb);
         xo = (d2*)c.cl_xo.get(nb);
         yo = (d2*)c.cl_yo.get(nb);
-        d2* te = (d2*)c.cl_t.get(nb);
         if (Ye_given) ye = (d2*)Ye_given;
         else clover_mhat(c, op, blk, Xe, ye, 0);
-        dslash(c, op, 1, P64, SpinorPtr{(void*)Xe, nullptr}, P64, SpinorPtr{xo, nullptr});
-        clover_apply(c, g, blk, 1, xo, nullptr, 0.0, 0, 0, xo);
-        spinor_lincomb(c, g, 0.0, ye, 1.0, ye, 1, te);   // te = g5 Y_e
-        dslash(c, op, 1, P64, SpinorPtr{te, nullptr}, P64, SpinorPtr{yo, nullptr});
-        clover_apply(c, g, blk, 1, yo, nullptr, 0.0, 1, 0, yo);   // A^-1 g5 (D_oe g5 Y_e)
+        const FermionOp oc = with_blocks(op, blk);
+        dslash(c, oc, 1, P64, SpinorPtr{(void*)Xe, nullptr}, P64, SpinorPtr{xo, nullptr});   // A_oo^-1 D_oe X_e
+        hop_oe_g5(c, oc, ye, yo, 1);                                                         // A_oo^-1 g5 D_oe g5 Y_e
         fermion_force_xyo(c, op, Xe, xo, ye, yo, F, coef * pf_scale * k * k);
     }
     hipLaunchKernelGGL(k_clover_kt, dim3(nb_of(g.V)), dim3(CBS), 0, c.stream, g, sigma_blocks(c),

@@ -169,6 +169,78 @@ struct DArgs {
     int xcd;    // XCD-aware block order
     int cgs;    // M_HOP reduction block of the Chronopoulos-Gear form
     SpinorPtr dir, adir;   // M_CGS: p and s = A p, in the precision of x and r
+    const void* blk;       // clover kernels: the blocks of the output parity's sites, in the links' precision
+    long bstride;          // their stride (V)
+};
+
+// The clover term is site-local, so its kernels are the Wilson ones with one
+// product by the site's two 6x6 blocks: A_oo^-1 on a hop onto odd sites, A_ee on
+// the centre of the Schur-shaped modes.  Both are Hermitian: the upper triangle
+// is read and the lower is its conjugate (21 of 36 entries).
+template <int PB, typename R> __device__ __forceinline__ cx<R> blk_entry(const void* blk, long stride, int k, int s) {
+    if constexpr (PB == P64) {
+        const d2 e = ((const d2*)blk)[k * stride + s];
+        return {R(e.x), R(e.y)};
+    } else {
+        const f2 e = ((const f2*)blk)[k * stride + s];
+        return {R(e.x), R(e.y)};
+    }
+}
+// y += e x and y += conj(e) x
+template <typename R> __device__ __forceinline__ void cfma(cx<R>& y, cx<R> e, cx<R> x) {
+    y.re = fma(e.re, x.re, y.re);
+    y.re = fma(-e.im, x.im, y.re);
+    y.im = fma(e.re, x.im, y.im);
+    y.im = fma(e.im, x.re, y.im);
+}
+// v = A v for a whole site
+template <int PB, typename R>
+__device__ __forceinline__ void clover_mul(const void* blk, long stride, int s, cx<R> v[4][3]) {
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        cx<R> o[6];
+#pragma unroll
+        for (int r = 0; r < 6; r++) o[r] = {R(0), R(0)};
+#pragma unroll
+        for (int r = 0; r < 6; r++)
+#pragma unroll
+            for (int c = r; c < 6; c++) {
+                const cx<R> e = blk_entry<PB, R>(blk, stride, b * 36 + r * 6 + c, s);
+                if (c == r) {
+                    o[r].re = fma(e.re, v[2 * b + c / 3][c % 3].re, o[r].re);
+                    o[r].im = fma(e.re, v[2 * b + c / 3][c % 3].im, o[r].im);
+                } else {
+                    cfma(o[r], e, v[2 * b + c / 3][c % 3]);
+                    cfma(o[c], conj(e), v[2 * b + r / 3][r % 3]);
+                }
+            }
+#pragma unroll
+        for (int r = 0; r < 6; r++) v[2 * b + r / 3][r % 3] = o[r];
+    }
+}
+// One wave's half block (split kernels): the spin w = 2 b + h of a site holds
+// rows 3 h .. 3 h + 2 of block b.
+template <int PB, typename R> struct HalfBlk {
+    cx<R> e[3][6];
+    __device__ __forceinline__ void load(const void* blk, long stride, int s, int w) {
+        const int b = w >> 1, r0 = 3 * (w & 1);
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+#pragma unroll
+            for (int c = 0; c < 6; c++) {
+                const int r = r0 + k;
+                const cx<R> v = blk_entry<PB, R>(blk, stride, b * 36 + (c >= r ? r * 6 + c : c * 6 + r), s);
+                e[k][c] = c >= r ? v : conj(v);
+            }
+    }
+    __device__ __forceinline__ void mul(const cx<R> v[6], cx<R> o[3]) const {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            o[k] = {R(0), R(0)};
+#pragma unroll
+            for (int c = 0; c < 6; c++) cfma(o[k], e[k][c], v[c]);
+        }
+    }
 };
 
 // Chronopoulos-Gear form (Chronopoulos and Gear, J. Comput. Appl. Math. 25
@@ -203,8 +275,8 @@ __device__ __forceinline__ void cgs_state_update(CGState* st, const StateView& S
     }
 }
 
-// NT: the links are streamed with non-temporal loads (see links_streamed)
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool NT>
+// NT: the links are streamed with non-temporal loads (see links_streamed); CL: the clover operator
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool NT, bool CL>
 __device__ __forceinline__ void dslash_body(const DArgs& A, int b, int nb, double* lds) {
     typedef typename Real<PIN == P64 ? P64 : P32>::T R;
     const Geom& g = A.g;
@@ -236,10 +308,12 @@ __device__ __forceinline__ void dslash_body(const DArgs& A, int b, int nb, doubl
         hop_sum<PL, RECON, NT, R>(g, A.p_out, s, A.links, ld, acc);
         if (A.g5out) flip_lower(acc);
         if (MODE == M_HOP) {
+            if constexpr (CL) clover_mul<PL, R>(A.blk, A.bstride, s, acc);
             SpinorIO<POUT, R>::store(A.out, s, g.Vh, acc);
         } else {
             cx<R> cen[4][3];
             SpinorIO<PC, R>::load(A.center, s, g.Vh, cen);
+            if constexpr (CL) clover_mul<PL, R>(A.blk, A.bstride, s, cen);
             const R k2 = R(A.kappa2);
 #pragma unroll
             for (int i = 0; i < 4; i++)
@@ -345,14 +419,14 @@ __device__ __forceinline__ void dslash_body(const DArgs& A, int b, int nb, doubl
     if (threadIdx.x == 0) A.partial[b] = v[0];
 }
 
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool NT>
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool NT, bool CL>
 __global__ void __launch_bounds__(DBS) k_dslash(DArgs A) {
     __shared__ double lds[3 * DBS / 64];
     // site blocks in XCD-aware order (the same order in every kernel of the
     // solver, so a site stays on one XCD); a reduction block comes last
     const int nb = (A.g.Vh + blockDim.x - 1) / blockDim.x;
     const int b = (int)blockIdx.x < nb ? (A.xcd ? xcd_block(blockIdx.x, nb) : (int)blockIdx.x) : blockIdx.x;
-    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, NT>(A, b, nb, lds);
+    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, NT, CL>(A, b, nb, lds);
 }
 
 // ------------------------------------------------ split sites (small lattices) ---
@@ -478,7 +552,7 @@ template <typename R> struct SplitLds {
 // early: leave before any load when this launch has nothing to do (batched
 // launches, where finished chains must not keep the chip busy); otherwise the
 // state is only waited for after the hops, its latency hidden behind theirs.
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool CL>
 __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb, int early,
                                                   SplitLds<typename Real<PIN == P64 ? P64 : P32>::T>& L) {
     typedef typename Real<PIN == P64 ? P64 : P32>::T R;
@@ -510,7 +584,16 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
     // the epilogue's operands, in flight beside the hops'
     cx<R> cen[3], ph[3];
     cx<RX> av[3], xv[3], rv[3], pv[3], sv[3];
-    if constexpr (MODE != M_HOP) load_spin<PC, R>(A.center, s, g.Vh, w, cen);
+    if constexpr (MODE != M_HOP && !CL) load_spin<PC, R>(A.center, s, g.Vh, w, cen);
+    [[maybe_unused]] HalfBlk<PL, R> hb;
+    [[maybe_unused]] cx<R> six[6];
+    if constexpr (CL) {
+        hb.load(A.blk, A.bstride, s, w);
+        if constexpr (MODE != M_HOP) {
+            load_spin<PC, R>(A.center, s, g.Vh, w & 2, six);
+            load_spin<PC, R>(A.center, s, g.Vh, w | 1, six + 3);
+        }
+    }
     if constexpr (MODE == M_RESID) load_spin<PC, R>(A.aux, s, g.Vh, w, ph);
     if constexpr (MODE == M_CGX || MODE == M_CGS) {
         load_spin<PC, RX>(A.aux, s, g.Vh, w, av);
@@ -535,11 +618,22 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
     __syncthreads();
     if (A.st && (A.gate ? !S.act : S.stop_at <= iter)) return;
     cx<R> acc[3];
+    if constexpr (CL && MODE == M_HOP) {   // A_oo^-1 needs both spins of the wave's block
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        const int e = 3 * w + k;
-        acc[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
-        if (A.g5out && w >= 2) acc[k] = -acc[k];
+        for (int k = 0; k < 6; k++) {
+            const int e = 3 * (w & 2) + k;
+            six[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
+            if (A.g5out && w >= 2) six[k] = -six[k];
+        }
+        hb.mul(six, acc);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int e = 3 * w + k;
+            acc[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
+            if (A.g5out && w >= 2) acc[k] = -acc[k];
+        }
+        if constexpr (CL) hb.mul(six, cen);
     }
     double nrm = 0.0, rs = 0.0, ps = 0.0;
     if constexpr (MODE == M_HOP) {
@@ -621,12 +715,12 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
     if (threadIdx.x == 0) A.partial[b] = v[0];
 }
 
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool CL>
 __global__ void __launch_bounds__(256) k_dslash_split(DArgs A) {
     __shared__ SplitLds<typename Real<PIN == P64 ? P64 : P32>::T> L;
     const int nb = (A.g.Vh + SPLIT_SITES - 1) / SPLIT_SITES;
     const int b = (int)blockIdx.x < nb ? (A.xcd ? xcd_block(blockIdx.x, nb) : (int)blockIdx.x) : blockIdx.x;
-    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>(A, b, nb, 0, L);
+    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, CL>(A, b, nb, 0, L);
 }
 
 // one chain's part of a concatenated spinor field / link field
@@ -676,7 +770,7 @@ __global__ void __launch_bounds__(DBS) k_dslash_b(DArgs base, const ChainDesc* _
     const int2 m = map[gb];
     const ChainDesc& d = cd[m.x];
     const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
-    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, m.y, d.nblk[GRID_DS], lds);
+    dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false, false>(A, m.y, d.nblk[GRID_DS], lds);
 }
 
 template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
@@ -687,7 +781,7 @@ __global__ void __launch_bounds__(256) k_dslash_split_b(DArgs base, const ChainD
     const int2 m = map[gb];
     const ChainDesc& d = cd[m.x];
     const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
-    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN>(A, m.y, d.nblk[GRID_DS], 1, L);
+    dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, m.y, d.nblk[GRID_DS], 1, L);
 }
 
 // First kernel of a CG iteration: p = r + beta p, stored in p's precision.
@@ -1240,46 +1334,51 @@ static int links_streamed(const FermionOp& op, long nlinks) {
 // blocks (= partials) of the Dslash-shaped kernels on a lattice
 static int ds_blocks(const Ctx& c, int Vh) { return nblk(Vh, ds_sites(c, Vh)); }
 
-template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN>
-static void launch_dslash_nt(Ctx& c, bool nt, int nb, DArgs& a) {
-    if (nt) hipLaunchKernelGGL((k_dslash<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, true>), dim3(nb), dim3(c.ds_bs), 0, c.stream, a);
-    else hipLaunchKernelGGL((k_dslash<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>), dim3(nb), dim3(c.ds_bs), 0, c.stream, a);
-}
-
-template <int MODE, int PIN, int PC, int POUT, int PX, int G5IN>
-static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = false) {
-    const bool nt = links_streamed(op, 4L * a.g.V);
-    a.xcd = c.ds_xcd;
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool CL>
+static void launch_dslash_rec(Ctx& c, const FermionOp& op, DArgs& a, bool plain) {
     // an M_HOP inside CG (state and partials) carries the pAp reduction block
     const int extra = (MODE == M_HOP && a.st && a.partial) ? 1 : 0;
     if (!plain && site_split(a.g.Vh)) {
-        const dim3 nb(nblk(a.g.Vh, SPLIT_SITES) + extra), bs(256);
-        if constexpr (PIN == P64) {
-            if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
-            hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>), nb, bs, 0, c.stream, a);
-        } else {
-            if (op.prec == P32 && op.recon == 18)
-                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P32, 18, G5IN>), nb, bs, 0, c.stream, a);
-            else if (op.prec == P32)
-                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P32, 12, G5IN>), nb, bs, 0, c.stream, a);
-            else if (op.prec == P16 && op.recon == 18)
-                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P16, 18, G5IN>), nb, bs, 0, c.stream, a);
-            else if (op.prec == P16)
-                hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, P16, 12, G5IN>), nb, bs, 0, c.stream, a);
-            else throw Error(-1, "sloppy spinors need sloppy links");
-        }
-        FGI_LAUNCH_CHECK();
+        hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, CL>),
+                           dim3(nblk(a.g.Vh, SPLIT_SITES) + extra), dim3(256), 0, c.stream, a);
         return;
     }
-    int nb = nblk(a.g.Vh, c.ds_bs) + extra;
+    const dim3 nb(nblk(a.g.Vh, c.ds_bs) + extra), bs(c.ds_bs);
+    if (links_streamed(op, 4L * a.g.V))
+        hipLaunchKernelGGL((k_dslash<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, true, CL>), nb, bs, 0, c.stream, a);
+    else hipLaunchKernelGGL((k_dslash<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false, CL>), nb, bs, 0, c.stream, a);
+}
+
+// op.blk selects the clover kernels: A_oo^-1 on hops onto odd sites, A_ee on the
+// centre of the other modes
+template <int MODE, int PIN, int PC, int POUT, int PX, int G5IN>
+static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = false) {
+    a.xcd = c.ds_xcd;
+    if (op.blk) {
+        if constexpr (PIN != P16 && MODE != M_CGS) {
+            a.bstride = a.g.V;
+            a.blk = (const char*)op.blk + (size_t)a.p_out * a.g.Vh * (op.prec == P64 ? sizeof(d2) : sizeof(f2));
+            if constexpr (PIN == P64) {
+                if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
+                launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, true>(c, op, a, plain);
+            } else {
+                if (op.prec != P32) throw Error(-1, "the clover kernels take FP64 or FP32 links");
+                if (op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, true>(c, op, a, plain);
+                else launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, true>(c, op, a, plain);
+            }
+            FGI_LAUNCH_CHECK();
+            return;
+        }
+        throw Error(-1, "no clover kernel for this storage");
+    }
     if constexpr (PIN == P64) {
         if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
-        launch_dslash_nt<MODE, PIN, PC, POUT, PX, P64, 18, G5IN>(c, nt, nb, a);
+        launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, false>(c, op, a, plain);
     } else {
-        if (op.prec == P32 && op.recon == 18) launch_dslash_nt<MODE, PIN, PC, POUT, PX, P32, 18, G5IN>(c, nt, nb, a);
-        else if (op.prec == P32) launch_dslash_nt<MODE, PIN, PC, POUT, PX, P32, 12, G5IN>(c, nt, nb, a);
-        else if (op.prec == P16 && op.recon == 18) launch_dslash_nt<MODE, PIN, PC, POUT, PX, P16, 18, G5IN>(c, nt, nb, a);
-        else if (op.prec == P16) launch_dslash_nt<MODE, PIN, PC, POUT, PX, P16, 12, G5IN>(c, nt, nb, a);
+        if (op.prec == P32 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, false>(c, op, a, plain);
+        else if (op.prec == P32) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, false>(c, op, a, plain);
+        else if (op.prec == P16 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 18, G5IN, false>(c, op, a, plain);
+        else if (op.prec == P16) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 12, G5IN, false>(c, op, a, plain);
         else throw Error(-1, "sloppy spinors need sloppy links");
     }
     FGI_LAUNCH_CHECK();
@@ -1502,16 +1601,8 @@ void fermion_force_xyo(Ctx& c, const FermionOp& op64, const d2* Xe, const d2* Xo
     FGI_LAUNCH_CHECK();
 }
 
-// out_o = D_oe g5 in_e (FP64): the first hop of Mhat^+ = g5 Mhat g5
-void hop_oe_g5(Ctx& c, const FermionOp& op64, const d2* in_e, d2* out_o) { hop_g5(c, op64, in_e, out_o, 0); }
-
-// the same with FP32 spinors on FP32 links
-void hop_oe_g5_p32(Ctx& c, const FermionOp& op32, void* in_e, void* out_o) {
-    DArgs a = base_args(op32, 1);
-    a.in = sp(in_e);
-    a.out = sp(out_o);
-    launch_dslash<M_HOP, P32, P32, P32, P32, 1>(c, op32, a);
-}
+// out_o = [g5] A_oo^-1 D_oe g5 in_e (FP64; no A_oo^-1 without op64.blk)
+void hop_oe_g5(Ctx& c, const FermionOp& op64, const d2* in_e, d2* out_o, int g5out) { hop_g5(c, op64, in_e, out_o, g5out); }
 
 // ---------------------------------------------------------------- CG ------
 // |v|^2 into the device scalar out
@@ -1685,7 +1776,7 @@ static void cgs_partials(Ctx& c, const Geom& g, const CGVecs& v) {
 template <int PP, int PX>
 static void cg_batch_eager(Ctx& c, const FermionOp& ops, const CGVecs& v, int B) {
     for (int j = 0; j < B; j++) {
-        if (c.cg_form) cg_iteration_cgs<PP, PX>(c, ops, v, j);
+        if (c.cg_form && !ops.blk) cg_iteration_cgs<PP, PX>(c, ops, v, j);
         else cg_iteration<PP, PX>(c, ops, v, j);
     }
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(DBS), 0, c.stream, dev_state(c), (const double*)partial_buf(c, *ops.g),
@@ -1742,8 +1833,8 @@ static GraphEntry& cached_graph(Ctx& c, const std::string& key, Body body) {
 template <int PP, int PX>
 static std::string graph_key(const char* what, Ctx& c, const FermionOp& ops, const CGVecs& v, int n) {
     char key[512];
-    snprintf(key, sizeof key, "%s/%d/%d/%p/%.17g/%d/%d/%d/%d/%d/%d/%d/%p/%p/%p/%p/%p/%p/%p/%p/%d/%d/%d/%d/%p/%p/%p/%p",
-             what, PP, PX, ops.links, ops.kappa, ops.prec, ops.recon, ops.g->L[0], ops.g->L[1], ops.g->L[2],
+    snprintf(key, sizeof key, "%s/%d/%d/%p/%p/%.17g/%d/%d/%d/%d/%d/%d/%d/%p/%p/%p/%p/%p/%p/%p/%p/%d/%d/%d/%d/%p/%p/%p/%p",
+             what, PP, PX, ops.links, ops.blk, ops.kappa, ops.prec, ops.recon, ops.g->L[0], ops.g->L[1], ops.g->L[2],
              ops.g->L[3], ops.g->Vh, v.x.v, v.r.v, v.p.v, v.q.v, v.t.v, (void*)v.p.norm, (void*)dev_state(c),
              (void*)partial_buf(c, *ops.g), n, c.ds_bs, c.ds_xcd, c.cg_form, v.pf.v, v.sf.v, v.rt.v,
              (void*)v.rt.norm);
@@ -1862,7 +1953,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
         convert<P64, PP>(c, g, sp(r_start), v.p);
     }
     partial_buf(c, g);  // allocate before any capture
-    const bool cgs = c.cg_form != 0;
+    const bool cgs = c.cg_form != 0 && !ops.blk;
     if (cgs) {  // Chronopoulos-Gear form: p = s = 0, rt = r, and the partials its first iteration sums
         const size_t nx = PX == P64 ? n64 : sizeof(float) * 24 * (size_t)g.Vh;
         v.pf = sp(c.s_pf.get(nx));
@@ -1889,7 +1980,8 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     // of the launches empty where a run takes ten iterations, and each run
     // waited twice.  The iterates do not depend on the counts.
     int k = 0, base0 = 0;   // iterations launched so far; start of the current inner run
-    int kcap = B * ((maxiter + B - 1) / B);   // where an unfinished run is cut off: whole batches from base0
+    const int whole = op64.blk ? 1 : B;
+    int kcap = whole * ((maxiter + whole - 1) / whole);   // where an unfinished run is cut off: whole batches from base0
     int n = std::min(std::min(B, 8), kcap);
     double rr_first = 0.0;
     for (;;) {
@@ -1921,6 +2013,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
         const bool inner_done = hs.stop_at <= kend;
         k = kend;
         const double now = hs.rr[kend & 1];
+        if (!std::isfinite(now)) throw Error(-4, "CG: non-finite residual");
         double stop = hs.rr_stop;
         if (inner_done || kend >= kcap) {
             if (PX != P64) {
@@ -1951,7 +2044,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
                 cgs_partials<PP, PX>(c, g, v);
             }
             base0 = kend;
-            kcap = kend + B * ((maxiter - kend + B - 1) / B);
+            kcap = kend + whole * ((maxiter - kend + whole - 1) / whole);
             stop = std::max(run.ru2 * now, target);
         }
         const double need = std::log(stop / now) / (std::log(now / rr_first) / kend);

@@ -104,8 +104,8 @@ struct Ctx {
     // exact force gradient of the Hasenbusch ratio term
     DevBuf hs_dchi, hs_xo, hs_yo, hs_dxo, hs_dyo, hs_zero, hs_t1;
     // clover term: blocks (A_ee, A_oo^-1), field strengths / force matrices,
-    // log dets, and the vectors of its operator, solver and force
-    DevBuf cl_sig, cl_blk, cl_blk2, cl_blk32, cl_s32, cl_fh, cl_ld, cl_to, cl_te, cl_ue, cl_r, cl_p, cl_ap, cl_t, cl_ye, cl_xo, cl_yo;
+    // log dets, and the vectors of its operator and force
+    DevBuf cl_sig, cl_blk, cl_blk2, cl_blk32, cl_fh, cl_ld, cl_to, cl_ye, cl_xo, cl_yo;
     DevBuf cdesc, bstate, bscal, bh0, bh1, bres;  // batched chains
     DevBuf br_jp, br_jf, br_jj;   // force gradients of the dt^4 brackets
     DevBuf halo_a, halo_b;        // face buffers of the t-decomposed hop (timing)
@@ -270,6 +270,7 @@ struct FermionOp {
     double kappa;
     const void* links;   // gauge storage for this operator
     int prec, recon;     // link storage precision / reconstruction
+    const void* blk = nullptr;   // clover: A_ee and A_oo^-1 (72 complex per site, the links' precision), else null
 };
 // out_{1-p} = D_{(1-p) p} in_p  (hopping term between parities)
 // plain: always with the summation order of the halo hop (one thread per site),
@@ -310,9 +311,8 @@ void spinor_lincomb(Ctx&, const Geom&, double a, const d2* x, double b, const d2
 // F += coef * TA(U C(X, Y)) for given even and odd halves of X and Y
 void fermion_force_xyo(Ctx&, const FermionOp& op64, const d2* Xe, const d2* Xo, const d2* Ye, const d2* Yo,
                        double* F, double coef);
-// out_o = D_oe g5 in_e (FP64)
-void hop_oe_g5(Ctx&, const FermionOp& op64, const d2* in_e, d2* out_o);
-void hop_oe_g5_p32(Ctx&, const FermionOp& op32, void* in_e, void* out_o);
+// out_o = [g5] A_oo^-1 D_oe g5 in_e (FP64)
+void hop_oe_g5(Ctx&, const FermionOp& op64, const d2* in_e, d2* out_o, int g5out);
 //   J += coef * J_V[F_F] given Z = A^-1 rhs (after fermion_tangent_rhs on the same X_e)
 void fermion_force_tangent(Ctx&, const FermionOp& op64, const FermionOp& opW, const double* Vd, const d2* Xe,
                            const d2* Z, double* J, double coef);
@@ -349,8 +349,8 @@ void clover_unpack(Ctx&, const Geom&, const d2* blk, void* out);
 void clover_mhat(Ctx&, const FermionOp& op64, const d2* blk, const d2* in_e, d2* out_e, int dagger);
 CGResult clover_cg(Ctx&, const FermionOp& op64, const d2* blk, const d2* phi, d2* x, double tol, int maxiter,
                    bool guess);
-// the same solve with an FP32 inner CG on the FP32 links of ops (defect
-// correction: the FP64 true residual decides convergence)
+// the same solve with an FP32 inner CG on the FP32 links of op32 and FP32 blocks
+// (reliable updates: the FP64 true residual decides convergence)
 CGResult clover_cg_mp(Ctx&, const FermionOp& op64, const FermionOp& op32, const d2* blk, const d2* phi, d2* x,
                       double tol, int maxiter, bool guess);
 // F += coef (pf_scale F_pf(X_e) + det_scale F_det); Xe may be null when pf_scale == 0
