@@ -117,7 +117,10 @@ Ctx& ctx_of(fgi_ctx* c) {
 
 struct StreamScope {
     Ctx& c;
-    StreamScope(Ctx& cc, void* s) : c(cc) { c.stream = (hipStream_t)s; }
+    StreamScope(Ctx& cc, void* s) : c(cc) {
+        c.stream = (hipStream_t)s;
+        c.split = true;
+    }
     ~StreamScope() { c.stream = nullptr; }
 };
 
@@ -185,6 +188,7 @@ struct Fields {
     Fields(Ctx& cc, const Geom& gg, const fgi_action& a) : c(cc), g(gg), act(a) {
         sp = sloppy_prec(&act);
         rc = sloppy_recon(&act);
+        c.split = sp != P16 || rc != 18;
     }
 
     FermionOp op64(const d2* u, double kappa) const { return FermionOp{&g, kappa, u, P64, 18}; }
@@ -728,7 +732,7 @@ int fgi_dslash(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const vo
         pack_even_spinor(c, g, in, vin);  // same layout for either parity
         FermionOp op = f.op64(u, a.kappa);
         if (f.sp == P64) {
-            dslash(c, op, out_parity, P64, SpinorPtr{vin, nullptr}, P64, SpinorPtr{vout, nullptr}, true);
+            dslash(c, op, out_parity, P64, SpinorPtr{vin, nullptr}, P64, SpinorPtr{vout, nullptr});
         } else {
             void* us = c.sloppy.get(sloppy_bytes(g));
             make_sloppy(c, g, u, us, f.sp, f.rc);
@@ -737,7 +741,7 @@ int fgi_dslash(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const vo
             float* norms = (float*)c.s_norms.get(sizeof(float) * 3 * (size_t)g.Vh);
             SpinorPtr si{c.s_p.get(nb), norms}, so{c.s_q.get(nb), norms + g.Vh};
             convert_spinor(c, g, P64, SpinorPtr{vin, nullptr}, f.sp, si);
-            dslash(c, os, out_parity, f.sp, si, f.sp, so, true);
+            dslash(c, os, out_parity, f.sp, si, f.sp, so);
             convert_spinor(c, g, f.sp, so, P64, SpinorPtr{vout, nullptr});
         }
         unpack_even_spinor(c, g, vout, out);
@@ -898,7 +902,7 @@ int fgi_halo_time(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const
         t.interior_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 1); });
         t.faces_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 2); });
         t.all_us = timed([&] { dslash_halo(c, h.op, h.prec, 1, h.in, so, hb_, ha, 0); });
-        t.local_us = timed([&] { dslash(c, h.op, 1, h.prec, h.in, h.prec, so, true); });
+        t.local_us = timed([&] { dslash(c, h.op, 1, h.prec, h.in, h.prec, so); });
         t.face_sites = g.Vh / g.L[3];
         t.halo_bytes = (long)hb;
         FGI_HIP(hipEventDestroy(e0));
@@ -1854,6 +1858,7 @@ struct BFields {
     BFields(Ctx& cc, const fgi_action& a) : c(cc), act(a) {
         sp = sloppy_prec(&act);
         rc = sloppy_recon(&act);
+        c.split = sp != P16 || rc != 18;
     }
     FermionOp op64(const d2* u) const { return FermionOp{nullptr, 0.0, u, P64, 18}; }
     FermionOp ops(const d2* u, const void* us) const {
@@ -1984,13 +1989,13 @@ void upload_batch(Ctx& c, const std::vector<ChainDesc>& cd, Batch& B) {
     std::vector<int2> map[2];
     for (int k = 0; k < 2; k++) {
         for (int i = 0; i < B.nc; i++)
-            if (site_split(cd[i].g.Vh) == (k == DS_SPLIT)) {
+            if (site_split(c, cd[i].g.Vh) == (k == DS_SPLIT)) {
                 B.ds_nc[k]++;
                 for (int b = 0; b < cd[i].nblk[GRID_DS]; b++) map[k].push_back(make_int2(i, b));
             }
         B.ds_blk[k] = (int)map[k].size();
         for (int i = 0; i < B.nc; i++)
-            if (site_split(cd[i].g.Vh) == (k == DS_SPLIT)) map[k].push_back(make_int2(i, cd[i].nblk[GRID_DS]));
+            if (site_split(c, cd[i].g.Vh) == (k == DS_SPLIT)) map[k].push_back(make_int2(i, cd[i].nblk[GRID_DS]));
     }
     const size_t nd = sizeof(ChainDesc) * cd.size(), n0 = sizeof(int2) * map[0].size(), n1 = sizeof(int2) * map[1].size();
     std::vector<char> host(nd + n0 + n1);
@@ -2019,14 +2024,14 @@ extern "C" int fgi_trajectory_batched(fgi_ctx* ctx, int nchains, const fgi_chain
         if (act->csw != 0.0) throw Error(FGI_EINVAL, "batched chains have no clover term");
         if (act->fg_exact) throw Error(FGI_EINVAL, "batched chains use the displacement force-gradient form");
         const bool ferm = chains[0].kappa != 0.0;
-        std::vector<ChainDesc> cd;
-        Batch B;
-        describe_batch(c, nchains, chains, cd, B);
         auto t0 = std::chrono::steady_clock::now();
         const long cap0 = c.graph_captures;
         StreamScope ss(c, stream);
-        upload_batch(c, cd, B);
         BFields f(c, *act);
+        std::vector<ChainDesc> cd;
+        Batch B;
+        describe_batch(c, nchains, chains, cd, B);
+        upload_batch(c, cd, B);
         f.B = B;
         f.st = st;
         f.fermions = ferm;
@@ -2208,14 +2213,14 @@ int fgi_autotune_batched(fgi_ctx* ctx, int nchains, const fgi_chain* chains, con
         if (nchains < 1 || !chains) throw Error(FGI_EINVAL, "need chains");
         check_action(act);
         if (chains[0].kappa == 0.0) throw Error(FGI_EINVAL, "the CG schedule is tuned on chains with fermions");
-        std::vector<ChainDesc> cd;
-        Batch B;
-        describe_batch(c, nchains, chains, cd, B);
         StreamScope ss(c, stream);
-        upload_batch(c, cd, B);
         fgi_action a64 = *act;
         a64.cg_maxiter = 64;
         BFields f(c, *act), f64(c, a64);
+        std::vector<ChainDesc> cd;
+        Batch B;
+        describe_batch(c, nchains, chains, cd, B);
+        upload_batch(c, cd, B);
         f.B = B;
         f.fermions = true;
         const size_t gb = sizeof(d2) * 9 * (size_t)B.links, sb = sizeof(d2) * 12 * (size_t)B.sites;

@@ -433,11 +433,12 @@ __global__ void __launch_bounds__(DBS) k_dslash(DArgs A) {
 // One thread per site leaves most of the chip idle below a few hundred waves
 // (8^4: 32 waves on 1024 SIMDs), and the launch then lasts as long as one
 // thread's chain of eight dependent hops.  Here a block's four waves share 64
-// sites: wave w takes the two hops along direction w, with all its loads in
-// flight together, the four partial sums meet in LDS, and wave w finishes spin
-// w of the epilogue.  The sum of the four directions is ((0 + 1) + (2 + 3)), so
-// the bits differ from the one-thread order; the choice depends on the lattice
-// alone (site_split), so every path of one lattice makes it alike.
+// sites: wave w takes the two hops along direction w as far as the link times
+// half-spinor products, with all its loads in flight together; the products
+// meet in LDS and wave w sums spin w of the eight hops and finishes it.  The sum
+// runs over the hops in the one-thread order with the same multiply-adds, so a
+// site's result has the same bits; only the block sums of the reductions are
+// grouped differently, and site_split makes that a property of the lattice.
 
 // element e = 3 spin + colour of the spinor at s (R the working precision)
 template <int P, typename R> __device__ __forceinline__ cx<R> load_elem(const SpinorPtr& f, int s, int Vh, int e, float n) {
@@ -498,10 +499,21 @@ __device__ __forceinline__ void store_spin(const SpinorPtr& f, int s, int Vh, in
     }
 }
 
-// both hops along MU, every load issued before any arithmetic
+// U h (FWD) or U^+ h for both rows of a half spinor, into uh[2][3] of one hop
+template <bool FWD, typename R>
+__device__ __forceinline__ void link_half(const M3<R>& u, const cx<R> h[2][3], cx<R> (*out)[64], int lane) {
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+            out[3 * j + a][lane] = FWD ? cdot3(u.e[a][0], h[j][0], u.e[a][1], h[j][1], u.e[a][2], h[j][2])
+                                       : cdot3c(u.e[0][a], h[j][0], u.e[1][a], h[j][1], u.e[2][a], h[j][2]);
+}
+
+// the link products of both hops along MU, every load issued before any arithmetic
 template <int MU, int PIN, int PL, int RECON, int G5IN, typename R>
 __device__ __forceinline__ void hop_pair(const Geom& g, int p, int s, const Coord& c, const void* links,
-                                         const SpinorPtr& in, cx<R> acc[4][3]) {
+                                         const SpinorPtr& in, cx<R> (*uh)[6][64], int lane) {
     const int sf = cb_neighbour(g, c, MU, +1), sb = cb_neighbour(g, c, MU, -1);
     LoadPlain<PIN, G5IN, R> ld{in};
     typename LoadPlain<PIN, G5IN, R>::Raw rf, rb;
@@ -510,43 +522,71 @@ __device__ __forceinline__ void hop_pair(const Geom& g, int p, int s, const Coor
     fetch_link<PL, RECON, false>(links, MU, p, s, g.Vh, lf);
     ld.fetch(sb, g.Vh, rb);
     fetch_link<PL, RECON, false>(links, MU, 1 - p, sb, g.Vh, lb);
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int k = 0; k < 3; k++) acc[i][k] = {R(0), R(0)};
-    cx<R> psi[4][3], h[2][3], uh[2][3];
-    {
-        R w = ld.get(rf, psi) * R(link_unit<PL, RECON>());
-        spin_proj<MU, -1>(psi, h);
-        const M3<R> u = LinkIO<PL, RECON, R>::decode(lf);
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int a = 0; a < 3; a++)
-                uh[j][a] = cdot3(u.e[a][0], h[j][0], u.e[a][1], h[j][1], u.e[a][2], h[j][2]);
-        if (MU == 3 && c.c[3] == g.L[3] - 1) w = -w;
-        spin_recon_acc<MU, -1>(acc, uh, w);
-    }
-    {
-        R w = ld.get(rb, psi) * R(link_unit<PL, RECON>());
-        spin_proj<MU, +1>(psi, h);
-        const M3<R> u = LinkIO<PL, RECON, R>::decode(lb);
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int a = 0; a < 3; a++)
-                uh[j][a] = cdot3c(u.e[0][a], h[j][0], u.e[1][a], h[j][1], u.e[2][a], h[j][2]);
-        if (MU == 3 && c.c[3] == 0) w = -w;
-        spin_recon_acc<MU, +1>(acc, uh, w);
-    }
+    cx<R> psi[4][3], h[2][3];
+    ld.get(rf, psi);
+    spin_proj<MU, -1>(psi, h);
+    link_half<true>(LinkIO<PL, RECON, R>::decode(lf), h, uh[2 * MU], lane);
+    ld.get(rb, psi);
+    spin_proj<MU, +1>(psi, h);
+    link_half<false>(LinkIO<PL, RECON, R>::decode(lb), h, uh[2 * MU + 1], lane);
 }
 
-// the directions' partial sums: [direction][element][site of the block]
+// acc += w times spin S of the four-spinor that hop K = 2 MU + d rebuilds from
+// its half spinor (the multiply-adds of spin_recon_acc)
+template <int S, int K, typename R>
+__device__ __forceinline__ void recon_spin(cx<R> acc[3], const cx<R> (*uh)[64], int lane, R w) {
+    constexpr int MU = K >> 1;
+    constexpr bool NEG = (K & 1) == 0;   // (1 - g_mu), the forward hop
+    constexpr int J = S < 2 ? S : ((MU == 0 || MU == 1) ? 3 - S : S - 2);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const cx<R> x = uh[3 * J + c][lane];
+        cx<R> y = x;
+        if (S >= 2) {
+            if (MU == 0) y = NEG ? times_i(x) : times_mi(x);
+            else if (MU == 1) y = (S == 2) == NEG ? -x : x;
+            else if (MU == 2) y = (S == 2) == NEG ? times_i(x) : times_mi(x);
+            else y = NEG ? -x : x;
+        }
+        acc[c] = axpy(w, y, acc[c]);
+    }
+}
+template <int S, typename R>
+__device__ __forceinline__ void sum_spin(cx<R> acc[3], const cx<R> (*uh)[6][64], int lane, R unit, R wf, R wb) {
+#pragma unroll
+    for (int c = 0; c < 3; c++) acc[c] = {R(0), R(0)};
+    recon_spin<S, 0>(acc, uh[0], lane, unit);
+    recon_spin<S, 1>(acc, uh[1], lane, unit);
+    recon_spin<S, 2>(acc, uh[2], lane, unit);
+    recon_spin<S, 3>(acc, uh[3], lane, unit);
+    recon_spin<S, 4>(acc, uh[4], lane, unit);
+    recon_spin<S, 5>(acc, uh[5], lane, unit);
+    recon_spin<S, 6>(acc, uh[6], lane, wf);
+    recon_spin<S, 7>(acc, uh[7], lane, wb);
+}
+
+// the eight hops' link products: [hop][component][site of the block]
 template <typename R> struct SplitLds {
-    cx<R> part[4][12][64];
+    cx<R> uh[8][6][64];
     float mx[256];
     double red[3 * 4];
 };
+
+// spin w of the hop sum (w uniform over the wave); unit carries the link unit,
+// the antiperiodic boundary flips the sign of the t hops that cross it
+template <typename R>
+__device__ __forceinline__ void split_sum(const SplitLds<R>& L, int w, int lane, R unit, const Geom& g, const Coord& c,
+                                          int g5out, cx<R> acc[3]) {
+    const R wf = c.c[3] == g.L[3] - 1 ? -unit : unit, wb = c.c[3] == 0 ? -unit : unit;
+    if (w == 0) sum_spin<0>(acc, L.uh, lane, unit, wf, wb);
+    else if (w == 1) sum_spin<1>(acc, L.uh, lane, unit, wf, wb);
+    else if (w == 2) sum_spin<2>(acc, L.uh, lane, unit, wf, wb);
+    else sum_spin<3>(acc, L.uh, lane, unit, wf, wb);
+    if (g5out && w >= 2) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) acc[k] = -acc[k];
+    }
+}
 
 // A block's 64 sites of one Dslash-shaped kernel (the modes of dslash_body).
 // early: leave before any load when this launch has nothing to do (batched
@@ -604,35 +644,20 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
         load_spin<PX, RX>(A.dir, s, g.Vh, w, pv);
         load_spin<PX, RX>(A.adir, s, g.Vh, w, sv);
     }
-    {
-        cx<R> acc[4][3];
-        if (w == 0) hop_pair<0, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
-        else if (w == 1) hop_pair<1, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
-        else if (w == 2) hop_pair<2, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
-        else hop_pair<3, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, acc);
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int k = 0; k < 3; k++) L.part[w][3 * i + k][lane] = acc[i][k];
-    }
+    if (w == 0) hop_pair<0, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
+    else if (w == 1) hop_pair<1, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
+    else if (w == 2) hop_pair<2, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
+    else hop_pair<3, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
     __syncthreads();
     if (A.st && (A.gate ? !S.act : S.stop_at <= iter)) return;
+    const R unit = R(link_unit<PL, RECON>());
     cx<R> acc[3];
     if constexpr (CL && MODE == M_HOP) {   // A_oo^-1 needs both spins of the wave's block
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            const int e = 3 * (w & 2) + k;
-            six[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
-            if (A.g5out && w >= 2) six[k] = -six[k];
-        }
+        split_sum<R>(L, w & 2, lane, unit, g, c, A.g5out, six);
+        split_sum<R>(L, w | 1, lane, unit, g, c, A.g5out, six + 3);
         hb.mul(six, acc);
     } else {
-#pragma unroll
-        for (int k = 0; k < 3; k++) {
-            const int e = 3 * w + k;
-            acc[k] = (L.part[0][e][lane] + L.part[1][e][lane]) + (L.part[2][e][lane] + L.part[3][e][lane]);
-            if (A.g5out && w >= 2) acc[k] = -acc[k];
-        }
+        split_sum<R>(L, w, lane, unit, g, c, A.g5out, acc);
         if constexpr (CL) hb.mul(six, cen);
     }
     double nrm = 0.0, rs = 0.0, ps = 0.0;
@@ -1335,10 +1360,10 @@ static int links_streamed(const FermionOp& op, long nlinks) {
 static int ds_blocks(const Ctx& c, int Vh) { return nblk(Vh, ds_sites(c, Vh)); }
 
 template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON, int G5IN, bool CL>
-static void launch_dslash_rec(Ctx& c, const FermionOp& op, DArgs& a, bool plain) {
+static void launch_dslash_rec(Ctx& c, const FermionOp& op, DArgs& a) {
     // an M_HOP inside CG (state and partials) carries the pAp reduction block
     const int extra = (MODE == M_HOP && a.st && a.partial) ? 1 : 0;
-    if (!plain && site_split(a.g.Vh)) {
+    if (site_split(c, a.g.Vh)) {
         hipLaunchKernelGGL((k_dslash_split<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, CL>),
                            dim3(nblk(a.g.Vh, SPLIT_SITES) + extra), dim3(256), 0, c.stream, a);
         return;
@@ -1352,7 +1377,7 @@ static void launch_dslash_rec(Ctx& c, const FermionOp& op, DArgs& a, bool plain)
 // op.blk selects the clover kernels: A_oo^-1 on hops onto odd sites, A_ee on the
 // centre of the other modes
 template <int MODE, int PIN, int PC, int POUT, int PX, int G5IN>
-static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = false) {
+static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a) {
     a.xcd = c.ds_xcd;
     if (op.blk) {
         if constexpr (PIN != P16 && MODE != M_CGS) {
@@ -1360,11 +1385,11 @@ static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = fa
             a.blk = (const char*)op.blk + (size_t)a.p_out * a.g.Vh * (op.prec == P64 ? sizeof(d2) : sizeof(f2));
             if constexpr (PIN == P64) {
                 if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
-                launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, true>(c, op, a, plain);
+                launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, true>(c, op, a);
             } else {
                 if (op.prec != P32) throw Error(-1, "the clover kernels take FP64 or FP32 links");
-                if (op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, true>(c, op, a, plain);
-                else launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, true>(c, op, a, plain);
+                if (op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, true>(c, op, a);
+                else launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, true>(c, op, a);
             }
             FGI_LAUNCH_CHECK();
             return;
@@ -1373,12 +1398,12 @@ static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a, bool plain = fa
     }
     if constexpr (PIN == P64) {
         if (op.prec != P64) throw Error(-1, "FP64 spinors need FP64 links");
-        launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, false>(c, op, a, plain);
+        launch_dslash_rec<MODE, PIN, PC, POUT, PX, P64, 18, G5IN, false>(c, op, a);
     } else {
-        if (op.prec == P32 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, false>(c, op, a, plain);
-        else if (op.prec == P32) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, false>(c, op, a, plain);
-        else if (op.prec == P16 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 18, G5IN, false>(c, op, a, plain);
-        else if (op.prec == P16) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 12, G5IN, false>(c, op, a, plain);
+        if (op.prec == P32 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 18, G5IN, false>(c, op, a);
+        else if (op.prec == P32) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P32, 12, G5IN, false>(c, op, a);
+        else if (op.prec == P16 && op.recon == 18) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 18, G5IN, false>(c, op, a);
+        else if (op.prec == P16) launch_dslash_rec<MODE, PIN, PC, POUT, PX, P16, 12, G5IN, false>(c, op, a);
         else throw Error(-1, "sloppy spinors need sloppy links");
     }
     FGI_LAUNCH_CHECK();
@@ -1395,14 +1420,13 @@ static DArgs base_args(const FermionOp& op, int p_out) {
 
 static CGState* dev_state(Ctx& c) { return (CGState*)c.state.get(sizeof(CGState)); }
 
-void dslash(Ctx& c, const FermionOp& op, int out_parity, int prec_in, SpinorPtr in, int prec_out, SpinorPtr out,
-            bool plain) {
+void dslash(Ctx& c, const FermionOp& op, int out_parity, int prec_in, SpinorPtr in, int prec_out, SpinorPtr out) {
     DArgs a = base_args(op, out_parity);
     a.in = in;
     a.out = out;
-    if (prec_in == P64 && prec_out == P64) launch_dslash<M_HOP, P64, P64, P64, P64, 0>(c, op, a, plain);
-    else if (prec_in == P32 && prec_out == P32) launch_dslash<M_HOP, P32, P32, P32, P32, 0>(c, op, a, plain);
-    else if (prec_in == P16 && prec_out == P16) launch_dslash<M_HOP, P16, P16, P16, P32, 0>(c, op, a, plain);
+    if (prec_in == P64 && prec_out == P64) launch_dslash<M_HOP, P64, P64, P64, P64, 0>(c, op, a);
+    else if (prec_in == P32 && prec_out == P32) launch_dslash<M_HOP, P32, P32, P32, P32, 0>(c, op, a);
+    else if (prec_in == P16 && prec_out == P16) launch_dslash<M_HOP, P16, P16, P16, P32, 0>(c, op, a);
     else throw Error(-1, "dslash: unsupported precision pair");
 }
 
@@ -1659,7 +1683,7 @@ static void cg_iteration(Ctx& c, const FermionOp& ops, const CGVecs& v, int j) {
     CGState* st = dev_state(c);
     double* part = partial_buf(c, *ops.g);
     const int Vh = ops.g->Vh;
-    if (site_split(Vh))
+    if (site_split(c, Vh))
         hipLaunchKernelGGL((k_cg_p_split<PP, PX>), dim3(ds_blocks(c, Vh)), dim3(256), 0, c.stream, Vh, v.p, v.r, st,
                            (const double*)part, c.ds_xcd, j);
     else
@@ -1916,7 +1940,8 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     CGState* st = dev_state(c);
     double* scal = (double*)c.scal.get(sizeof(double) * 64);
     norm2(c, g, phi, scal);
-    const CGRun run{tol * tol, PX == P64 ? 0.0 : c.ru_delta * c.ru_delta, scal, c.host_scal};
+    const double drop = c.ru_delta;
+    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, scal, c.host_scal};
     d2* r64 = (d2*)c.cg_r.get(n64);
     auto start = [&](const double* part, int nb) {
         hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(DBS), 0, c.stream, st, run, part, nb);
@@ -2289,6 +2314,7 @@ template <int PP, int PX>
 static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops,
                                       const d2* phi, d2* X, double tol, int maxiter, bool guess) {
     const int nc = B.nc;
+    const double drop = c.ru_delta, ru2 = drop * drop;
     const size_t n64 = sizeof(d2) * 12 * (size_t)B.sites;
     std::vector<CGResult> res(nc, CGResult{0, 0, 0.0, 0});
     double* part = partial_buf(c, B);
@@ -2354,7 +2380,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
         CGState& h = hs[i];
         h = CGState{};
         h.rr[0] = rr0[i];
-        h.rr_stop = (PX == P64) ? target[i] : std::max(c.ru_delta * c.ru_delta * rr0[i], target[i]);
+        h.rr_stop = (PX == P64) ? target[i] : std::max(ru2 * rr0[i], target[i]);
         const bool zero = bb[i] == 0.0, there = guess && !zero && rr0[i] <= target[i];
         h.stop_at = (zero || there) ? 0 : INT_MAX;
         if (zero || there) {
@@ -2423,7 +2449,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             hs[i].stop_at = INT_MAX;
             hs[i].base = kend[i];
             hs[i].base0 = kend[i];
-            hs[i].rr_stop = (PX == P64) ? target[i] : std::max(c.ru_delta * c.ru_delta * rr, target[i]);
+            hs[i].rr_stop = (PX == P64) ? target[i] : std::max(ru2 * rr, target[i]);
         }
         upload_states(c, st, hs);  // act still set for the restarting chains
         if (restart && PX != P64) {

@@ -136,6 +136,12 @@ struct Ctx {
     // threads (= even sites) per block, and XCD-aware block order on/off
     int ds_bs = 256;
     int ds_xcd = 1;
+    // whether this call's Dslash-shaped kernels may share a site between waves:
+    // not with 16-bit fixed-point links, whose iteration counts on an
+    // ill-conditioned field move with the rounding of the FP16 projection (the
+    // compiler fuses it differently in the two kernels; 241 to 276 on a
+    // thermalised 8^4 at kappa = 0.158 over right-hand sides, either kernel)
+    bool split = true;
     double ru_delta = 0.1;     // reliable-update trigger |r| drop
     // single-lattice CG iteration: 0 the classic form (five launches), 1 the
     // Chronopoulos-Gear form with exact <p, A p> (four launches; fermion.hip)
@@ -159,9 +165,9 @@ struct Ctx {
 // 71.2 -> 70.0, 50.2 -> 52.3.
 constexpr int SPLIT_SITES = 64;
 constexpr int SPLIT_MAX_VH = 32768;
-inline bool site_split(int Vh) { return Vh <= SPLIT_MAX_VH; }
+inline bool site_split(const Ctx& c, int Vh) { return c.split && Vh <= SPLIT_MAX_VH; }
 // sites per block of the Dslash-shaped kernels on a lattice of Vh even sites
-inline int ds_sites(const Ctx& c, int Vh) { return site_split(Vh) ? SPLIT_SITES : c.ds_bs; }
+inline int ds_sites(const Ctx& c, int Vh) { return site_split(c, Vh) ? SPLIT_SITES : c.ds_bs; }
 enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
 
 // A batch of independent chains: their descriptors on the device and the
@@ -273,10 +279,8 @@ struct FermionOp {
     const void* blk = nullptr;   // clover: A_ee and A_oo^-1 (72 complex per site, the links' precision), else null
 };
 // out_{1-p} = D_{(1-p) p} in_p  (hopping term between parities)
-// plain: always with the summation order of the halo hop (one thread per site),
-// whatever the lattice size
 void dslash(Ctx&, const FermionOp&, int out_parity, int prec_in, SpinorPtr in, int prec_out,
-            SpinorPtr out, bool plain = false);
+            SpinorPtr out);
 // out_e = [g5] (in_e - kappa^2 D_eo t_o)  where t_o = D_oe in_e is computed too
 void mhat(Ctx&, const FermionOp&, int prec, SpinorPtr in_e, SpinorPtr tmp_o, SpinorPtr out_e,
           int dagger);
