@@ -1940,7 +1940,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     CGState* st = dev_state(c);
     double* scal = (double*)c.scal.get(sizeof(double) * 64);
     norm2(c, g, phi, scal);
-    const double drop = c.ru_delta;
+    const double drop = ru_drop(c, PP);
     const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, scal, c.host_scal};
     d2* r64 = (d2*)c.cg_r.get(n64);
     auto start = [&](const double* part, int nb) {
@@ -2314,7 +2314,7 @@ template <int PP, int PX>
 static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops,
                                       const d2* phi, d2* X, double tol, int maxiter, bool guess) {
     const int nc = B.nc;
-    const double drop = c.ru_delta, ru2 = drop * drop;
+    const double drop = ru_drop(c, PP), ru2 = drop * drop;
     const size_t n64 = sizeof(d2) * 12 * (size_t)B.sites;
     std::vector<CGResult> res(nc, CGResult{0, 0, 0.0, 0});
     double* part = partial_buf(c, B);

@@ -142,7 +142,7 @@ struct Ctx {
     // compiler fuses it differently in the two kernels; 241 to 276 on a
     // thermalised 8^4 at kappa = 0.158 over right-hand sides, either kernel)
     bool split = true;
-    double ru_delta = 0.1;     // reliable-update trigger |r| drop
+    double ru_delta = 0.0;     // reliable-update trigger |r| drop; 0: ru_drop's choice by storage
     // single-lattice CG iteration: 0 the classic form (five launches), 1 the
     // Chronopoulos-Gear form with exact <p, A p> (four launches; fermion.hip)
     int cg_form = 0;
@@ -168,6 +168,16 @@ constexpr int SPLIT_MAX_VH = 32768;
 inline bool site_split(const Ctx& c, int Vh) { return c.split && Vh <= SPLIT_MAX_VH; }
 // sites per block of the Dslash-shaped kernels on a lattice of Vh even sites
 inline int ds_sites(const Ctx& c, int Vh) { return site_split(c, Vh) ? SPLIT_SITES : c.ds_bs; }
+// |r| drop at which the true residual replaces an inner run's own: the caller's
+// (option "ru_delta"), or by storage.  FP32 loses nothing by a drop of 0.01: iterations
+// and us per solve to 1e-12, 0.1 against 0.01, 223, 14742 -> 223, 13885 on
+// 16^3x32 and 139, 4385 -> 139, 3960 on 12x10x14x18 (half the FP64 residuals);
+// near kappa_c on a thermalised 8^4 the iterations rise by 1 to 4 %, at 0.001 by
+// 4 to 7 %.  16-bit storage stays at 0.1: the rounding of its vectors drives the
+// recursion away there (fixed-point links, 0.03: 6 % at 223 iterations, a
+// quarter on a thermalised field near kappa_c).
+inline double ru_drop(const Ctx& c, int prec) { return c.ru_delta > 0.0 ? c.ru_delta : (prec == P32 ? 0.01 : 0.1); }
+
 enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
 
 // A batch of independent chains: their descriptors on the device and the
