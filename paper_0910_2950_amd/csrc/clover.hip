@@ -89,9 +89,11 @@ __device__ __forceinline__ int plane_index(int mu, int nu) {
 
 __device__ __forceinline__ int site_of(const Geom& g, const Coord& y) { return coord_parity(y) * g.Vh + cb_index(g, y); }
 
-// Fhat_{mu nu}(x) for the six planes, one thread per site (both parities)
-__global__ void __launch_bounds__(CBS) k_clover_fhat(Geom g, const d2* __restrict__ U, d2* __restrict__ fh) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+// Fhat_{mu nu}(x) for the six planes, one thread per site (both parities); in
+// XCD-owned slabs like k_clover_force (16^3x32, linear -> slabs: 162 -> 130 us,
+// the force 535 -> 421; the force at two waves per SIMD spills, 762)
+__global__ void __launch_bounds__(CBS) k_clover_fhat(Geom g, const d2* __restrict__ U, d2* __restrict__ fh, int xcd) {
+    const int t = slab_thread(g.Vh, 2, xcd);
     if (t >= g.V) return;
     const int p = t / g.Vh, s = t % g.Vh;
     const Coord x = cb_coords(g, p, s);
@@ -336,8 +338,8 @@ __device__ __forceinline__ M3<double> kt_at(const Geom& g, const d2* __restrict_
 //   S_dn = K(x) C + C K(x+mu) + U_nu(x-nu)^+ [K(x-nu) U_mu(x-nu) + U_mu(x-nu) K(x-nu+mu)] U_nu(x-nu+mu),
 // e_a of the sum is Re Tr[T^a U (S_up + S_dn^+)], so F_a += coef [TA(U (S_up + S_dn^+))]_a / 2.
 __global__ void __launch_bounds__(CBS) k_clover_force(Geom g, const d2* __restrict__ U, const d2* __restrict__ kt,
-                                                      double coef, double* __restrict__ F) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+                                                      double coef, double* __restrict__ F, int xcd) {
+    const int t = slab_thread(g.Vh, 8, xcd);
     if (t >= 4 * g.V) return;
     const int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
     const Coord x = cb_coords(g, p, s);
@@ -438,7 +440,7 @@ void clover_build(Ctx& c, const Geom& g, double kappa, double csw, const d2* U, 
                   double* det_action) {
     d2* fh = (d2*)c.cl_fh.get(sizeof(d2) * 54 * (size_t)g.V);
     double* ld = (double*)c.cl_ld.get(sizeof(double) * 2 * (size_t)g.V);
-    hipLaunchKernelGGL(k_clover_fhat, dim3(nb_of(g.V)), dim3(CBS), 0, c.stream, g, U, fh);
+    hipLaunchKernelGGL(k_clover_fhat, dim3(slab_blocks(g.Vh, 2, CBS, c.ds_xcd)), dim3(CBS), 0, c.stream, g, U, fh, c.ds_xcd);
     FGI_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_clover_blocks, dim3(nb_of(2L * g.V)), dim3(CBS), 0, c.stream, g, sigma_blocks(c),
                        kappa * csw, (const d2*)fh, blk, ld, invert_odd);
@@ -538,8 +540,8 @@ void clover_force(Ctx& c, const FermionOp& op, double csw, const d2* blk, const 
                        pf ? -2.0 * kc * pf_scale : 0.0, pf ? -2.0 * k * k * kc * pf_scale : 0.0,
                        -2.0 * kc * det_scale, (const d2*)Xe, (const d2*)xo, (const d2*)ye, (const d2*)yo, blk, kt);
     FGI_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_clover_force, dim3(nb_of(4L * g.V)), dim3(CBS), 0, c.stream, g, (const d2*)op.links,
-                       (const d2*)kt, coef, F);
+    hipLaunchKernelGGL(k_clover_force, dim3(slab_blocks(g.Vh, 8, CBS, c.ds_xcd)), dim3(CBS), 0, c.stream, g,
+                       (const d2*)op.links, (const d2*)kt, coef, F, c.ds_xcd);
     FGI_LAUNCH_CHECK();
 }
 

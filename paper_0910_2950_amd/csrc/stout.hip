@@ -72,6 +72,11 @@ __device__ __forceinline__ void link_of(const Geom& g, int t, int& mu, int& p, i
 
 }  // namespace
 
+// Block order of the three kernels below: XCD-owned slabs (slab_thread), so the
+// neighbour links (and M) of a block come from its own XCD's L2.  They are bound
+// by those loads and their register-held products at one or two waves per SIMD;
+// 16^3x32, linear -> slabs: level 161 -> 110 us, gamma 281 -> 225, gather 296 ->
+// 207 (two waves forced on gamma and gather spill 0.5 KB a lane: 241 and 507).
 // U' = exp(TA(C U^+)) U on link t
 __device__ __forceinline__ void stout_level_body(const Geom& g, double rho, const d2* __restrict__ U,
                                                  d2* __restrict__ Up, int t) {
@@ -87,8 +92,8 @@ __device__ __forceinline__ void stout_level_body(const Geom& g, double rho, cons
 }
 
 __global__ void __launch_bounds__(256) k_stout_level(Geom g, double rho, const d2* __restrict__ U,
-                                                    d2* __restrict__ Up) {
-    stout_level_body(g, rho, U, Up, blockIdx.x * blockDim.x + threadIdx.x);
+                                                    d2* __restrict__ Up, int xcd) {
+    stout_level_body(g, rho, U, Up, slab_thread(g.Vh, 8, xcd));
 }
 
 // batched chains (links of chain c from 9 * link0, 256 links per block)
@@ -153,8 +158,8 @@ __device__ __forceinline__ void stout_gamma_body(const Geom& g, double rho, cons
 
 __global__ void __launch_bounds__(256) k_stout_gamma(Geom g, double rho, const d2* __restrict__ U,
                                                     const double* __restrict__ Gp, double* __restrict__ part,
-                                                    d2* __restrict__ Mout) {
-    stout_gamma_body(g, rho, U, Gp, part, Mout, blockIdx.x * blockDim.x + threadIdx.x);
+                                                    d2* __restrict__ Mout, int xcd) {
+    stout_gamma_body(g, rho, U, Gp, part, Mout, slab_thread(g.Vh, 8, xcd));
 }
 
 __global__ void __launch_bounds__(256) k_stout_gamma_b(const ChainDesc* __restrict__ cd, int nc, double rho,
@@ -210,8 +215,8 @@ __device__ __forceinline__ void stout_gather_body(const Geom& g, const d2* __res
 
 __global__ void __launch_bounds__(256) k_stout_gather(Geom g, const d2* __restrict__ U, const d2* __restrict__ M,
                                                      const double* __restrict__ part, double* __restrict__ G,
-                                                     double coef, int accumulate) {
-    stout_gather_body(g, U, M, part, G, coef, accumulate, blockIdx.x * blockDim.x + threadIdx.x);
+                                                     double coef, int accumulate, int xcd) {
+    stout_gather_body(g, U, M, part, G, coef, accumulate, slab_thread(g.Vh, 8, xcd));
 }
 
 __global__ void __launch_bounds__(256) k_stout_gather_b(const ChainDesc* __restrict__ cd, int nc,
@@ -229,7 +234,8 @@ const d2* stout_smear(Ctx& c, const Geom& g, double rho, int n, const d2* U, d2*
     const d2* in = U;
     for (int k = 0; k < n; k++) {
         d2* out = levels + k * sz;
-        hipLaunchKernelGGL(k_stout_level, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, rho, in, out);
+        hipLaunchKernelGGL(k_stout_level, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, rho, in,
+                           out, c.ds_xcd);
         FGI_LAUNCH_CHECK();
         in = out;
     }
@@ -247,12 +253,12 @@ void stout_backprop(Ctx& c, const Geom& g, double rho, int n, const d2* U, const
     const double* Gin = Fs;
     for (int k = n - 1; k >= 0; k--) {
         const d2* Uk = k == 0 ? U : levels + (k - 1) * sz;
-        hipLaunchKernelGGL(k_stout_gamma, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, rho, Uk, Gin, part,
-                           M);
+        hipLaunchKernelGGL(k_stout_gamma, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, rho, Uk,
+                           Gin, part, M, c.ds_xcd);
         FGI_LAUNCH_CHECK();
         double* Gout = k == 0 ? F : ((n - 1 - k) % 2 == 0 ? ga : gb);
-        hipLaunchKernelGGL(k_stout_gather, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, Uk, M, part, Gout,
-                           k == 0 ? coef : 1.0, k == 0 ? accumulate : 0);
+        hipLaunchKernelGGL(k_stout_gather, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, Uk, M,
+                           part, Gout, k == 0 ? coef : 1.0, k == 0 ? accumulate : 0, c.ds_xcd);
         FGI_LAUNCH_CHECK();
         Gin = Gout;
     }
