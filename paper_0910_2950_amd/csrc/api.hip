@@ -1,6 +1,7 @@
 // C-ABI entry points, context and the integrator driver (host side).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <climits>
 #include <cmath>
@@ -1979,6 +1980,8 @@ void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<Ch
         d.user_U = ch.U;
         d.user_P = ch.P;
         d.user_eta = ch.eta;
+        B.min_vol = i ? std::min(B.min_vol, (long)d.g.V) : d.g.V;
+        B.max_vol = std::max(B.max_vol, (long)d.g.V);
         B.sites += d.g.Vh;
         B.vol += d.g.V;
         B.links += 4L * d.g.V;

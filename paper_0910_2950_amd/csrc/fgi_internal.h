@@ -187,6 +187,7 @@ struct Batch {
     int nc = 0;
     int nblk[4] = {0, 0, 0, 0};
     long sites = 0, vol = 0, links = 0;  // totals: sum Vh, sum V, sum 4V
+    long min_vol = 0, max_vol = 0;       // smallest and largest chain
     // Dslash-shaped launches, one per DsKind that has chains: block -> (chain,
     // block of the chain), then one (chain, its block count) per chain for the
     // reduction blocks

@@ -317,6 +317,96 @@ __global__ void __launch_bounds__(256) k_gauge_force(Geom g, double beta, const 
     gauge_force_body(g, beta, U, F, coef, accumulate, slab_thread(g.Vh, 8, xcd));
 }
 
+// Small lattices: one thread per link leaves the chip idle (4^4: 16 waves) and
+// the launch lasts as long as one thread's thirteen dependent products.  Here a
+// block's six waves share 64 links of one (mu, parity): wave w forms staple
+// w & 1 of the w / 2-th plane, the six staples meet in LDS and are summed in the
+// one-thread order, and four waves form the entries of U A that their force
+// components need.  The same operations in the same order: the same bits.
+// A force evaluation and a link update together, one thread per link -> split
+// (us): 4^4 18.5 -> 13.2, 6^4 22.0 -> 14.4, 8^4 20.4 -> 14.8, 8^3x16 24.1 -> 21.5;
+// above the line every SIMD has its waves already: 13440 sites 28.7 -> 31.2, 16^4
+// 73.0 -> 88.9.
+constexpr int GAUGE_SPLIT_MAX_V = 8192;
+struct GaugeSplitLds {
+    cx<double> st[6][9][64];
+    cx<double> A[9][64];
+};
+
+template <int MU>
+__device__ __forceinline__ void gauge_force_split_link(const Geom& g, double beta, const d2* __restrict__ U,
+                                                       double* __restrict__ F, double coef, int accumulate, int s,
+                                                       bool live, int p, int r, GaugeSplitLds& L) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k = w >> 1, nu = k + (k >= MU);
+    const Coord c = cb_coords(g, p, s);
+    M3<double> S;
+    if ((w & 1) == 0) {
+        const int s_pmu = cb_neighbour(g, c, MU, +1), s_pnu = cb_neighbour(g, c, nu, +1);
+        S = m3_mul_nd(m3_mul_nd(gauge_load(U, nu, 1 - p, s_pmu, g.Vh), gauge_load(U, MU, 1 - p, s_pnu, g.Vh)),
+                      gauge_load(U, nu, p, s, g.Vh));
+    } else {
+        const int s_mnu = cb_neighbour(g, c, nu, -1), s_pmu_mnu = cb_neighbour(g, cb_shift(g, c, MU, +1), nu, -1);
+        const M3<double> ed = m3_mul(gauge_load(U, MU, 1 - p, s_mnu, g.Vh), gauge_load(U, nu, p, s_pmu_mnu, g.Vh));
+        S = m3_mul_dn(ed, gauge_load(U, nu, 1 - p, s_mnu, g.Vh));
+    }
+    const M3<double> u = gauge_load(U, MU, p, s, g.Vh);
+#pragma unroll
+    for (int e = 0; e < 9; e++) L.st[w][e][lane] = S.e[e / 3][e % 3];
+    __syncthreads();
+    for (int e = w; e < 9; e += 6) {
+        cx<double> a = {0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < 6; j++) a = a + L.st[j][e][lane];
+        L.A[e][lane] = a;
+    }
+    __syncthreads();
+    if (w > 3 || !live) return;
+    auto W = [&](int i, int j) {
+        return u.e[i][0] * L.A[j][lane] + u.e[i][1] * L.A[3 + j][lane] + u.e[i][2] * L.A[6 + j][lane];
+    };
+    double* o = F + (size_t)(r * 8) * g.Vh + s;
+    const double f = -beta / 6.0 * coef;
+    auto put = [&](int a, double x) {
+        const double v = f * x;
+        o[(size_t)a * g.Vh] = accumulate ? o[(size_t)a * g.Vh] + v : v;
+    };
+    // the components of ta_components, from the entries they are made of
+    if (w == 0) {
+        const cx<double> a = W(0, 1), b = W(1, 0);
+        put(0, a.im + b.im);
+        put(1, a.re - b.re);
+    } else if (w == 1) {
+        const cx<double> a = W(0, 2), b = W(2, 0);
+        put(3, a.im + b.im);
+        put(4, a.re - b.re);
+    } else if (w == 2) {
+        const cx<double> a = W(1, 2), b = W(2, 1);
+        put(5, a.im + b.im);
+        put(6, a.re - b.re);
+    } else {
+        const double a = W(0, 0).im, b = W(1, 1).im, d = W(2, 2).im;
+        put(2, a - b);
+        put(7, 0.57735026918962576451 * (a + b - 2.0 * d));
+    }
+}
+
+__global__ void __launch_bounds__(384) k_gauge_force_split(Geom g, double beta, const d2* __restrict__ U,
+                                                          double* __restrict__ F, double coef, int accumulate,
+                                                          int xcd) {
+    __shared__ GaugeSplitLds L;
+    const int B = xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int r = B & 7, p = r & 1, s_ = (B >> 3) * 64 + (threadIdx.x & 63);
+    const bool live = s_ < g.Vh;
+    const int s = live ? s_ : g.Vh - 1;
+    switch (r >> 1) {
+    case 0: gauge_force_split_link<0>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
+    case 1: gauge_force_split_link<1>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
+    case 2: gauge_force_split_link<2>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
+    default: gauge_force_split_link<3>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
+    }
+}
+
 __global__ void __launch_bounds__(256) k_gauge_force_b(const ChainDesc* __restrict__ cd, int nc,
                                                       const d2* __restrict__ U, double* __restrict__ F, double coef,
                                                       int accumulate) {
@@ -329,8 +419,12 @@ __global__ void __launch_bounds__(256) k_gauge_force_b(const ChainDesc* __restri
 void rect_force(Ctx& c, const Geom& g, double beta, double c1, const d2* U, double* F, double coef);
 
 void gauge_force(Ctx& c, const Geom& g, double beta, const d2* U, double* F, double coef, int accumulate, double c1) {
-    hipLaunchKernelGGL(k_gauge_force, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, beta, U, F,
-                       coef * (1.0 - 8.0 * c1), accumulate, c.ds_xcd);
+    if (g.V <= GAUGE_SPLIT_MAX_V)
+        hipLaunchKernelGGL(k_gauge_force_split, dim3(8 * nblocks(g.Vh, 64)), dim3(384), 0, c.stream, g, beta, U, F,
+                           coef * (1.0 - 8.0 * c1), accumulate, c.ds_xcd);
+    else
+        hipLaunchKernelGGL(k_gauge_force, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, beta, U,
+                           F, coef * (1.0 - 8.0 * c1), accumulate, c.ds_xcd);
     FGI_LAUNCH_CHECK();
     if (c1 != 0.0) rect_force(c, g, beta, c1, U, F, coef);
 }
@@ -701,6 +795,13 @@ void rect_tangent(Ctx& c, const Geom& g, double beta, double c1, const d2* U, co
 }
 
 // ------------------------------------------------------------ updates ----
+// Lattices of at most SERIES_MAX_V sites take the exponential's series: their
+// update lasts as long as one wave's chain of transcendental calls (4^4, force
+// and update together 13.2 -> 10.1 us).  Large updates are bound by their 352
+// bytes per link either way (16^3x32: 35 us), and above the line the links keep
+// the bits that the seeded thermalisations and the committed calibration rest on.
+constexpr int SERIES_MAX_V = 2048;
+template <bool SERIES>
 __device__ __forceinline__ void link_update_body(const Geom& g, double h, const double* __restrict__ X,
                                                  const d2* __restrict__ src, d2* __restrict__ dst,
                                                  void* __restrict__ sloppy, int prec, int recon, int t) {
@@ -710,7 +811,7 @@ __device__ __forceinline__ void link_update_body(const Geom& g, double h, const 
     mom_load(X, mu, p, s, g.Vh, x);
 #pragma unroll
     for (int a = 0; a < 8; a++) x[a] *= h;
-    M3<double> E = su3_exp(alg_matrix(x));
+    M3<double> E = SERIES ? su3_exp_series(alg_matrix(x)) : su3_exp(alg_matrix(x));
     M3<double> u = m3_mul(E, gauge_load(src, mu, p, s, g.Vh));
     gauge_store(dst, mu, p, s, g.Vh, u);
     if (sloppy) {
@@ -721,25 +822,33 @@ __device__ __forceinline__ void link_update_body(const Geom& g, double h, const 
     }
 }
 
+template <bool SERIES>
 __global__ void __launch_bounds__(256) k_link_update(Geom g, double h, const double* __restrict__ X, const d2* __restrict__ src,
                               d2* __restrict__ dst, void* __restrict__ sloppy, int prec, int recon) {
-    link_update_body(g, h, X, src, dst, sloppy, prec, recon, blockIdx.x * blockDim.x + threadIdx.x);
+    link_update_body<SERIES>(g, h, X, src, dst, sloppy, prec, recon, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+// the chains of one kind (SERIES: at most SERIES_MAX_V sites)
+template <bool SERIES>
 __global__ void __launch_bounds__(256) k_link_update_b(const ChainDesc* __restrict__ cd, int nc, double h, const double* __restrict__ X,
                                 const d2* __restrict__ src, d2* __restrict__ dst, void* __restrict__ sloppy, int prec,
                                 int recon) {
     const int c = find_chain(cd, nc, blockIdx.x, GRID_4V);
     const ChainDesc& d = cd[c];
-    link_update_body(d.g, h, X + 8 * d.link0, src + 9 * d.link0, dst + 9 * d.link0,
+    if (SERIES != (d.g.V <= SERIES_MAX_V)) return;
+    link_update_body<SERIES>(d.g, h, X + 8 * d.link0, src + 9 * d.link0, dst + 9 * d.link0,
                      sloppy ? (char*)sloppy + sloppy_byte_off(d, prec, recon) : nullptr, prec, recon,
                      (blockIdx.x - d.blk0[GRID_4V]) * blockDim.x + threadIdx.x);
 }
 
 void link_update(Ctx& c, const Geom& g, double h, const double* X, const d2* src, d2* dst, void* sloppy, int prec,
                  int recon) {
-    hipLaunchKernelGGL(k_link_update, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, h, X, src, dst, sloppy,
-                       prec, recon);
+    if (g.V <= SERIES_MAX_V)   // blocks of one wave: more of the chip
+        hipLaunchKernelGGL(k_link_update<true>, dim3(nblocks(4L * g.V, 64)), dim3(64), 0, c.stream, g, h, X, src, dst,
+                           sloppy, prec, recon);
+    else
+        hipLaunchKernelGGL(k_link_update<false>, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, h, X, src, dst,
+                           sloppy, prec, recon);
     FGI_LAUNCH_CHECK();
 }
 
@@ -887,8 +996,12 @@ void gauge_force_b(Ctx& c, const Batch& B, const d2* U, double* F, double coef, 
 
 void link_update_b(Ctx& c, const Batch& B, double h, const double* X, const d2* src, d2* dst, void* sloppy, int prec,
                    int recon) {
-    hipLaunchKernelGGL(k_link_update_b, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, h, X, src, dst, sloppy,
-                       prec, recon);
+    if (B.min_vol <= SERIES_MAX_V)
+        hipLaunchKernelGGL(k_link_update_b<true>, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, h, X, src,
+                           dst, sloppy, prec, recon);
+    if (B.max_vol > SERIES_MAX_V)
+        hipLaunchKernelGGL(k_link_update_b<false>, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, h, X, src,
+                           dst, sloppy, prec, recon);
     FGI_LAUNCH_CHECK();
 }
 
