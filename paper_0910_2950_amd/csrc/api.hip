@@ -1972,9 +1972,10 @@ void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<Ch
         d.kappa = ch.kappa;
         const long n[4] = {d.g.Vh, d.g.V, 4L * d.g.V, d.g.Vh};
         const int bsz[4] = {256, 256, 256, ds_sites(c, d.g.Vh)};
-        for (int k = 0; k < 4; k++) {
+        for (int k = 0; k < 5; k++) {
             d.blk0[k] = B.nblk[k];
-            d.nblk[k] = (int)((n[k] + bsz[k] - 1) / bsz[k]);
+            d.nblk[k] = k == GRID_GS ? (d.g.V <= GAUGE_SPLIT_MAX_V ? 8 * ((d.g.Vh + 63) / 64) : 0)
+                                     : (int)((n[k] + bsz[k] - 1) / bsz[k]);
             B.nblk[k] += d.nblk[k];
         }
         d.user_U = ch.U;

@@ -116,7 +116,8 @@ __device__ __forceinline__ int slab_thread(int Vh, int nt, int xcd) {
 // --------------------------------------------------------------------------
 // GRID_VH, GRID_V, GRID_4V: blocks of 256 even sites, sites or links;
 // GRID_DS: even sites in blocks of the Dslash block size (a tuned schedule)
-enum GridKind { GRID_VH = 0, GRID_V = 1, GRID_4V = 2, GRID_DS = 3 };
+// GRID_GS: 64 links of one (mu, parity), of the chains whose gauge force is split
+enum GridKind { GRID_VH = 0, GRID_V = 1, GRID_4V = 2, GRID_DS = 3, GRID_GS = 4 };
 
 struct ChainDesc {
     Geom g;
@@ -124,8 +125,8 @@ struct ChainDesc {
     long vol0;      // sum of V (per-site densities)
     long link0;     // sum of 4V (link / momentum offsets)
     double beta, kappa;
-    int blk0[4];    // first block of the chain in each grid kind
-    int nblk[4];    // its number of blocks there
+    int blk0[5];    // first block of the chain in each grid kind
+    int nblk[5];    // its number of blocks there
     const void* user_U;   // user-layout buffers (pack / unpack)
     void* user_P;
     const void* user_eta;

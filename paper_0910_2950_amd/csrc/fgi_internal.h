@@ -178,6 +178,14 @@ inline int ds_sites(const Ctx& c, int Vh) { return site_split(c, Vh) ? SPLIT_SIT
 // quarter on a thermalised field near kappa_c).
 inline double ru_drop(const Ctx& c, int prec) { return c.ru_delta > 0.0 ? c.ru_delta : (prec == P32 ? 0.01 : 0.1); }
 
+// Lattices of at most GAUGE_SPLIT_MAX_V sites form a link's staples in six waves
+// (k_gauge_force_split).  A force evaluation and a link update together, one thread
+// per link -> split (us): 4^4 18.5 -> 13.2, 6^4 22.0 -> 14.4, 8^4 20.4 -> 14.8,
+// 8^3x16 24.1 -> 21.5; with the rectangles 46.8 -> 18.1, 52.3 -> 20.1, 53.3 -> 25.0,
+// 56.8 -> 39.3.  Above the line every SIMD has its waves already: 13440 sites
+// 28.7 -> 31.2 (with the rectangles 68.0 -> 66.7), 16^4 73.0 -> 88.9 (203 -> 200).
+constexpr int GAUGE_SPLIT_MAX_V = 8192;
+
 enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
 
 // A batch of independent chains: their descriptors on the device and the
@@ -185,7 +193,7 @@ enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
 struct Batch {
     const ChainDesc* cd = nullptr;   // device array [nc]
     int nc = 0;
-    int nblk[4] = {0, 0, 0, 0};
+    int nblk[5] = {0, 0, 0, 0, 0};
     long sites = 0, vol = 0, links = 0;  // totals: sum Vh, sum V, sum 4V
     long min_vol = 0, max_vol = 0;       // smallest and largest chain
     // Dslash-shaped launches, one per DsKind that has chains: block -> (chain,

@@ -264,35 +264,201 @@ void final_sum(Ctx& c, const double* partial, int n, double* out) {
 //                                     + U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)];
 // the part of S_G holding U_mu(x) is -beta/3 ReTr(U_mu(x) A_mu(x)), so
 // F_mu(x) = -e S = -(beta/6) TA(U_mu(x) A_mu(x)).
+//
+// The improved action adds c1 times the six rectangle staples per nu.  They are
+// the two plaquette staples with one of their three links replaced by that link's
+// own staple pointing outwards: the upper one, a b^+ c^+ (a = U_nu(x+mu), b =
+// U_mu(x+nu), c = U_nu(x)), with a by a' = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^+,
+// b by b' = U_nu(x+nu) U_mu(x+2nu) U_nu(x+mu+nu)^+ or c by c' = U_mu(x-mu)^+
+// U_nu(x-mu) U_mu(x-mu+nu); the lower one, (e d)^+ f, alike.  So
+//   f0 a b^+ c^+ + f1 (a' b^+ c^+ + a b'^+ c^+ + a b^+ c'^+)
+//     = [f0 a b^+ + f1 (a' b^+ + a b'^+)] c^+ + f1 (a b^+) c'^+,
+// eleven products for a half, the plaquette included.
+struct ForceCoef { double f0, f1; };   // of the plaquette and of the rectangle staples
+
+// the upper (UP) or lower plaquette staple of link (MU, x) in the (MU, nu) plane
+template <int MU, bool UP>
+__device__ __forceinline__ M3<double> staple(const Geom& g, const d2* __restrict__ U, const Coord& c, int p, int s,
+                                             int nu) {
+    const Coord cm = cb_shift(g, c, MU, +1);
+    if (UP) {   // U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
+        const int sm = cb_index(g, cm), sn = cb_neighbour(g, c, nu, +1);
+        return m3_mul_nd(m3_mul_nd(gauge_load(U, nu, 1 - p, sm, g.Vh), gauge_load(U, MU, 1 - p, sn, g.Vh)),
+                         gauge_load(U, nu, p, s, g.Vh));
+    }
+    // (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
+    const int sb = cb_neighbour(g, c, nu, -1), smb = cb_neighbour(g, cm, nu, -1);
+    return m3_mul_dn(m3_mul(gauge_load(U, MU, 1 - p, sb, g.Vh), gauge_load(U, nu, p, smb, g.Vh)),
+                     gauge_load(U, nu, 1 - p, sb, g.Vh));
+}
+
+// One of the three turns of a half of the improved staples, added to A; T is
+// carried from turn to turn.  Turn 0: T = f0 a b^+, A += f1 (a b^+) c'^+; turn 1:
+// T += f1 a b'^+; turn 2: T += f1 a' b^+, A += T c^+ (the lower half alike).  The
+// turns are blocks of a rolled loop: only A and T live across them (the links they
+// share are loaded again), so a turn's five matrices fit two waves per SIMD; as one
+// straight piece the compiler hoists the loads and spills 3 KB a lane.
+template <int MU, bool UP>
+__device__ __forceinline__ void rect_turn(const Geom& g, const d2* __restrict__ U, const Coord& c, int p, int s, int nu,
+                                          int turn, const ForceCoef& k, M3<double>& A, M3<double>& T) {
+    const int o = 1 - p;
+    const Coord cm = cb_shift(g, c, MU, +1);
+    // a load the compiler cannot take for one it has made before: the links that the
+    // turns share, kept live from turn to turn, would spill
+    auto ld = [&](int mu, int par, int site) {
+        asm volatile("" : "+v"(site));
+        return gauge_load(U, mu, par, site, g.Vh);
+    };
+    M3<double> l;
+    if (UP) {
+        const int sm = cb_index(g, cm), sn = cb_neighbour(g, c, nu, +1);
+        if (turn == 0) {          // c' = U_mu(x-mu)^+ U_nu(x-mu) U_mu(x-mu+nu)
+            const Coord cl = cb_shift(g, c, MU, -1);
+            const int sl = cb_index(g, cl);
+            l = m3_mul(m3_mul_dn(ld(MU, o, sl), ld(nu, o, sl)),
+                       ld(MU, p, cb_neighbour(g, cl, nu, +1)));
+            m3_scale(l, k.f1);
+            T = m3_mul_nd(ld(nu, o, sm), ld(MU, o, sn));
+            m3_acc(A, m3_mul_nd(T, l));
+            m3_scale(T, k.f0);
+        } else if (turn == 1) {   // b' = U_nu(x+nu) U_mu(x+2nu) U_nu(x+mu+nu)^+
+            const int s2n = cb_neighbour(g, cb_shift(g, c, nu, +1), nu, +1), smn = cb_neighbour(g, cm, nu, +1);
+            l = m3_mul_nd(m3_mul(ld(nu, o, sn), ld(MU, p, s2n)),
+                          ld(nu, p, smn));
+            m3_scale(l, k.f1);
+            m3_acc(T, m3_mul_nd(ld(nu, o, sm), l));
+        } else {                  // a' = U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^+
+            const int s2m = cb_neighbour(g, cm, MU, +1), smn = cb_neighbour(g, cm, nu, +1);
+            l = m3_mul_nd(m3_mul(ld(MU, o, sm), ld(nu, p, s2m)),
+                          ld(MU, p, smn));
+            m3_scale(l, k.f1);
+            m3_acc(T, m3_mul_nd(l, ld(MU, o, sn)));
+            m3_acc(A, m3_mul_nd(T, ld(nu, p, s)));
+        }
+    } else {
+        const Coord cb = cb_shift(g, c, nu, -1), cmb = cb_shift(g, cm, nu, -1);
+        const int sb = cb_index(g, cb), smb = cb_index(g, cmb);
+        if (turn == 0) {          // f' = U_mu(x-nu-mu)^+ U_nu(x-nu-mu) U_mu(x-mu)
+            const Coord cl = cb_shift(g, c, MU, -1);
+            const int slb = cb_neighbour(g, cl, nu, -1);
+            l = m3_mul(m3_mul_dn(ld(MU, p, slb), ld(nu, p, slb)),
+                       ld(MU, o, cb_index(g, cl)));
+            m3_scale(l, k.f1);
+            T = m3_mul(ld(MU, o, sb), ld(nu, p, smb));
+            m3_acc(A, m3_mul_dn(T, l));
+            m3_scale(T, k.f0);
+        } else if (turn == 1) {   // e' = U_nu(x-2nu)^+ U_mu(x-2nu) U_nu(x-2nu+mu)
+            const int s2b = cb_neighbour(g, cb, nu, -1), sm2b = cb_neighbour(g, cmb, nu, -1);
+            l = m3_mul(m3_mul_dn(ld(nu, p, s2b), ld(MU, p, s2b)),
+                       ld(nu, o, sm2b));
+            m3_scale(l, k.f1);
+            m3_acc(T, m3_mul(l, ld(nu, p, smb)));
+        } else {                  // d' = U_mu(x+mu-nu) U_nu(x+2mu-nu) U_mu(x+mu)^+
+            const int s2mb = cb_neighbour(g, cmb, MU, +1);
+            l = m3_mul_nd(m3_mul(ld(MU, p, smb), ld(nu, o, s2mb)),
+                          ld(MU, o, cb_index(g, cm)));
+            m3_scale(l, k.f1);
+            m3_acc(T, m3_mul(ld(MU, o, sb), l));
+            m3_acc(A, m3_mul_dn(T, ld(nu, o, sb)));
+        }
+    }
+}
+
+// s, as a value the compiler cannot recognise as one it has used before
+__device__ __forceinline__ int again(int s) {
+    asm volatile("" : "+v"(s));
+    return s;
+}
+
+// The same half as three turns of rect_turn, in one piece: one wave of a split
+// link has nothing else to do while it waits, so the loads of a turn overlap the
+// products of the last (force and update, turns -> piece, us: 4^4 25.5 -> 18.4,
+// 8^3x16 60.7 -> 40.5; over the six halves of an unsplit link the turns are the
+// faster, 16^3x32 409 -> 382, 32^3x64 8068 -> 7617).  again() marks links that are
+// loaded again because, kept live, they would spill.
+template <int MU, bool UP>
+__device__ __forceinline__ M3<double> rect_half(const Geom& g, const d2* __restrict__ U, const Coord& c, int p, int s,
+                                                int nu, const ForceCoef& k) {
+    const int o = 1 - p;
+    const Coord cm = cb_shift(g, c, MU, +1);
+    const Coord cl = cb_shift(g, c, MU, -1);
+    M3<double> A, T;
+    if (UP) {
+        const int sm = again(cb_index(g, cm)), sn = cb_neighbour(g, c, nu, +1), sl = again(cb_index(g, cl));
+        const Coord cmn = cb_shift(g, cm, nu, +1);
+        const int smn = cb_index(g, cmn);
+        M3<double> l = m3_mul(m3_mul_dn(gauge_load(U, MU, o, sl, g.Vh), gauge_load(U, nu, o, sl, g.Vh)),
+                              gauge_load(U, MU, p, cb_neighbour(g, cl, nu, +1), g.Vh));
+        m3_scale(l, k.f1);
+        T = m3_mul_nd(gauge_load(U, nu, o, sm, g.Vh), gauge_load(U, MU, o, sn, g.Vh));
+        A = m3_mul_nd(T, l);
+        m3_scale(T, k.f0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int s2n = cb_neighbour(g, cb_shift(g, c, nu, +1), nu, +1);
+        l = m3_mul_nd(m3_mul(gauge_load(U, nu, o, sn, g.Vh), gauge_load(U, MU, p, s2n, g.Vh)),
+                      gauge_load(U, nu, p, smn, g.Vh));
+        m3_scale(l, k.f1);
+        m3_acc(T, m3_mul_nd(gauge_load(U, nu, o, again(sm), g.Vh), l));
+        __builtin_amdgcn_sched_barrier(0);
+        const int s2m = cb_neighbour(g, cm, MU, +1);
+        l = m3_mul_nd(m3_mul(gauge_load(U, MU, o, again(sm), g.Vh), gauge_load(U, nu, p, s2m, g.Vh)),
+                      gauge_load(U, MU, p, smn, g.Vh));
+        m3_scale(l, k.f1);
+        m3_acc(T, m3_mul_nd(l, gauge_load(U, MU, o, again(sn), g.Vh)));
+        m3_acc(A, m3_mul_nd(T, gauge_load(U, nu, p, again(s), g.Vh)));
+    } else {
+        const Coord cb = cb_shift(g, c, nu, -1), cmb = cb_shift(g, cm, nu, -1), clb = cb_shift(g, cl, nu, -1);
+        const int sm = again(cb_index(g, cm)), sb = cb_index(g, cb), smb = cb_index(g, cmb), slb = cb_index(g, clb);
+        M3<double> l = m3_mul(m3_mul_dn(gauge_load(U, MU, p, slb, g.Vh), gauge_load(U, nu, p, slb, g.Vh)),
+                              gauge_load(U, MU, o, again(cb_index(g, cl)), g.Vh));
+        m3_scale(l, k.f1);
+        T = m3_mul(gauge_load(U, MU, o, sb, g.Vh), gauge_load(U, nu, p, smb, g.Vh));
+        A = m3_mul_dn(T, l);
+        m3_scale(T, k.f0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int s2b = cb_neighbour(g, cb, nu, -1), sm2b = cb_neighbour(g, cmb, nu, -1);
+        l = m3_mul(m3_mul_dn(gauge_load(U, nu, p, s2b, g.Vh), gauge_load(U, MU, p, s2b, g.Vh)),
+                   gauge_load(U, nu, o, sm2b, g.Vh));
+        m3_scale(l, k.f1);
+        m3_acc(T, m3_mul(l, gauge_load(U, nu, p, again(smb), g.Vh)));
+        __builtin_amdgcn_sched_barrier(0);
+        const int s2mb = cb_neighbour(g, cmb, MU, +1);
+        l = m3_mul_nd(m3_mul(gauge_load(U, MU, p, again(smb), g.Vh), gauge_load(U, nu, o, s2mb, g.Vh)),
+                      gauge_load(U, MU, o, sm, g.Vh));
+        m3_scale(l, k.f1);
+        m3_acc(T, m3_mul(gauge_load(U, MU, o, again(sb), g.Vh), l));
+        m3_acc(A, m3_mul_dn(T, gauge_load(U, nu, o, again(sb), g.Vh)));
+    }
+    return A;
+}
+
 // one link U_mu(x); MU known at compile time (every block of the force
 // launch holds links of one direction, so the switch below does not diverge)
-template <int MU>
-__device__ __forceinline__ void gauge_force_link(const Geom& g, double beta, const d2* __restrict__ U,
-                                                 double* __restrict__ F, double coef, int accumulate, int s, int p,
-                                                 int r) {
+template <int MU, bool IMP>
+__device__ __forceinline__ void gauge_force_link(const Geom& g, double f, const ForceCoef& k, const d2* __restrict__ U,
+                                                 double* __restrict__ F, int accumulate, int s, int p, int r) {
     const Coord c = cb_coords(g, p, s);
-    const int s_pmu = cb_neighbour(g, c, MU, +1);
-    const Coord cpm = cb_shift(g, c, MU, +1);
     M3<double> A = m3_zero<double>();
+    if constexpr (IMP) {
+        M3<double> T = m3_zero<double>();
 #pragma unroll 1
-    for (int nu = 0; nu < 4; nu++) {
-        if (nu == MU) continue;
-        int s_pnu = cb_neighbour(g, c, nu, +1);
-        int s_mnu = cb_neighbour(g, c, nu, -1);
-        int s_pmu_mnu = cb_neighbour(g, cpm, nu, -1);
-        // upper: U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
-        M3<double> up = m3_mul_nd(m3_mul_nd(gauge_load(U, nu, 1 - p, s_pmu, g.Vh), gauge_load(U, MU, 1 - p, s_pnu, g.Vh)),
-                                  gauge_load(U, nu, p, s, g.Vh));
-        m3_acc(A, up);
-        // lower: (U_mu(x-nu) U_nu(x+mu-nu))^+ U_nu(x-nu)
-        M3<double> ed = m3_mul(gauge_load(U, MU, 1 - p, s_mnu, g.Vh), gauge_load(U, nu, p, s_pmu_mnu, g.Vh));
-        m3_acc(A, m3_mul_dn(ed, gauge_load(U, nu, 1 - p, s_mnu, g.Vh)));
+        for (int j = 0; j < 18; j++) {
+            const int h = j / 3, turn = j - 3 * h, nu = (h >> 1) + ((h >> 1) >= MU);
+            if (h & 1) rect_turn<MU, false>(g, U, c, p, s, nu, turn, k, A, T);
+            else rect_turn<MU, true>(g, U, c, p, s, nu, turn, k, A, T);
+        }
+    } else {
+#pragma unroll 1
+        for (int nu = 0; nu < 4; nu++) {
+            if (nu == MU) continue;
+            m3_acc(A, staple<MU, true>(g, U, c, p, s, nu));
+            m3_acc(A, staple<MU, false>(g, U, c, p, s, nu));
+        }
     }
     M3<double> W = m3_mul(gauge_load(U, MU, p, s, g.Vh), A);
     double x[8];
     ta_components(W, x);
     double* o = F + (size_t)(r * 8) * g.Vh + s;
-    double f = -beta / 6.0 * coef;
 #pragma unroll
     for (int a = 0; a < 8; a++) {
         double v = f * x[a];
@@ -300,21 +466,29 @@ __device__ __forceinline__ void gauge_force_link(const Geom& g, double beta, con
     }
 }
 
-__device__ __forceinline__ void gauge_force_body(const Geom& g, double beta, const d2* __restrict__ U,
-                                                 double* __restrict__ F, double coef, int accumulate, int t) {
+template <bool IMP>
+__device__ __forceinline__ void gauge_force_body(const Geom& g, double f, const ForceCoef& k, const d2* __restrict__ U,
+                                                 double* __restrict__ F, int accumulate, int t) {
     if (t >= 4 * g.V) return;
     int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
     switch (mu) {
-    case 0: gauge_force_link<0>(g, beta, U, F, coef, accumulate, s, p, r); break;
-    case 1: gauge_force_link<1>(g, beta, U, F, coef, accumulate, s, p, r); break;
-    case 2: gauge_force_link<2>(g, beta, U, F, coef, accumulate, s, p, r); break;
-    default: gauge_force_link<3>(g, beta, U, F, coef, accumulate, s, p, r); break;
+    case 0: gauge_force_link<0, IMP>(g, f, k, U, F, accumulate, s, p, r); break;
+    case 1: gauge_force_link<1, IMP>(g, f, k, U, F, accumulate, s, p, r); break;
+    case 2: gauge_force_link<2, IMP>(g, f, k, U, F, accumulate, s, p, r); break;
+    default: gauge_force_link<3, IMP>(g, f, k, U, F, accumulate, s, p, r); break;
     }
 }
 
-__global__ void __launch_bounds__(256) k_gauge_force(Geom g, double beta, const d2* __restrict__ U,
-                                                    double* __restrict__ F, double coef, int accumulate, int xcd) {
-    gauge_force_body(g, beta, U, F, coef, accumulate, slab_thread(g.Vh, 8, xcd));
+// f multiplies TA(U A); with IMP the staples carry k.f0 and k.f1.  With IMP bound by
+// FP64 VALU at two waves per SIMD: 67 products a link, 1.3e4 flops, 20 TFLOP/s at
+// 16^3x32.  A plaquette launch and one of the 18 rectangle staples, paired on the
+// steps they share, read links twice and F back: force and update at 16^3x32 487 ->
+// 381 us, 32^3x64 9.93 -> 7.66 ms.  Storing the link staples that the rectangles
+// share needs fewer products and lost to the traffic (581 us).
+template <bool IMP>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_gauge_force(Geom g, double f, ForceCoef k, const d2* __restrict__ U, double* __restrict__ F, int accumulate, int xcd) {
+    gauge_force_body<IMP>(g, f, k, U, F, accumulate, slab_thread(g.Vh, 8, xcd));
 }
 
 // Small lattices: one thread per link leaves the chip idle (4^4: 16 waves) and
@@ -322,33 +496,27 @@ __global__ void __launch_bounds__(256) k_gauge_force(Geom g, double beta, const 
 // block's six waves share 64 links of one (mu, parity): wave w forms staple
 // w & 1 of the w / 2-th plane, the six staples meet in LDS and are summed in the
 // one-thread order, and four waves form the entries of U A that their force
-// components need.  The same operations in the same order: the same bits.
-// A force evaluation and a link update together, one thread per link -> split
-// (us): 4^4 18.5 -> 13.2, 6^4 22.0 -> 14.4, 8^4 20.4 -> 14.8, 8^3x16 24.1 -> 21.5;
-// above the line every SIMD has its waves already: 13440 sites 28.7 -> 31.2, 16^4
-// 73.0 -> 88.9.
-constexpr int GAUGE_SPLIT_MAX_V = 8192;
+// components need.  Without the rectangles: the same operations in the same order
+// as unsplit, the same bits.
 struct GaugeSplitLds {
     cx<double> st[6][9][64];
     cx<double> A[9][64];
 };
 
-template <int MU>
-__device__ __forceinline__ void gauge_force_split_link(const Geom& g, double beta, const d2* __restrict__ U,
-                                                       double* __restrict__ F, double coef, int accumulate, int s,
-                                                       bool live, int p, int r, GaugeSplitLds& L) {
+template <int MU, bool IMP>
+__device__ __forceinline__ void gauge_force_split_link(const Geom& g, double f, const ForceCoef& kf,
+                                                       const d2* __restrict__ U, double* __restrict__ F, int accumulate,
+                                                       int s, bool live, int p, int r, GaugeSplitLds& L) {
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int k = w >> 1, nu = k + (k >= MU);
     const Coord c = cb_coords(g, p, s);
     M3<double> S;
-    if ((w & 1) == 0) {
-        const int s_pmu = cb_neighbour(g, c, MU, +1), s_pnu = cb_neighbour(g, c, nu, +1);
-        S = m3_mul_nd(m3_mul_nd(gauge_load(U, nu, 1 - p, s_pmu, g.Vh), gauge_load(U, MU, 1 - p, s_pnu, g.Vh)),
-                      gauge_load(U, nu, p, s, g.Vh));
+    if constexpr (IMP) {
+        if (w & 1) S = rect_half<MU, false>(g, U, c, p, s, nu, kf);
+        else S = rect_half<MU, true>(g, U, c, p, s, nu, kf);
     } else {
-        const int s_mnu = cb_neighbour(g, c, nu, -1), s_pmu_mnu = cb_neighbour(g, cb_shift(g, c, MU, +1), nu, -1);
-        const M3<double> ed = m3_mul(gauge_load(U, MU, 1 - p, s_mnu, g.Vh), gauge_load(U, nu, p, s_pmu_mnu, g.Vh));
-        S = m3_mul_dn(ed, gauge_load(U, nu, 1 - p, s_mnu, g.Vh));
+        if (w & 1) S = staple<MU, false>(g, U, c, p, s, nu);
+        else S = staple<MU, true>(g, U, c, p, s, nu);
     }
     const M3<double> u = gauge_load(U, MU, p, s, g.Vh);
 #pragma unroll
@@ -366,7 +534,6 @@ __device__ __forceinline__ void gauge_force_split_link(const Geom& g, double bet
         return u.e[i][0] * L.A[j][lane] + u.e[i][1] * L.A[3 + j][lane] + u.e[i][2] * L.A[6 + j][lane];
     };
     double* o = F + (size_t)(r * 8) * g.Vh + s;
-    const double f = -beta / 6.0 * coef;
     auto put = [&](int a, double x) {
         const double v = f * x;
         o[(size_t)a * g.Vh] = accumulate ? o[(size_t)a * g.Vh] + v : v;
@@ -391,42 +558,64 @@ __device__ __forceinline__ void gauge_force_split_link(const Geom& g, double bet
     }
 }
 
-__global__ void __launch_bounds__(384) k_gauge_force_split(Geom g, double beta, const d2* __restrict__ U,
-                                                          double* __restrict__ F, double coef, int accumulate,
-                                                          int xcd) {
-    __shared__ GaugeSplitLds L;
-    const int B = xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+template <bool IMP>
+__device__ __forceinline__ void gauge_force_split_block(const Geom& g, double f, const ForceCoef& k,
+                                                        const d2* __restrict__ U, double* __restrict__ F,
+                                                        int accumulate, int B, GaugeSplitLds& L) {
     const int r = B & 7, p = r & 1, s_ = (B >> 3) * 64 + (threadIdx.x & 63);
     const bool live = s_ < g.Vh;
     const int s = live ? s_ : g.Vh - 1;
     switch (r >> 1) {
-    case 0: gauge_force_split_link<0>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
-    case 1: gauge_force_split_link<1>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
-    case 2: gauge_force_split_link<2>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
-    default: gauge_force_split_link<3>(g, beta, U, F, coef, accumulate, s, live, p, r, L); break;
+    case 0: gauge_force_split_link<0, IMP>(g, f, k, U, F, accumulate, s, live, p, r, L); break;
+    case 1: gauge_force_split_link<1, IMP>(g, f, k, U, F, accumulate, s, live, p, r, L); break;
+    case 2: gauge_force_split_link<2, IMP>(g, f, k, U, F, accumulate, s, live, p, r, L); break;
+    default: gauge_force_split_link<3, IMP>(g, f, k, U, F, accumulate, s, live, p, r, L); break;
     }
 }
 
-__global__ void __launch_bounds__(256) k_gauge_force_b(const ChainDesc* __restrict__ cd, int nc,
-                                                      const d2* __restrict__ U, double* __restrict__ F, double coef,
-                                                      int accumulate) {
-    const int c = find_chain(cd, nc, blockIdx.x, GRID_4V);
-    const ChainDesc& d = cd[c];
-    gauge_force_body(d.g, d.beta, U + 9 * d.link0, F + 8 * d.link0, coef, accumulate,
-                     (blockIdx.x - d.blk0[GRID_4V]) * blockDim.x + threadIdx.x);
+template <bool IMP>
+__global__ void __launch_bounds__(384) k_gauge_force_split(Geom g, double f, ForceCoef k, const d2* __restrict__ U,
+                                                          double* __restrict__ F, int accumulate, int xcd) {
+    __shared__ GaugeSplitLds L;
+    gauge_force_split_block<IMP>(g, f, k, U, F, accumulate, xcd ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x, L);
 }
 
-void rect_force(Ctx& c, const Geom& g, double beta, double c1, const d2* U, double* F, double coef);
+// the chains of a batch that take the split kernel (GRID_GS)
+template <bool IMP>
+__global__ void __launch_bounds__(384) k_gauge_force_split_b(const ChainDesc* __restrict__ cd, int nc,
+                                                            const d2* __restrict__ U, double* __restrict__ F,
+                                                            double coef, double c1, int accumulate) {
+    __shared__ GaugeSplitLds L;
+    const int c = find_chain(cd, nc, blockIdx.x, GRID_GS);
+    const ChainDesc& d = cd[c];
+    gauge_force_split_block<IMP>(d.g, -d.beta / 6.0 * coef, ForceCoef{1.0 - 8.0 * c1, c1}, U + 9 * d.link0,
+                                 F + 8 * d.link0, accumulate, blockIdx.x - d.blk0[GRID_GS], L);
+}
+
+template <bool IMP>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_gauge_force_b(const ChainDesc* __restrict__ cd, int nc, const d2* __restrict__ U, double* __restrict__ F, double coef,
+                double c1, int accumulate) {
+    const int c = find_chain(cd, nc, blockIdx.x, GRID_4V);
+    const ChainDesc& d = cd[c];
+    if (d.g.V <= GAUGE_SPLIT_MAX_V) return;
+    gauge_force_body<IMP>(d.g, -d.beta / 6.0 * coef, ForceCoef{1.0 - 8.0 * c1, c1}, U + 9 * d.link0, F + 8 * d.link0,
+                          accumulate, (blockIdx.x - d.blk0[GRID_4V]) * blockDim.x + threadIdx.x);
+}
 
 void gauge_force(Ctx& c, const Geom& g, double beta, const d2* U, double* F, double coef, int accumulate, double c1) {
-    if (g.V <= GAUGE_SPLIT_MAX_V)
-        hipLaunchKernelGGL(k_gauge_force_split, dim3(8 * nblocks(g.Vh, 64)), dim3(384), 0, c.stream, g, beta, U, F,
-                           coef * (1.0 - 8.0 * c1), accumulate, c.ds_xcd);
-    else
-        hipLaunchKernelGGL(k_gauge_force, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, beta, U,
-                           F, coef * (1.0 - 8.0 * c1), accumulate, c.ds_xcd);
+    const double f = -beta / 6.0 * coef;
+    const ForceCoef k{1.0 - 8.0 * c1, c1};
+    if (g.V <= GAUGE_SPLIT_MAX_V) {
+        const dim3 nb(8 * nblocks(g.Vh, 64)), bs(384);
+        if (c1 != 0.0) hipLaunchKernelGGL(k_gauge_force_split<true>, nb, bs, 0, c.stream, g, f, k, U, F, accumulate, c.ds_xcd);
+        else hipLaunchKernelGGL(k_gauge_force_split<false>, nb, bs, 0, c.stream, g, f, k, U, F, accumulate, c.ds_xcd);
+    } else {
+        const dim3 nb(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), bs(BS);
+        if (c1 != 0.0) hipLaunchKernelGGL(k_gauge_force<true>, nb, bs, 0, c.stream, g, f, k, U, F, accumulate, c.ds_xcd);
+        else hipLaunchKernelGGL(k_gauge_force<false>, nb, bs, 0, c.stream, g, f, k, U, F, accumulate, c.ds_xcd);
+    }
     FGI_LAUNCH_CHECK();
-    if (c1 != 0.0) rect_force(c, g, beta, c1, U, F, coef);
 }
 
 // Tangent of the gauge force along a field of su(3) elements V:
@@ -663,83 +852,6 @@ __global__ void __launch_bounds__(256) k_rect_density_b(const ChainDesc* __restr
 void rect_density_add(Ctx& c, const Geom& g, double bc1, const d2* U, double* h) {
     hipLaunchKernelGGL(k_rect_density, dim3(slab_blocks(g.Vh, 2, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, bc1, U, h,
                        c.ds_xcd);
-    FGI_LAUNCH_CHECK();
-}
-
-// The six shapes per nu pair up on their first step from x + mu (+mu, +nu,
-// -nu): A gathers F (R_a + R_b) with F the shared first factor and R_a, R_b
-// the four-link remainders, 21 products per nu in place of 24. Loops stay
-// rolled, one link load and one product per step, so only four 3x3 matrices
-// (A, R, the running product, the factor) are live.
-__constant__ int RECT_PAIRS[3][9] = {{1, 2, -1, -1, -2, -2, -1, -1, 2},
-                                     {2, -1, -1, -2, 1, 2, -1, -2, -2},
-                                     {-2, -1, -1, 2, 1, -2, -1, 2, 2}};
-
-__device__ __forceinline__ M3<double> rect_staples_paired(const Geom& g, const d2* __restrict__ U, const Coord& c,
-                                                          int mu) {
-    M3<double> A = m3_zero<double>(), dl;
-#pragma unroll 1
-    for (int nu = 0; nu < 4; nu++) {
-        if (nu == mu) continue;
-#pragma unroll 1
-        for (int k = 0; k < 3; k++) {
-            Coord y0 = c;
-            coord_step(g, y0, mu, 1);
-            const int st0 = RECT_PAIRS[k][0];
-            Coord y1 = y0;
-            coord_step(g, y1, (st0 == 1 || st0 == -1) ? mu : nu, st0 > 0);
-            M3<double> R;
-#pragma unroll 1
-            for (int h = 0; h < 2; h++) {
-                Coord y = y1;
-                const int* st = RECT_PAIRS[k] + 1 + 4 * h;
-                M3<double> P = path_factor<false>(g, U, nullptr, y, (st[0] == 1 || st[0] == -1) ? mu : nu, st[0] > 0, dl);
-#pragma unroll 1
-                for (int j = 1; j < 4; j++) {
-                    const int d = (st[j] == 1 || st[j] == -1) ? mu : nu;
-                    P = m3_mul(P, path_factor<false>(g, U, nullptr, y, d, st[j] > 0, dl));
-                }
-                if (h == 0) R = P;
-                else m3_acc(R, P);
-            }
-            m3_acc(A, m3_mul(path_factor<false>(g, U, nullptr, y0, (st0 == 1 || st0 == -1) ? mu : nu, st0 > 0, dl), R));
-        }
-    }
-    return A;
-}
-
-// F_mu(x) += f TA(U_mu(x) A^R_mu(x)), f = -beta c1 coef / 6
-__device__ __forceinline__ void rect_force_body(const Geom& g, double f, const d2* __restrict__ U,
-                                                double* __restrict__ F, int t) {
-    if (t >= 4 * g.V) return;
-    const int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
-    const Coord c = cb_coords(g, p, s);
-    const M3<double> A = rect_staples_paired(g, U, c, mu);
-    const M3<double> W = m3_mul(gauge_load(U, mu, p, s, g.Vh), A);
-    double x[8];
-    ta_components(W, x);
-    double* o = F + (size_t)(r * 8) * g.Vh + s;
-#pragma unroll
-    for (int a = 0; a < 8; a++) o[(size_t)a * g.Vh] += f * x[a];
-}
-
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_rect_force(Geom g, double f, const d2* __restrict__ U,
-                                                   double* __restrict__ F, int xcd) {
-    rect_force_body(g, f, U, F, slab_thread(g.Vh, 8, xcd));
-}
-
-// batched chains: f = -beta_c c1 coef / 6 per chain
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_rect_force_b(const ChainDesc* __restrict__ cd, int nc, double c1, double coef,
-                                                     const d2* __restrict__ U, double* __restrict__ F) {
-    const int c = find_chain(cd, nc, blockIdx.x, GRID_4V);
-    const ChainDesc& d = cd[c];
-    rect_force_body(d.g, -d.beta * c1 * coef / 6.0, U + 9 * d.link0, F + 8 * d.link0,
-                    (blockIdx.x - d.blk0[GRID_4V]) * blockDim.x + threadIdx.x);
-}
-
-void rect_force(Ctx& c, const Geom& g, double beta, double c1, const d2* U, double* F, double coef) {
-    hipLaunchKernelGGL(k_rect_force, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g,
-                       -beta * c1 * coef / 6.0, U, F, c.ds_xcd);
     FGI_LAUNCH_CHECK();
 }
 
@@ -984,14 +1096,20 @@ void final_sums_b(Ctx& c, const Batch& B, const double* partial, int kind, doubl
     FGI_LAUNCH_CHECK();
 }
 
-void gauge_force_b(Ctx& c, const Batch& B, const d2* U, double* F, double coef, int accumulate, double c1) {
-    hipLaunchKernelGGL(k_gauge_force_b, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, U, F,
-                       coef * (1.0 - 8.0 * c1), accumulate);
+template <bool IMP>
+static void launch_gauge_force_b(Ctx& c, const Batch& B, const d2* U, double* F, double coef, int accumulate, double c1) {
+    if (B.nblk[GRID_GS])
+        hipLaunchKernelGGL(k_gauge_force_split_b<IMP>, dim3(B.nblk[GRID_GS]), dim3(384), 0, c.stream, B.cd, B.nc, U, F,
+                           coef, c1, accumulate);
+    if (B.max_vol > GAUGE_SPLIT_MAX_V)
+        hipLaunchKernelGGL(k_gauge_force_b<IMP>, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, U, F, coef, c1,
+                           accumulate);
     FGI_LAUNCH_CHECK();
-    if (c1 != 0.0) {
-        hipLaunchKernelGGL(k_rect_force_b, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, c1, coef, U, F);
-        FGI_LAUNCH_CHECK();
-    }
+}
+
+void gauge_force_b(Ctx& c, const Batch& B, const d2* U, double* F, double coef, int accumulate, double c1) {
+    if (c1 != 0.0) launch_gauge_force_b<true>(c, B, U, F, coef, accumulate, c1);
+    else launch_gauge_force_b<false>(c, B, U, F, coef, accumulate, c1);
 }
 
 void link_update_b(Ctx& c, const Batch& B, double h, const double* X, const d2* src, d2* dst, void* sloppy, int prec,
