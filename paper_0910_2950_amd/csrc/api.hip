@@ -460,8 +460,7 @@ int fgi_destroy(fgi_ctx* ctx) {
         if (c.cap_stream) hipStreamDestroy(c.cap_stream);
         if (c.host_scal) hipHostFree(c.host_scal);
         if (c.host_state) hipHostFree(c.host_state);
-        if (c.host_bstates) hipHostFree(c.host_bstates);
-        if (c.host_bscal) hipHostFree(c.host_bscal);
+        if (c.host_bseen) hipHostFree(c.host_bseen);
         delete ctx;
     });
 }

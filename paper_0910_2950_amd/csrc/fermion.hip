@@ -768,7 +768,7 @@ template <int PL, int RECON> __device__ __forceinline__ size_t link_byte_off(con
 
 // One chain's arguments of a batched launch: its own geometry, kappa, solver
 // state (base.st[c]) and partials slice.
-template <int PIN, int PC, int POUT, int PX, int PL, int RECON>
+template <int MODE, int PIN, int PC, int POUT, int PX, int PL, int RECON>
 __device__ __forceinline__ DArgs chain_args(const DArgs& base, const ChainDesc& d, int c) {
     DArgs A = base;
     A.g = d.g;
@@ -778,7 +778,7 @@ __device__ __forceinline__ DArgs chain_args(const DArgs& base, const ChainDesc& 
     A.center = spin_off<PC>(base.center, d);
     A.aux = spin_off<PC>(base.aux, d);
     A.out = spin_off<POUT>(base.out, d);
-    A.x = spin_off<PX>(base.x, d);
+    A.x = spin_off<MODE == M_RESID ? POUT : PX>(base.x, d);
     A.r = spin_off<PX>(base.r, d);
     A.partial = base.partial ? base.partial + d.blk0[GRID_DS] : nullptr;
     A.st = base.st ? base.st + c : nullptr;
@@ -794,7 +794,7 @@ __global__ void __launch_bounds__(DBS) k_dslash_b(DArgs base, const ChainDesc* _
     const int gb = (int)blockIdx.x < nsb ? (base.xcd ? xcd_block(blockIdx.x, nsb) : (int)blockIdx.x) : blockIdx.x;
     const int2 m = map[gb];
     const ChainDesc& d = cd[m.x];
-    const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
+    const DArgs A = chain_args<MODE, PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
     dslash_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false, false>(A, m.y, d.nblk[GRID_DS], lds);
 }
 
@@ -805,7 +805,7 @@ __global__ void __launch_bounds__(256) k_dslash_split_b(DArgs base, const ChainD
     const int gb = (int)blockIdx.x < nsb ? (base.xcd ? xcd_block(blockIdx.x, nsb) : (int)blockIdx.x) : blockIdx.x;
     const int2 m = map[gb];
     const ChainDesc& d = cd[m.x];
-    const DArgs A = chain_args<PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
+    const DArgs A = chain_args<MODE, PIN, PC, POUT, PX, PL, RECON>(base, d, m.x);
     dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, m.y, d.nblk[GRID_DS], 1, L);
 }
 
@@ -996,12 +996,78 @@ __global__ void __launch_bounds__(DBS) k_cg_restart(CGState* st, CGRun C, const 
     C.seen[1] = rr;
 }
 
-// one block per chain
-__global__ void __launch_bounds__(DBS) k_advance_b(const ChainDesc* __restrict__ cd, CGState* st,
+// ---- the chains of a batch, one block each: as above, and each chain's own end
+__global__ void __launch_bounds__(DBS) k_cg_start_b(const ChainDesc* __restrict__ cd, CGState* st, CGChain* ch, CGRun C,
+                                                    const double* part, int maxiter) {
+    __shared__ double lds[DBS / 64];
+    const int i = blockIdx.x;
+    const double bb = C.bb[i], target = C.tol2 * bb;
+    const bool zero = bb == 0.0;
+    const double rr0 = part && !zero ? sum_partials(part + cd[i].blk0[GRID_DS], cd[i].nblk[GRID_DS], lds) : bb;
+    if (threadIdx.x) return;
+    const bool there = zero || (part && rr0 <= target);
+    CGState h{};
+    h.rr[0] = rr0;
+    h.rr_stop = inner_stop(C, rr0, target);
+    h.stop_at = there || !isfinite(rr0) ? 0 : INT_MAX;
+    st[i] = h;
+    CGChain e{};
+    e.bb = bb;
+    e.rr0 = e.rr = rr0;
+    e.status = there ? CH_CONVERGED : isfinite(rr0) ? CH_RUNNING : CH_BAD;
+    e.maxiter = maxiter;
+    ch[i] = e;
+}
+
+// act: chains whose inner run has ended, or been cut off, take the true residual next
+__global__ void __launch_bounds__(DBS) k_advance_b(const ChainDesc* __restrict__ cd, CGState* st, const CGChain* ch,
                                                    const double* partial, int n) {
     __shared__ double lds[DBS / 64];
-    const ChainDesc& d = cd[blockIdx.x];
-    advance_body(st + blockIdx.x, partial + d.blk0[GRID_DS], d.nblk[GRID_DS], n, lds);
+    const int i = blockIdx.x;
+    advance_body(st + i, partial + cd[i].blk0[GRID_DS], cd[i].nblk[GRID_DS], n, lds);
+    if (threadIdx.x) return;
+    const CGState& s = st[i];
+    st[i].act = ch[i].status == CH_RUNNING && (s.stop_at <= s.base || s.base >= ch[i].maxiter);
+}
+
+// seen: the pinned host copy of states and chains that the host reads once a round
+__global__ void __launch_bounds__(DBS) k_cg_restart_b(const ChainDesc* __restrict__ cd, CGState* st, CGChain* ch, CGRun C,
+                                                      const double* part, CGSeen* seen) {
+    __shared__ double lds[DBS / 64];
+    const int i = blockIdx.x;
+    CGState s = st[i];
+    CGChain e = ch[i];
+    const double rr = s.act ? sum_partials(part + cd[i].blk0[GRID_DS], cd[i].nblk[GRID_DS], lds) : 0.0;
+    if (threadIdx.x) return;
+    if (s.act) {
+        const double target = C.tol2 * e.bb;
+        const int kend = s.stop_at <= s.base ? s.stop_at : s.base;
+        e.rr = rr;
+        e.iters = kend;
+        s.act = 0;
+        if (!isfinite(rr) || rr <= target || kend >= e.maxiter) {
+            e.status = !isfinite(rr) ? CH_BAD : rr <= target ? CH_CONVERGED : CH_CUT;
+            s.stop_at = 0;   // no iteration runs from now on
+        } else {
+            e.updates++;
+            s.beta = rr / s.rr[(kend - 1) & 1];
+            s.rr[kend & 1] = rr;
+            s.rr_stop = inner_stop(C, rr, target);
+            s.stop_at = INT_MAX;
+            s.base = kend;
+            s.base0 = kend;
+        }
+        st[i] = s;
+        ch[i] = e;
+    }
+    seen[i].s = s;
+    seen[i].h = e;
+}
+
+// act: the chains with (zero) or without a zero right-hand side
+__global__ void k_cg_mask_b(int nc, CGState* st, const double* bb, int zero) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nc) st[i].act = (bb[i] == 0.0) == (zero != 0);
 }
 
 // conversion between storage precisions (through FP64 registers)
@@ -1243,9 +1309,9 @@ __global__ void k_sp_lincomb(int Vh, double a, const d2* x, double b, const d2* 
     const int s = (blockIdx.x - d.blk0[GRID_VH]) * blockDim.x + threadIdx.x
 
 template <int PA, int PB>
-__global__ void k_convert_b(const ChainDesc* __restrict__ cd, int nc, const CGState* st, SpinorPtr a, SpinorPtr b) {
+__global__ void k_convert_b(const ChainDesc* __restrict__ cd, int nc, SpinorPtr a, SpinorPtr b) {
     FGI_CHAIN_SITE(cd, nc);
-    if (s >= d.g.Vh || (st && !st[c_].act)) return;
+    if (s >= d.g.Vh) return;
     cx<double> v[4][3];
     SpinorIO<PA, double>::load(spin_off<PA>(a, d), s, d.g.Vh, v);
     SpinorIO<PB, double>::store(spin_off<PB>(b, d), s, d.g.Vh, v);
@@ -1266,11 +1332,11 @@ __global__ void k_add_to64_b(const ChainDesc* __restrict__ cd, int nc, const CGS
     SpinorIO<P64, double>::store(yy, s, d.g.Vh, b);
 }
 
-// zero a chain's FP32 / FP64 spinor (only chains with act set when st is given)
+// zero the spinors of the chains with act set
 template <int P>
 __global__ void k_zero_spinor_b(const ChainDesc* __restrict__ cd, int nc, const CGState* st, SpinorPtr v) {
     FGI_CHAIN_SITE(cd, nc);
-    if (s >= d.g.Vh || (st && !st[c_].act)) return;
+    if (s >= d.g.Vh || !st[c_].act) return;
     cx<double> z[4][3];
 #pragma unroll
     for (int i = 0; i < 4; i++)
@@ -2201,10 +2267,10 @@ void pf_density_b(Ctx& c, const Batch& B, const d2* phi, const d2* X, const d2* 
     final_sums_b(c, B, partial, GRID_VH, out);
 }
 
-// r = phi - Mhat^+ Mhat X and |r|^2 -> res[c] for the chains with act set
-// (res[c] of the other chains is meaningless)
-static void true_residual_b(Ctx& c, const Batch& B, const FermionOp& op64, const d2* phi, const d2* X, d2* r64,
-                            CGState* st, double* res) {
+// true_residual for the chains with act set
+template <int PR>
+static void true_residual_b(Ctx& c, const Batch& B, const FermionOp& op64, const d2* phi, const d2* X, SpinorPtr r,
+                            SpinorPtr x0, CGState* st) {
     size_t n = sizeof(d2) * 12 * (size_t)B.sites;
     d2* t = (d2*)c.tmp_o.get(n);
     d2* q = (d2*)c.cg_q.get(n);
@@ -2219,13 +2285,13 @@ static void true_residual_b(Ctx& c, const Batch& B, const FermionOp& op64, const
     b.in = sp(t);
     b.center = sp(q);
     b.aux = sp(phi);
-    b.out = sp(r64);
+    b.out = r;
+    b.x = x0;
     b.g5out = 1;
     b.partial = partial_buf(c, B);
     b.st = st;
     b.gate = 1;
-    launch_dslash_b<M_RESID, P64, P64, P64, P64, 0>(c, B, op64, b);
-    final_sums_b(c, B, b.partial, GRID_DS, res);
+    launch_dslash_b<M_RESID, P64, P64, PR, P64, 0>(c, B, op64, b);
 }
 
 template <int PP, int PX>
@@ -2281,77 +2347,55 @@ static void cg_iteration_b(Ctx& c, const Batch& B, const FermionOp& ops, const C
 }
 
 template <int PP, int PX>
-static void cg_batch_b(Ctx& c, const Batch& B, const FermionOp& ops, const CGVecs& v, int nit, CGState* st) {
+static void cg_batch_b(Ctx& c, const Batch& B, const FermionOp& ops, const CGVecs& v, int nit, CGState* st,
+                       const CGChain* ch) {
     for (int j = 0; j < nit; j++) cg_iteration_b<PP, PX>(c, B, ops, v, j, st);
-    hipLaunchKernelGGL(k_advance_b, dim3(B.nc), dim3(DBS), 0, c.stream, B.cd, st, (const double*)partial_buf(c, B), nit);
+    hipLaunchKernelGGL(k_advance_b, dim3(B.nc), dim3(DBS), 0, c.stream, B.cd, st, ch,
+                       (const double*)partial_buf(c, B), nit);
     FGI_LAUNCH_CHECK();
-}
-
-// The pinned staging buffer is rewritten only after the stream has drained, so
-// an earlier upload still queued behind kernels cannot pick up a later state
-// (two uploads in a row at a reliable update differ in the act flags).
-static void upload_states(Ctx& c, CGState* dev, const std::vector<CGState>& h) {
-    FGI_HIP(hipStreamSynchronize(c.stream));
-    std::copy(h.begin(), h.end(), c.host_bstates);
-    FGI_HIP(hipMemcpyAsync(dev, c.host_bstates, sizeof(CGState) * h.size(), hipMemcpyHostToDevice, c.stream));
-}
-
-static void download_states(Ctx& c, const CGState* dev, std::vector<CGState>& h) {
-    FGI_HIP(hipMemcpyAsync(c.host_bstates, dev, sizeof(CGState) * h.size(), hipMemcpyDeviceToHost, c.stream));
-    FGI_HIP(hipStreamSynchronize(c.stream));
-    std::copy(c.host_bstates, c.host_bstates + h.size(), h.begin());
-}
-
-static void download_doubles(Ctx& c, const double* dev, int n) {
-    FGI_HIP(hipMemcpyAsync(c.host_bscal, dev, sizeof(double) * n, hipMemcpyDeviceToHost, c.stream));
-    FGI_HIP(hipStreamSynchronize(c.stream));
 }
 
 // All chains of the batch solved together: every kernel covers every chain,
 // each chain with its own CG state; chains stop on their own and take their
 // reliable updates in masked steps.
+//
+// A round is half as many iterations again as the slowest chain's inner run still
+// needs by its decay so far, one masked true residual for the chains that the
+// device finds at their end, and one wait.  A chain past its end costs its blocks'
+// exit; one that misses a round waits for the next residual, and the FP64
+// residual costs all chains as much as three iterations.  Rounds of eight with the
+// masks set by the host -> rounds by need -> with half as many again (ms, a
+// trajectory): 96 chains of 4^4 to 8^3x16 in FP16 storage 148 -> 137 -> 124, 12 of
+// them 96 -> 67 -> 60, 24 in FP32 109 -> 69 -> 61, in FP64 118 -> 82 -> 82.  The
+// iterates do not depend on the counts.
 template <int PP, int PX>
 static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops,
                                       const d2* phi, d2* X, double tol, int maxiter, bool guess) {
     const int nc = B.nc;
-    const double drop = ru_drop(c, PP), ru2 = drop * drop;
+    const double drop = ru_drop(c, PP);
     const size_t n64 = sizeof(d2) * 12 * (size_t)B.sites;
     std::vector<CGResult> res(nc, CGResult{0, 0, 0.0, 0});
     double* part = partial_buf(c, B);
-    double* dres = (double*)c.bscal.get(sizeof(double) * nc);
-    CGState* st = (CGState*)c.bstate.get(sizeof(CGState) * nc);
+    double* bb = (double*)c.bscal.get(sizeof(double) * nc);
+    CGState* st = (CGState*)c.bstate.get((sizeof(CGState) + sizeof(CGChain)) * nc);
+    CGChain* ch = (CGChain*)(st + nc);
+    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, bb, nullptr};
     hipLaunchKernelGGL(k_norm2_partials_b, dim3(B.nblk[GRID_VH]), dim3(DBS), 0, c.stream, B.cd, nc, phi, part);
     FGI_LAUNCH_CHECK();
-    final_sums_b(c, B, part, GRID_VH, dres);
-    download_doubles(c, dres, nc);
-    std::vector<double> bb(c.host_bscal, c.host_bscal + nc), target(nc), rr0(bb);
+    final_sums_b(c, B, part, GRID_VH, bb);
     if (!guess) zero_doubles(c, (double*)X, 24 * (size_t)B.sites);
     d2* r64 = (d2*)c.cg_r.get(n64);
-    std::vector<CGState> hs(nc);
-    std::vector<int> done(nc, 0);
-    for (int i = 0; i < nc; i++) {
-        target[i] = tol * tol * bb[i];
-        hs[i] = CGState{};
-        hs[i].act = bb[i] != 0.0;
-    }
     if (guess) {  // every chain with a nonzero right-hand side starts from its true residual
-        upload_states(c, st, hs);
-        true_residual_b(c, B, op64, phi, X, r64, st, dres);
-        download_doubles(c, dres, nc);
-        bool any_zero = false;
-        for (int i = 0; i < nc; i++) {
-            hs[i].act = bb[i] == 0.0;
-            any_zero = any_zero || bb[i] == 0.0;
-            if (bb[i] == 0.0) continue;
-            rr0[i] = c.host_bscal[i];
-            if (!std::isfinite(rr0[i])) throw Error(-4, "batched CG: non-finite residual of the starting point");
-        }
-        if (any_zero) {  // phi = 0: the solution is 0, whatever the start
-            upload_states(c, st, hs);
-            FGI_B_LAUNCH((k_zero_spinor_b<P64>), B.nblk[GRID_VH]), B.cd, nc, st, sp(X));
-            FGI_LAUNCH_CHECK();
-        }
+        const dim3 nb(nblk(nc, DBS)), bs(DBS);
+        hipLaunchKernelGGL(k_cg_mask_b, nb, bs, 0, c.stream, nc, st, (const double*)bb, 1);
+        FGI_B_LAUNCH((k_zero_spinor_b<P64>), B.nblk[GRID_VH]), B.cd, nc, st, sp(X));   // phi = 0: the solution is 0
+        hipLaunchKernelGGL(k_cg_mask_b, nb, bs, 0, c.stream, nc, st, (const double*)bb, 0);
+        FGI_LAUNCH_CHECK();
+        true_residual_b<P64>(c, B, op64, phi, X, sp(r64), SpinorPtr{}, st);
     }
+    hipLaunchKernelGGL(k_cg_start_b, dim3(nc), dim3(DBS), 0, c.stream, B.cd, st, ch, run,
+                       guess ? (const double*)part : nullptr, maxiter);
+    FGI_LAUNCH_CHECK();
     CGVecs v{};
     float* norms = (float*)c.s_norms.get(sizeof(float) * 3 * (size_t)B.sites);
     const d2* r_start = guess ? r64 : phi;
@@ -2372,24 +2416,10 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
         v.q = sp(c.s_q.get(np), norms + B.sites);
         v.t = sp(c.s_t.get(np), norms + 2 * (size_t)B.sites);
         zero_doubles(c, (double*)v.x.v, 12 * (size_t)B.sites);
-        FGI_B_LAUNCH((k_convert_b<P64, PX>), B.nblk[GRID_VH]), B.cd, nc, nullptr, sp(r_start), v.r);
-        FGI_B_LAUNCH((k_convert_b<P64, PP>), B.nblk[GRID_VH]), B.cd, nc, nullptr, sp(r_start), v.p);
+        FGI_B_LAUNCH((k_convert_b<P64, PX>), B.nblk[GRID_VH]), B.cd, nc, sp(r_start), v.r);
+        FGI_B_LAUNCH((k_convert_b<P64, PP>), B.nblk[GRID_VH]), B.cd, nc, sp(r_start), v.p);
         FGI_LAUNCH_CHECK();
     }
-    for (int i = 0; i < nc; i++) {
-        CGState& h = hs[i];
-        h = CGState{};
-        h.rr[0] = rr0[i];
-        h.rr_stop = (PX == P64) ? target[i] : std::max(ru2 * rr0[i], target[i]);
-        const bool zero = bb[i] == 0.0, there = guess && !zero && rr0[i] <= target[i];
-        h.stop_at = (zero || there) ? 0 : INT_MAX;
-        if (zero || there) {
-            done[i] = 1;
-            res[i].converged = 1;
-            res[i].rel_resid = zero ? 0.0 : std::sqrt(rr0[i] / bb[i]);
-        }
-    }
-    upload_states(c, st, hs);
     const int Bi = c.cg_batch;
     GraphEntry* ge = nullptr;
     if (c.use_graphs) {
@@ -2399,66 +2429,45 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
                  ops.links, ops.prec, ops.recon, nc, B.ds_blk[0], B.ds_blk[1], (void*)B.ds_map[0], (void*)B.ds_map[1],
                  B.sites, (void*)B.cd, v.x.v, v.r.v, v.p.v,
                  v.q.v, v.t.v, (void*)v.p.norm, (void*)st, (void*)part, Bi, c.ds_bs, c.ds_xcd);
-        ge = &cached_graph(c, key, [&] { cg_batch_b<PP, PX>(c, B, ops, v, Bi, st); });
+        ge = &cached_graph(c, key, [&] { cg_batch_b<PP, PX>(c, B, ops, v, Bi, st, ch); });
     }
-    int left = 0;
-    for (int i = 0; i < nc; i++) left += !done[i];
-    while (left > 0) {
-        if (ge) FGI_HIP(hipGraphLaunch(ge->exec, c.stream));
-        else cg_batch_b<PP, PX>(c, B, ops, v, Bi, st);
-        download_states(c, st, hs);
-        bool any = false;
-        std::vector<int> kend(nc, 0);
-        for (int i = 0; i < nc; i++) {
-            hs[i].act = 0;
-            if (done[i]) continue;
-            bool inner = hs[i].stop_at <= hs[i].base;
-            kend[i] = inner ? hs[i].stop_at : hs[i].base;
-            if (inner || kend[i] >= maxiter) {
-                hs[i].act = 1;
-                any = true;
-            }
+    for (int n = std::min(Bi, 8); n > 0;) {
+        for (int left = n; left > 0;) {
+            const int m = std::min(left, Bi);
+            if (ge && m == Bi) FGI_HIP(hipGraphLaunch(ge->exec, c.stream));
+            else cg_batch_b<PP, PX>(c, B, ops, v, m, st, ch);
+            left -= m;
         }
-        if (!any) continue;
-        upload_states(c, st, hs);
         if (PX != P64) {
             FGI_B_LAUNCH((k_add_to64_b<PX>), B.nblk[GRID_VH]), B.cd, nc, st, v.x, sp(X));
             FGI_LAUNCH_CHECK();
         }
-        true_residual_b(c, B, op64, phi, X, r64, st, dres);
-        download_doubles(c, dres, nc);
-        bool restart = false;
+        true_residual_b<PX>(c, B, op64, phi, X, v.r, PX == P64 ? SpinorPtr{} : v.x, st);
+        hipLaunchKernelGGL(k_cg_restart_b, dim3(nc), dim3(DBS), 0, c.stream, B.cd, st, ch, run, (const double*)part,
+                           c.host_bseen);
+        FGI_LAUNCH_CHECK();
+        FGI_HIP(hipStreamSynchronize(c.stream));
+        n = 0;
+        int room = INT_MAX;
         for (int i = 0; i < nc; i++) {
-            if (!hs[i].act) continue;
-            double rr = c.host_bscal[i];
-            if (!std::isfinite(rr)) throw Error(-4, "batched CG: non-finite residual");
-            res[i].iters = kend[i];
-            res[i].rel_resid = bb[i] > 0 ? std::sqrt(rr / bb[i]) : 0.0;
-            if (rr <= target[i] || kend[i] >= maxiter) {
-                res[i].converged = rr <= target[i];
-                done[i] = 1;
-                left--;
-                hs[i].act = 0;
-                hs[i].stop_at = hs[i].base;  // no-op from now on
-                continue;
-            }
-            res[i].reliable_updates++;
-            restart = true;
-            hs[i].beta = rr / hs[i].rr[(kend[i] - 1) & 1];
-            hs[i].rr[kend[i] & 1] = rr;
-            hs[i].stop_at = INT_MAX;
-            hs[i].base = kend[i];
-            hs[i].base0 = kend[i];
-            hs[i].rr_stop = (PX == P64) ? target[i] : std::max(ru2 * rr, target[i]);
+            const CGState& s = c.host_bseen[i].s;
+            const CGChain& e = c.host_bseen[i].h;
+            if (e.status == CH_BAD)
+                throw Error(-4, guess && !e.iters ? "batched CG: non-finite residual of the starting point"
+                                                  : "batched CG: non-finite residual");
+            if (e.status != CH_RUNNING) continue;
+            const double now = s.rr[s.base & 1];
+            if (!std::isfinite(now)) throw Error(-4, "batched CG: non-finite residual");
+            const double need = std::log(s.rr_stop / now) / (std::log(now / e.rr0) / s.base);
+            n = std::max(n, !(need > 0.0) || need > 1e6 ? Bi : (int)std::min(std::ceil(1.5 * need), 64.0));
+            // an unfinished run is cut off whole batches after its start
+            room = std::min(room, s.base0 + Bi * ((maxiter - s.base0 + Bi - 1) / Bi) - s.base);
         }
-        upload_states(c, st, hs);  // act still set for the restarting chains
-        if (restart && PX != P64) {
-            FGI_B_LAUNCH((k_convert_b<P64, PX>), B.nblk[GRID_VH]), B.cd, nc, st, sp(r64), v.r);
-            FGI_B_LAUNCH((k_zero_spinor_b<PX>), B.nblk[GRID_VH]), B.cd, nc, st, v.x);
-            FGI_LAUNCH_CHECK();
-        }
-        for (int i = 0; i < nc; i++) hs[i].act = 0;
-        upload_states(c, st, hs);
+        n = std::min(n, room);
+    }
+    for (int i = 0; i < nc; i++) {
+        const CGChain& e = c.host_bseen[i].h;
+        res[i] = CGResult{e.iters, e.status == CH_CONVERGED, e.bb > 0 ? std::sqrt(e.rr / e.bb) : 0.0, e.updates};
     }
     return res;
 }
@@ -2466,10 +2475,10 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
 std::vector<CGResult> cg_solve_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops, int sprec,
                                  const d2* phi, d2* X, double tol, int maxiter, bool guess) {
     if ((size_t)B.nc > c.host_b_cap) {
-        if (c.host_bstates) hipHostFree(c.host_bstates);
-        if (c.host_bscal) hipHostFree(c.host_bscal);
-        FGI_HIP(hipHostMalloc((void**)&c.host_bstates, sizeof(CGState) * B.nc, hipHostMallocDefault));
-        FGI_HIP(hipHostMalloc((void**)&c.host_bscal, sizeof(double) * B.nc, hipHostMallocDefault));
+        if (c.host_bseen) hipHostFree(c.host_bseen);
+        c.host_bseen = nullptr;
+        c.host_b_cap = 0;
+        FGI_HIP(hipHostMalloc((void**)&c.host_bseen, sizeof(CGSeen) * B.nc, hipHostMallocDefault));
         c.host_b_cap = B.nc;
     }
     if (sprec == P64) return cg_run_b<P64, P64>(c, B, op64, op64, phi, X, tol, maxiter, guess);

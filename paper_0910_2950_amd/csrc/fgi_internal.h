@@ -57,6 +57,17 @@ struct alignas(64) CGState {
 };
 static_assert(sizeof(CGState) == 64, "CGState is read as 16-byte vectors");
 
+// A chain's solve in a batch, beside its CGState, and the host's copy of both.
+enum ChainStatus { CH_RUNNING = 0, CH_CONVERGED = 1, CH_CUT = 2, CH_BAD = 3 };   // CUT: at maxiter; BAD: not finite
+struct CGChain {
+    double bb, rr0, rr;              // |phi|^2; |r|^2 at the start and of the last true residual
+    int status, iters, updates, maxiter;
+};
+struct CGSeen {
+    CGState s;
+    CGChain h;
+};
+
 // All fields of a state in four 16-byte loads issued together (kernels read
 // the state once, up front, instead of one memory round trip per use).
 struct StateView {
@@ -109,8 +120,7 @@ struct Ctx {
     DevBuf cdesc, bstate, bscal, bh0, bh1, bres;  // batched chains
     DevBuf br_jp, br_jf, br_jj;   // force gradients of the dt^4 brackets
     DevBuf halo_a, halo_b;        // face buffers of the t-decomposed hop (timing)
-    CGState* host_bstates = nullptr;          // pinned [host_b_cap]
-    double* host_bscal = nullptr;             // pinned [host_b_cap]
+    CGSeen* host_bseen = nullptr;             // pinned [host_b_cap]
     size_t host_b_cap = 0;
     double* host_scal = nullptr;   // pinned, 64 doubles
     CGState* host_state = nullptr; // pinned
