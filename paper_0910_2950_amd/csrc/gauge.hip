@@ -9,51 +9,64 @@ namespace fgi {
 static inline int nblocks(long n, int bs) { return (int)((n + bs - 1) / bs); }
 static const int BS = 256;
 
-// lexicographic index of checkerboard site (p, s)
-__device__ __forceinline__ int lex_index(const Geom& g, int p, int s) {
-    Coord c = cb_coords(g, p, s);
-    return c.c[0] + g.L[0] * (c.c[1] + g.L[1] * (c.c[2] + g.L[2] * c.c[3]));
-}
-
 // ---------------------------------------------------------------- layout ---
-__device__ __forceinline__ void pack_gauge_body(const Geom& g, const d2* __restrict__ user, d2* __restrict__ U,
-                                                int to_internal, int t) {
-    if (t >= 4 * g.V) return;
-    int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
-    int i = lex_index(g, p, s);
-    d2* in = U + (size_t)((mu * 2 + p) * 9) * g.Vh + s;
-    const size_t ub = ((size_t)mu * g.V + i) * 9;
+// User links and momenta are [mu][site] records of NE entries (links 9 complex,
+// momenta 8 doubles).  A block moves 256 records: it meets user memory in one
+// contiguous stretch and each parity's planes in runs of 128, with the transpose
+// in LDS.  (Sites 2q and 2q + 1 are checkerboard index q of the two parities.)
+// Bound by memory; a thread per record of one parity fetched every line once per
+// parity.  32^3x64: links in 690 -> 492 us, momenta out 401 -> 211, the rate of
+// a copy.
+template <typename T, int NE, int PAD>
+__device__ __forceinline__ void pack_records(const Geom& g, T* __restrict__ user, T* __restrict__ in, int to_internal,
+                                             int blk, T* lds) {
+    constexpr int ROW = NE + PAD;
+    const int t = threadIdx.x, r0 = blk * 256, n = min(256, 4 * g.V - r0);   // first record, records
+    // this thread's record in the planes
+    const int p = t >> 7, q = (r0 >> 1) + (t & 127), mu = q / g.Vh, s = q - mu * g.Vh;
+    const bool live = 2 * (t & 127) < n;
+    const int rec = 2 * (t & 127) + (live ? cb_coords(g, p, s).c[0] & 1 : 0);
+    T* pl = in + (size_t)((mu * 2 + p) * NE) * g.Vh + s;
+    T* us = user + (size_t)r0 * NE;
+    T v[NE];
     if (to_internal) {
 #pragma unroll
-        for (int k = 0; k < 9; k++) in[(size_t)k * g.Vh] = user[ub + k];
-    } else {
+        for (int j = 0; j < NE; j++)
+            if (t + 256 * j < n * NE) v[j] = us[t + 256 * j];
 #pragma unroll
-        for (int k = 0; k < 9; k++) ((d2*)user)[ub + k] = in[(size_t)k * g.Vh];
+        for (int j = 0; j < NE; j++) {
+            const int e = t + 256 * j;
+            if (e < n * NE) lds[(e / NE) * ROW + e % NE] = v[j];
+        }
+        __syncthreads();
+        if (!live) return;
+#pragma unroll
+        for (int k = 0; k < NE; k++) pl[(size_t)k * g.Vh] = lds[rec * ROW + k];
+    } else {
+        if (live) {
+#pragma unroll
+            for (int k = 0; k < NE; k++) v[k] = pl[(size_t)k * g.Vh];
+#pragma unroll
+            for (int k = 0; k < NE; k++) lds[rec * ROW + k] = v[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NE; j++) {
+            const int e = t + 256 * j;
+            if (e < n * NE) us[e] = lds[(e / NE) * ROW + e % NE];
+        }
     }
 }
+constexpr int PACK_LINK_LDS = 256 * 9, PACK_MOM_LDS = 256 * 9;   // elements; a momentum row is padded to 9
 
-__global__ void k_pack_gauge(Geom g, const d2* __restrict__ user, d2* __restrict__ U, int to_internal) {
-    pack_gauge_body(g, user, U, to_internal, blockIdx.x * blockDim.x + threadIdx.x);
+__global__ void __launch_bounds__(256) k_pack_gauge(Geom g, const d2* user, d2* U, int to_internal) {
+    __shared__ d2 lds[PACK_LINK_LDS];
+    pack_records<d2, 9, 0>(g, (d2*)user, U, to_internal, blockIdx.x, lds);
 }
 
-__device__ __forceinline__ void pack_mom_body(const Geom& g, const double* __restrict__ user, double* __restrict__ P,
-                                              int to_internal, int t) {
-    if (t >= 4 * g.V) return;
-    int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
-    int i = lex_index(g, p, s);
-    double* in = P + (size_t)((mu * 2 + p) * 8) * g.Vh + s;
-    const size_t ub = ((size_t)mu * g.V + i) * 8;
-    if (to_internal) {
-#pragma unroll
-        for (int a = 0; a < 8; a++) in[(size_t)a * g.Vh] = user[ub + a];
-    } else {
-#pragma unroll
-        for (int a = 0; a < 8; a++) ((double*)user)[ub + a] = in[(size_t)a * g.Vh];
-    }
-}
-
-__global__ void k_pack_mom(Geom g, const double* __restrict__ user, double* __restrict__ P, int to_internal) {
-    pack_mom_body(g, user, P, to_internal, blockIdx.x * blockDim.x + threadIdx.x);
+__global__ void __launch_bounds__(256) k_pack_mom(Geom g, const double* user, double* P, int to_internal) {
+    __shared__ double lds[PACK_MOM_LDS];
+    pack_records<double, 8, 1>(g, (double*)user, P, to_internal, blockIdx.x, lds);
 }
 
 // user even spinor: entry k (= checkerboard index of the k-th even site) holds [4][3] complex
@@ -74,14 +87,18 @@ __global__ void k_pack_even(Geom g, const d2* __restrict__ user, d2* __restrict_
 }
 
 // batched: field 0 links, 1 momenta, 2 even spinor (the chain's user pointer)
-__global__ void k_pack_b(const ChainDesc* __restrict__ cd, int nc, void* internal, int field, int to_internal) {
+__global__ void __launch_bounds__(256) k_pack_b(const ChainDesc* __restrict__ cd, int nc, void* internal, int field,
+                                                int to_internal) {
+    __shared__ d2 lds[PACK_LINK_LDS];
     const int kind = field == 2 ? GRID_VH : GRID_4V;
     const int c = find_chain(cd, nc, blockIdx.x, kind);
     const ChainDesc& d = cd[c];
-    const int t = (blockIdx.x - d.blk0[kind]) * blockDim.x + threadIdx.x;
-    if (field == 0) pack_gauge_body(d.g, (const d2*)d.user_U, (d2*)internal + 9 * d.link0, to_internal, t);
-    else if (field == 1) pack_mom_body(d.g, (const double*)d.user_P, (double*)internal + 8 * d.link0, to_internal, t);
-    else pack_even_body(d.g, (const d2*)d.user_eta, (d2*)internal + 12 * d.site0, to_internal, t);
+    const int b = blockIdx.x - d.blk0[kind];
+    if (field == 0) pack_records<d2, 9, 0>(d.g, (d2*)d.user_U, (d2*)internal + 9 * d.link0, to_internal, b, lds);
+    else if (field == 1)
+        pack_records<double, 8, 1>(d.g, (double*)d.user_P, (double*)internal + 8 * d.link0, to_internal, b, (double*)lds);
+    else
+        pack_even_body(d.g, (const d2*)d.user_eta, (d2*)internal + 12 * d.site0, to_internal, b * 256 + (int)threadIdx.x);
 }
 
 void pack_gauge(Ctx& c, const Geom& g, const void* user, d2* U) {
