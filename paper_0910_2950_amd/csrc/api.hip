@@ -607,8 +607,7 @@ int fgi_stout_force(fgi_ctx* ctx, const fgi_geom* gg, double rho, int n, const v
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
         double* fs = (double*)c.force2.get(mom_bytes(g));
         double* f = (double*)c.force.get(mom_bytes(g));
-        pack_gauge(c, g, U, u);
-        pack_mom(c, g, (const double*)Fs, fs);
+        pack_inputs(c, g, U, u, (const double*)Fs, fs, nullptr, nullptr);
         if (n == 0) {
             unpack_mom(c, g, fs, (double*)F);
             return;
@@ -633,8 +632,7 @@ int fgi_force_gradient(fgi_ctx* ctx, const fgi_geom* gg, double beta, const void
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
         double* v = (double*)c.force2.get(mom_bytes(g));
         double* j = (double*)c.force.get(mom_bytes(g));
-        pack_gauge(c, g, U, u);
-        pack_mom(c, g, (const double*)Vd, v);
+        pack_inputs(c, g, U, u, (const double*)Vd, v, nullptr, nullptr);
         gauge_force_tangent(c, g, beta, u, v, j, 1.0, 0);
         unpack_mom(c, g, j, (double*)J);
     });
@@ -659,8 +657,7 @@ int fgi_improved_gauge_hvp(fgi_ctx* ctx, const fgi_geom* gg, double beta, double
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
         double* v = (double*)c.force2.get(mom_bytes(g));
         double* j = (double*)c.force.get(mom_bytes(g));
-        pack_gauge(c, g, U, u);
-        pack_mom(c, g, (const double*)Vd, v);
+        pack_inputs(c, g, U, u, (const double*)Vd, v, nullptr, nullptr);
         gauge_force_tangent(c, g, beta, u, v, j, 1.0, 0, 1, c1);
         unpack_mom(c, g, j, (double*)HV);
     });
@@ -676,8 +673,7 @@ int fgi_link_update(fgi_ctx* ctx, const fgi_geom* gg, double h, const void* P, v
         StreamScope ss(c, stream);
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
         double* pm = (double*)c.mom.get(mom_bytes(g));
-        pack_gauge(c, g, U, u);
-        pack_mom(c, g, (const double*)P, pm);
+        pack_inputs(c, g, U, u, (const double*)P, pm, nullptr, nullptr);
         link_update(c, g, h, pm, u, u, nullptr, P64, 18);
         unpack_gauge(c, g, u, U);
     });
@@ -726,10 +722,9 @@ int fgi_dslash(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const vo
         a.prec = prec;
         Fields f(c, g, a);
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
-        pack_gauge(c, g, U, u);
         d2* vin = (d2*)c.tmp_e.get(spinor_bytes(g));
         d2* vout = (d2*)c.X.get(spinor_bytes(g));
-        pack_even_spinor(c, g, in, vin);  // same layout for either parity
+        pack_inputs(c, g, U, u, nullptr, nullptr, in, vin);  // same layout for either parity
         FermionOp op = f.op64(u, a.kappa);
         if (f.sp == P64) {
             dslash(c, op, out_parity, P64, SpinorPtr{vin, nullptr}, P64, SpinorPtr{vout, nullptr});
@@ -923,11 +918,10 @@ int fgi_mhat(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, const void
         need(out, "out", 16);
         StreamScope ss(c, stream);
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
-        pack_gauge(c, g, U, u);
         d2* vin = (d2*)c.tmp_e.get(spinor_bytes(g));
         d2* vout = (d2*)c.X.get(spinor_bytes(g));
         d2* t = (d2*)c.Xo.get(spinor_bytes(g));
-        pack_even_spinor(c, g, in, vin);
+        pack_inputs(c, g, U, u, nullptr, nullptr, in, vin);
         FermionOp op{&g, act->kappa, u, P64, 18};
         if (act->csw != 0.0 && act->kappa != 0.0) {
             d2* blk = (d2*)c.cl_blk.get(sizeof(d2) * 72 * (size_t)g.V);
@@ -1133,9 +1127,8 @@ int fgi_fermion_force(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action* act, c
         need(F, "F", 8);
         StreamScope ss(c, stream);
         d2* u = (d2*)c.gauge.get(gauge_bytes(g));
-        pack_gauge(c, g, U, u);
         d2* x = (d2*)c.X.get(spinor_bytes(g));
-        pack_even_spinor(c, g, X, x);
+        pack_inputs(c, g, U, u, nullptr, nullptr, X, x);
         double* fm = (double*)c.force.get(mom_bytes(g));
         zero_doubles(c, fm, mom_bytes(g) / sizeof(double));
         const FermionOp op{&g, act->kappa, u, P64, 18};
@@ -1635,8 +1628,7 @@ extern "C" int fgi_trajectory(fgi_ctx* ctx, const fgi_geom* gg, const fgi_action
         f.st = st;
         f.U = (d2*)c.gauge.get(gauge_bytes(g));
         trajectory_buffers(c, g, f);
-        pack_gauge(c, g, U, f.U);
-        pack_mom(c, g, (const double*)P, f.P);
+        pack_inputs(c, g, U, f.U, (const double*)P, f.P, nullptr, nullptr);
         d2 *eta = nullptr, *eta_2 = nullptr;
         if (ferm && pf_is_phi) {
             pack_even_spinor(c, g, eta1, f.phi[0]);

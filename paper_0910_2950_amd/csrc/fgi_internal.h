@@ -233,6 +233,7 @@ inline int slab_blocks(long Vh, int nt, int bs, int xcd) {
 }
 
 // ---------------- gauge.hip ----------------
+void pack_inputs(Ctx& c, const Geom& g, const void* U, d2* u, const double* P, double* pm, const void* X, d2* x);
 void pack_gauge(Ctx&, const Geom&, const void* user, d2* internal);
 void unpack_gauge(Ctx&, const Geom&, const d2* internal, void* user);
 void pack_mom(Ctx&, const Geom&, const double* user, double* internal);
