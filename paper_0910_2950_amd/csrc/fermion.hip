@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(256) k_dslash_split_b(DArgs base, const ChainD
 // partials, summed in every block in the same order (so all blocks agree
 // bitwise), and beta = rr / rr_prev; block 0 records rr and beta, or the
 // stop once rr <= rr_stop, for the kernels after it.  The first iteration of
-// a run (start or reliable update) takes rr and beta from the host.
+// a run (start or reliable update) takes the rr and beta it was set up with.
 template <int PP, int PX>
 __device__ __forceinline__ void cg_p_body(int Vh, SpinorPtr p, SpinorPtr r, CGState* st, const double* partial,
                                           int j, int b, int nb, double* lds) {
@@ -943,7 +943,7 @@ __device__ __forceinline__ void advance_body(CGState* st, const double* partial,
     if (threadIdx.x == 0) st->base = it;
 }
 
-// seen: the pinned host copy of the state that the host reads when it polls
+// seen: the pinned host copy of the state that the host reads at its waits
 __global__ void __launch_bounds__(DBS) k_advance(CGState* st, const double* partial, int nb, int n, CGState* seen) {
     __shared__ double lds[DBS / 64];
     advance_body(st, partial, nb, n, lds);
@@ -1028,6 +1028,22 @@ __global__ void __launch_bounds__(DBS) k_advance_b(const ChainDesc* __restrict__
     if (threadIdx.x) return;
     const CGState& s = st[i];
     st[i].act = ch[i].status == CH_RUNNING && (s.stop_at <= s.base || s.base >= ch[i].maxiter);
+}
+
+// Unless all running chains have ended their inner runs (or one was cut off), hold
+// the true residual back: the chains that wait keep in step with the few that need
+// some iterations more.
+__global__ void __launch_bounds__(DBS) k_cg_hold_b(int nc, CGState* st, const CGChain* ch) {
+    int open = 0, cut = 0;
+    for (int i = threadIdx.x; i < nc; i += DBS) {
+        const bool running = ch[i].status == CH_RUNNING;
+        open |= running && !st[i].act;
+        cut |= st[i].act && st[i].stop_at > st[i].base;
+    }
+    open = __syncthreads_or(open);
+    cut = __syncthreads_or(cut);
+    if (!open || cut) return;
+    for (int i = threadIdx.x; i < nc; i += DBS) st[i].act = 0;
 }
 
 // seen: the pinned host copy of states and chains that the host reads once a round
@@ -2361,13 +2377,14 @@ static void cg_batch_b(Ctx& c, const Batch& B, const FermionOp& ops, const CGVec
 //
 // A round is half as many iterations again as the slowest chain's inner run still
 // needs by its decay so far, one masked true residual for the chains that the
-// device finds at their end, and one wait.  A chain past its end costs its blocks'
-// exit; one that misses a round waits for the next residual, and the FP64
-// residual costs all chains as much as three iterations.  Rounds of eight with the
-// masks set by the host -> rounds by need -> with half as many again (ms, a
-// trajectory): 96 chains of 4^4 to 8^3x16 in FP16 storage 148 -> 137 -> 124, 12 of
-// them 96 -> 67 -> 60, 24 in FP32 109 -> 69 -> 61, in FP64 118 -> 82 -> 82.  The
-// iterates do not depend on the counts.
+// device finds at their end, and one wait.  A round that leaves chains unended is
+// held once (k_cg_hold_b) while those go on alone: without that they fall out of
+// step, and each goes through its iterations while the others wait.  A chain past
+// its end costs its blocks' exit.  Rounds of eight with the masks set by the host ->
+// by need, half as many again -> held (ms): 96 chains of 4^4 to 8^3x16 in FP16
+// storage 148 -> 124 -> 120, 12 of them 96 -> 60 -> 57, 24 in FP32 109 -> 61 -> 62,
+// in FP64 118 -> 82 -> 82, 2 chains of 16^3x32 98 -> 105 -> 94, 6 of them 265 -> 283
+// -> 255.  The iterates do not depend on the counts.
 template <int PP, int PX>
 static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops,
                                       const d2* phi, d2* X, double tol, int maxiter, bool guess) {
@@ -2431,6 +2448,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
                  v.q.v, v.t.v, (void*)v.p.norm, (void*)st, (void*)part, Bi, c.ds_bs, c.ds_xcd);
         ge = &cached_graph(c, key, [&] { cg_batch_b<PP, PX>(c, B, ops, v, Bi, st, ch); });
     }
+    bool hold = true;   // this round waits for chains that it leaves unended
     for (int n = std::min(Bi, 8); n > 0;) {
         for (int left = n; left > 0;) {
             const int m = std::min(left, Bi);
@@ -2438,6 +2456,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             else cg_batch_b<PP, PX>(c, B, ops, v, m, st, ch);
             left -= m;
         }
+        if (hold) hipLaunchKernelGGL(k_cg_hold_b, dim3(1), dim3(DBS), 0, c.stream, nc, st, (const CGChain*)ch);
         if (PX != P64) {
             FGI_B_LAUNCH((k_add_to64_b<PX>), B.nblk[GRID_VH]), B.cd, nc, st, v.x, sp(X));
             FGI_LAUNCH_CHECK();
@@ -2449,6 +2468,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
         FGI_HIP(hipStreamSynchronize(c.stream));
         n = 0;
         int room = INT_MAX;
+        bool held = false;
         for (int i = 0; i < nc; i++) {
             const CGState& s = c.host_bseen[i].s;
             const CGChain& e = c.host_bseen[i].h;
@@ -2456,6 +2476,10 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
                 throw Error(-4, guess && !e.iters ? "batched CG: non-finite residual of the starting point"
                                                   : "batched CG: non-finite residual");
             if (e.status != CH_RUNNING) continue;
+            if (s.stop_at <= s.base) {   // ended and held back
+                held = true;
+                continue;
+            }
             const double now = s.rr[s.base & 1];
             if (!std::isfinite(now)) throw Error(-4, "batched CG: non-finite residual");
             const double need = std::log(s.rr_stop / now) / (std::log(now / e.rr0) / s.base);
@@ -2464,6 +2488,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             room = std::min(room, s.base0 + Bi * ((maxiter - s.base0 + Bi - 1) / Bi) - s.base);
         }
         n = std::min(n, room);
+        hold = !held;
     }
     for (int i = 0; i < nc; i++) {
         const CGChain& e = c.host_bseen[i].h;

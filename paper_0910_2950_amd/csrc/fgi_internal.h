@@ -40,14 +40,14 @@ struct DevBuf {
 };
 
 // Device-resident iteration state of one CG solve.  Written by the solver
-// kernels and by the host between batches; copied to pinned host memory when
-// the host polls.  Reductions never use atomics: a kernel writes one partial
+// kernels alone, which leave the host a copy in pinned memory for its one wait
+// per inner run or round.  Reductions never use atomics: a kernel writes one partial
 // per block and the kernel after it sums them in a fixed order.
 struct alignas(64) CGState {
     int stop_at;       // first iteration index that must not run (INT_MAX while running)
     int base;          // iteration index of the first iteration of the current batch
     int base0;         // first iteration of the current run (start or reliable update):
-                       // its rr and beta come from the host, later ones from partials
+                       // its rr and beta are set with the run, later ones come from partials
     int act;           // batched solves: 1 when this chain takes part in a masked step
     double rr[2];      // |r|^2 of the iteration vectors, slot k & 1 holds iteration k's
     double pAp;        // <p, A p> of the current iteration
@@ -141,7 +141,7 @@ struct Ctx {
     std::vector<GraphEntry> graphs;
     long graph_captures = 0;   // graphs captured and instantiated so far (a steady state adds none)
     // solver tuning
-    int cg_batch = 8;          // iterations launched between host polls
+    int cg_batch = 8;          // iterations in one captured graph
     // schedule of the Dslash-shaped kernels (set by hand or by fgi_autotune_cg):
     // threads (= even sites) per block, and XCD-aware block order on/off
     int ds_bs = 256;
