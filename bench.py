@@ -692,11 +692,10 @@ def chain_leg(R, U_therm, act, n, ntraj, seed=0x5EED):
                 solves_per_traj=st["solves"] / ntraj, cg_iters_per_traj=st["cg_iters"] / ntraj)
 
 
-# SU(3) products per link of the rectangle force: per nu != mu three pairs of
-# five-link staples sharing their first factor (two four-link remainders of 3
-# products each, summed, then 1 product with the shared factor) and U A; 198
-# flops per 3x3 complex product (27 complex multiply-adds)
-RECT_FORCE_FLOPS_PER_LINK = (3 * 3 * 7 + 1) * 198
+# SU(3) products per link that the rectangles add to the gauge force: eleven
+# instead of two for each half of a (mu, nu) plane; 198 flops per 3x3 complex
+# product (27 complex multiply-adds)
+RECT_FORCE_FLOPS_PER_LINK = (3 * 2 * 9) * 198
 FP64_PEAK_TFLOPS = 78.6
 
 
@@ -706,10 +705,10 @@ def improved_gauge_leg(R, U_therm, inputs, n, c1=-1.0 / 12.0):
     1) from the thermalised links with the timed momenta, timed for both
     actions (no fermions, so the difference is the rectangle kernels' share of
     a trajectory; the field is in equilibrium for the Wilson action only, so
-    the Symanzik dH is a cost probe, not an acceptance), and the rectangle force
-    kernel alone: the total gauge force with and without the rectangles, HIP
-    events on the library's stream around 20 calls each (packing and the
-    plaquette kernel are common to both)."""
+    the Symanzik dH is a cost probe, not an acceptance), and what the rectangles
+    add to the gauge force kernel: the total gauge force with and without them,
+    HIP events on the library's stream around 20 calls each (packing is common
+    to both)."""
     torch = R.torch
     integ = R.fgi.integrator_builtin("FG", 0.1932)
     U = torch.empty_like(U_therm)

@@ -122,8 +122,8 @@ typedef struct {
                            kappa^2 D_eo A_oo^-1 D_oe and the action gains
                            -2 sum_{x odd} log det A(x).  0 = Wilson; in [0, 10],
                            else FGI_EINVAL.  With kappa != 0 it takes prec =
-                           FGI_FP64, or FGI_MP32 (an FP32 inner CG on the FP32
-                           links with FP64 defect correction; the FP64 true
+                           FGI_FP64, or FGI_MP32 (FP32 links, spinors and blocks
+                           inside, reliable updates in FP64; the FP64 true
                            residual decides, so cg_tol holds as in FP64), not
                            FGI_MP16 (FGI_EINVAL); with the Hasenbusch split
                            S_1 and S_2 use the clover operators at kappa' and
@@ -198,9 +198,12 @@ int fgi_create(fgi_ctx** out, int device);
 int fgi_destroy(fgi_ctx* ctx);
 /* Text of the calling thread's last failure ("" if none). */
 const char* fgi_last_error(void);
-/* Tuning/diagnostic options: "cg_batch" (CG iterations launched between host
- * polls; each batch is one replay of a captured HIP graph), "dslash_block"
- * (64, 128 or 256 even sites per block of the Dslash-shaped kernels),
+/* Tuning/diagnostic options: "cg_batch" (CG iterations in one
+ * captured HIP graph; a solve replays it as often as its decay asks for and
+ * launches the rest one by one; a solve that reaches cg_maxiter ends on a whole
+ * batch), "dslash_block" (64, 128 or 256 even sites per block of the
+ * Dslash-shaped kernels; lattices of at most 32768 even sites use blocks of 64
+ * sites by four waves instead, except with 18-real 16-bit links),
  * "xcd_order" (1: XCD-aware block order, 0: linear; also the block order of
  * the force kernels), "fg_start" (1, the default: in the displacement form of
  * an FG stage the solves of the displaced force start from the solutions at
@@ -227,7 +230,7 @@ int fgi_get_profile(fgi_ctx* ctx, double* ms, long* launches, long* sites);
 typedef struct {
     int dslash_block;             /* even sites (threads) per block of the Dslash-shaped kernels: 64, 128, 256 */
     int xcd_order;                /* 1: blocks ordered so each XCD owns a contiguous slab of sites; 0: linear */
-    int cg_batch;                 /* CG iterations launched between host polls */
+    int cg_batch;                 /* CG iterations in one captured HIP graph */
     int cg_form;                  /* single-lattice CG: 0 classic (five launches per iteration), 1 the
                                      Chronopoulos-Gear form (four); batched solves use the classic form */
     double sched_us_per_iter[6];  /* measured: candidate (block 64, 128, 256) x (order 0, 1), index 2 k + order */
