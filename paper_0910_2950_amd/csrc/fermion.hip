@@ -13,6 +13,7 @@
 #include <climits>
 #include <cmath>
 
+#include "cg_stop.h"
 #include "fgi_internal.h"
 
 namespace fgi {
@@ -282,12 +283,13 @@ __device__ __forceinline__ void dslash_body(const DArgs& A, int b, int nb, doubl
     const Geom& g = A.g;
     // Solver state, read up front in one batch of loads (reading each field
     // where it is used puts a memory round trip per branch in front of the
-    // data loads).  Nothing read here is written by the same launch.
+    // data loads).  Of what is used here the same launch writes only stop_at
+    // (see cg_leaves).
     StateView S{INT_MAX, 0, 0, 1, {0.0, 0.0}, 0.0, 0.0, 0.0};
     if (A.st) S = load_state(A.st);
     const int iter = S.base + A.iter;
-    if (A.st) {  // uniform over the chain's blocks: converged / masked chains no-op
-        if (A.gate ? !S.act : S.stop_at <= iter) return;
+    if (A.st) {  // converged / masked chains no-op
+        if (A.gate ? !S.act : cg_leaves(S.stop_at, iter, MODE == M_HOP && A.cgs && b < nb)) return;
         if constexpr (MODE == M_HOP) {
             if (b >= nb) {  // the reduction block: pAp of this iteration, or the CG-form state
                 if (A.cgs) {
@@ -601,8 +603,9 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
     StateView S{INT_MAX, 0, 0, 1, {0.0, 0.0}, 0.0, 0.0, 0.0};
     if (A.st) S = load_state(A.st);
     const int iter = S.base + A.iter;
+    const bool idle = A.st && (A.gate ? !S.act : cg_leaves(S.stop_at, iter, MODE == M_HOP && A.cgs && b < nb));
     if (A.st && (early || b >= nb)) {
-        if (A.gate ? !S.act : S.stop_at <= iter) return;
+        if (idle) return;
         if constexpr (MODE == M_HOP) {
             if (b >= nb) {
                 if (A.cgs) {
@@ -649,7 +652,7 @@ __device__ __forceinline__ void dslash_split_body(const DArgs& A, int b, int nb,
     else if (w == 2) hop_pair<2, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
     else hop_pair<3, PIN, PL, RECON, G5IN, R>(g, A.p_out, s, c, A.links, A.in, L.uh, lane);
     __syncthreads();
-    if (A.st && (A.gate ? !S.act : S.stop_at <= iter)) return;
+    if (idle) return;
     const R unit = R(link_unit<PL, RECON>());
     cx<R> acc[3];
     if constexpr (CL && MODE == M_HOP) {   // A_oo^-1 needs both spins of the wave's block
@@ -809,6 +812,19 @@ __global__ void __launch_bounds__(256) k_dslash_split_b(DArgs base, const ChainD
     dslash_split_body<MODE, PIN, PC, POUT, PX, PL, RECON, G5IN, false>(A, m.y, d.nblk[GRID_DS], 1, L);
 }
 
+// The iteration's rr, beta or stop (cg_open); block 0 records them for the kernels after it.
+__device__ __forceinline__ bool open_iteration(CGState* st, const StateView& S, int iter, const double* partial, int b,
+                                               int nb, double* lds, double& beta) {
+    return cg_open(
+        S, iter, b == 0 && threadIdx.x == 0, [&] { return sum_partials(partial, nb, lds); },
+        [&](double rr, double be, bool stop) {
+            st->rr[iter & 1] = rr;
+            if (stop) st->stop_at = iter;
+            else st->beta = be;
+        },
+        beta);
+}
+
 // First kernel of a CG iteration: p = r + beta p, stored in p's precision.
 // Later iterations of a run take |r_iter|^2 from the previous M_CGX's
 // partials, summed in every block in the same order (so all blocks agree
@@ -828,20 +844,8 @@ __device__ __forceinline__ void cg_p_body(int Vh, SpinorPtr p, SpinorPtr r, CGSt
     RawSp<PP> pp_raw;
     fetch_sp<PX>(r, sl, Vh, rr_raw);
     fetch_sp<PP>(p, sl, Vh, pp_raw);
-    const int iter = S.base + j;
-    if (S.stop_at <= iter) return;
-    double beta = S.beta;
-    if (iter != S.base0) {
-        const double rr = sum_partials(partial, nb, lds);
-        const bool stop = rr <= S.rr_stop;
-        beta = rr / ((iter & 1) ? S.rr[0] : S.rr[1]);  // |r|^2 of iteration iter - 1
-        if (b == 0 && threadIdx.x == 0) {
-            st->rr[iter & 1] = rr;
-            if (stop) st->stop_at = iter;
-            else st->beta = beta;
-        }
-        if (stop) return;
-    }
+    double beta = 0.0;
+    if (!open_iteration(st, S, S.base + j, partial, b, nb, lds, beta)) return;
     if (s >= Vh) return;
     cx<R> rv[4][3], pv[4][3];
     SpinorIO<PX, R>::decode(rr_raw, rv);
@@ -882,20 +886,8 @@ __device__ __forceinline__ void cg_p_split_body(int Vh, const SpinorPtr& p, cons
     cx<R> rv[3], pv[3];
     load_spin<PX, R>(r, s, Vh, w, rv);
     load_spin<PP, R>(p, s, Vh, w, pv);
-    const int iter = S.base + j;
-    if (S.stop_at <= iter) return;
-    double beta = S.beta;
-    if (iter != S.base0) {
-        const double rr = sum_partials(partial, nb, lds);
-        const bool stop = rr <= S.rr_stop;
-        beta = rr / ((iter & 1) ? S.rr[0] : S.rr[1]);  // |r|^2 of iteration iter - 1
-        if (b == 0 && threadIdx.x == 0) {
-            st->rr[iter & 1] = rr;
-            if (stop) st->stop_at = iter;
-            else st->beta = beta;
-        }
-        if (stop) return;
-    }
+    double beta = 0.0;
+    if (!open_iteration(st, S, S.base + j, partial, b, nb, lds, beta)) return;
     const R be = R(beta);
 #pragma unroll
     for (int k = 0; k < 3; k++) {
