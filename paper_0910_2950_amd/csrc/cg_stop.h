@@ -36,4 +36,13 @@ constexpr bool cg_open(const State& S, int iter, bool first, Sum sum, Record rec
 // records the stop beside it (its output is scratch, so it just goes on).
 constexpr bool cg_leaves(int stop_at, int iter, bool opens) { return opens ? stop_at < iter : stop_at <= iter; }
 
+// Where an inner run that began at iteration base0 is cut off: after the whole
+// batches that reach maxiter (any maxiter up to the largest int; the sum past it
+// stays there).
+constexpr int cg_cut(int base0, int maxiter, int batch) {
+    const long long left = (long long)maxiter - base0;
+    const long long cut = base0 + (left + batch - 1) / batch * batch;
+    return cut < 0x7fffffff ? (int)cut : 0x7fffffff;
+}
+
 }  // namespace fgi

@@ -2080,7 +2080,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     // waited twice.  The iterates do not depend on the counts.
     int k = 0, base0 = 0;   // iterations launched so far; start of the current inner run
     const int whole = op64.blk ? 1 : B;
-    int kcap = whole * ((maxiter + whole - 1) / whole);   // where an unfinished run is cut off: whole batches from base0
+    int kcap = cg_cut(0, maxiter, whole);   // where an unfinished run is cut off
     int n = std::min(std::min(B, 8), kcap);
     double rr_first = 0.0;
     for (;;) {
@@ -2143,7 +2143,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
                 cgs_partials<PP, PX>(c, g, v);
             }
             base0 = kend;
-            kcap = kend + whole * ((maxiter - kend + whole - 1) / whole);
+            kcap = cg_cut(kend, maxiter, whole);
             stop = std::max(run.ru2 * now, target);
         }
         const double need = std::log(stop / now) / (std::log(now / rr_first) / kend);

@@ -87,3 +87,34 @@ def test_every_interleaving_of_a_block(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
     assert r.stdout.startswith("768 runs"), r.stdout
+
+
+CUTS = r"""
+#include <climits>
+#include <cstdio>
+#include <initializer_list>
+#include "cg_stop.h"
+using fgi::cg_cut;
+int main() {
+    int faults = 0;
+    for (int batch : {1, 3, 8, 1024})
+        for (int base0 : {0, 1, 7, 10, 1000})
+            for (int maxiter : {base0 + 1, base0 + 7, base0 + 8, base0 + 9, 20000, INT_MAX - 8, INT_MAX - 1, INT_MAX}) {
+                const int cut = cg_cut(base0, maxiter, batch);
+                if (cut < maxiter) faults++;   // never short of the limit, and less than a batch past it
+                if (cut != INT_MAX && ((cut - base0) % batch || cut - maxiter >= batch)) faults++;
+                if (cut == INT_MAX && maxiter < INT_MAX - batch) faults++;
+            }
+    printf("%d faults\n", faults);
+    return faults != 0;
+}
+"""
+
+
+def test_cut_off_of_a_run(tmp_path):
+    src, exe = tmp_path / "cuts.cpp", tmp_path / "cuts"
+    src.write_text(CUTS)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-fsanitize=undefined", "-fno-sanitize-recover", "-I", CSRC, str(src),
+                    "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
