@@ -948,6 +948,7 @@ struct CGRun {
     double tol2, ru2;      // tol^2, ru_delta^2 (0: the inner run goes straight to the target)
     const double* bb;      // |phi|^2 on the device
     double* seen;          // host: [0] |phi|^2, [1] |r|^2 of the last true residual
+    int maxiter, batch;    // of a batch's chains (cg_cut)
 };
 __device__ __forceinline__ double inner_stop(const CGRun& C, double rr, double target) {
     const double s = C.ru2 * rr;
@@ -990,7 +991,7 @@ __global__ void __launch_bounds__(DBS) k_cg_restart(CGState* st, CGRun C, const 
 
 // ---- the chains of a batch, one block each: as above, and each chain's own end
 __global__ void __launch_bounds__(DBS) k_cg_start_b(const ChainDesc* __restrict__ cd, CGState* st, CGChain* ch, CGRun C,
-                                                    const double* part, int maxiter) {
+                                                    const double* part) {
     __shared__ double lds[DBS / 64];
     const int i = blockIdx.x;
     const double bb = C.bb[i], target = C.tol2 * bb;
@@ -1007,7 +1008,7 @@ __global__ void __launch_bounds__(DBS) k_cg_start_b(const ChainDesc* __restrict_
     e.bb = bb;
     e.rr0 = e.rr = rr0;
     e.status = there ? CH_CONVERGED : isfinite(rr0) ? CH_RUNNING : CH_BAD;
-    e.maxiter = maxiter;
+    e.cut = cg_cut(0, C.maxiter, C.batch);
     ch[i] = e;
 }
 
@@ -1019,7 +1020,7 @@ __global__ void __launch_bounds__(DBS) k_advance_b(const ChainDesc* __restrict__
     advance_body(st + i, partial + cd[i].blk0[GRID_DS], cd[i].nblk[GRID_DS], n, lds);
     if (threadIdx.x) return;
     const CGState& s = st[i];
-    st[i].act = ch[i].status == CH_RUNNING && (s.stop_at <= s.base || s.base >= ch[i].maxiter);
+    st[i].act = ch[i].status == CH_RUNNING && (s.stop_at <= s.base || s.base >= ch[i].cut);
 }
 
 // Unless all running chains have ended their inner runs (or one was cut off), hold
@@ -1053,11 +1054,12 @@ __global__ void __launch_bounds__(DBS) k_cg_restart_b(const ChainDesc* __restric
         e.rr = rr;
         e.iters = kend;
         s.act = 0;
-        if (!isfinite(rr) || rr <= target || kend >= e.maxiter) {
+        if (!isfinite(rr) || rr <= target || kend >= C.maxiter) {
             e.status = !isfinite(rr) ? CH_BAD : rr <= target ? CH_CONVERGED : CH_CUT;
             s.stop_at = 0;   // no iteration runs from now on
         } else {
             e.updates++;
+            e.cut = cg_cut(kend, C.maxiter, C.batch);
             s.beta = rr / s.rr[(kend - 1) & 1];
             s.rr[kend & 1] = rr;
             s.rr_stop = inner_stop(C, rr, target);
@@ -2015,7 +2017,7 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     double* scal = (double*)c.scal.get(sizeof(double) * 64);
     norm2(c, g, phi, scal);
     const double drop = ru_drop(c, PP);
-    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, scal, c.host_scal};
+    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, scal, c.host_scal, maxiter, c.cg_batch};
     d2* r64 = (d2*)c.cg_r.get(n64);
     auto start = [&](const double* part, int nb) {
         hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(DBS), 0, c.stream, st, run, part, nb);
@@ -2388,7 +2390,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
     double* bb = (double*)c.bscal.get(sizeof(double) * nc);
     CGState* st = (CGState*)c.bstate.get((sizeof(CGState) + sizeof(CGChain)) * nc);
     CGChain* ch = (CGChain*)(st + nc);
-    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, bb, nullptr};
+    const CGRun run{tol * tol, PX == P64 ? 0.0 : drop * drop, bb, nullptr, maxiter, c.cg_batch};
     hipLaunchKernelGGL(k_norm2_partials_b, dim3(B.nblk[GRID_VH]), dim3(DBS), 0, c.stream, B.cd, nc, phi, part);
     FGI_LAUNCH_CHECK();
     final_sums_b(c, B, part, GRID_VH, bb);
@@ -2403,7 +2405,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
         true_residual_b<P64>(c, B, op64, phi, X, sp(r64), SpinorPtr{}, st);
     }
     hipLaunchKernelGGL(k_cg_start_b, dim3(nc), dim3(DBS), 0, c.stream, B.cd, st, ch, run,
-                       guess ? (const double*)part : nullptr, maxiter);
+                       guess ? (const double*)part : nullptr);
     FGI_LAUNCH_CHECK();
     CGVecs v{};
     float* norms = (float*)c.s_norms.get(sizeof(float) * 3 * (size_t)B.sites);
@@ -2476,8 +2478,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             if (!std::isfinite(now)) throw Error(-4, "batched CG: non-finite residual");
             const double need = std::log(s.rr_stop / now) / (std::log(now / e.rr0) / s.base);
             n = std::max(n, !(need > 0.0) || need > 1e6 ? Bi : (int)std::min(std::ceil(1.5 * need), 64.0));
-            // an unfinished run is cut off whole batches after its start
-            room = std::min(room, s.base0 + Bi * ((maxiter - s.base0 + Bi - 1) / Bi) - s.base);
+            room = std::min(room, e.cut - s.base);   // no chain past its cut-off
         }
         n = std::min(n, room);
         hold = !held;

@@ -61,7 +61,8 @@ static_assert(sizeof(CGState) == 64, "CGState is read as 16-byte vectors");
 enum ChainStatus { CH_RUNNING = 0, CH_CONVERGED = 1, CH_CUT = 2, CH_BAD = 3 };   // CUT: at maxiter; BAD: not finite
 struct CGChain {
     double bb, rr0, rr;              // |phi|^2; |r|^2 at the start and of the last true residual
-    int status, iters, updates, maxiter;
+    int status, iters, updates;
+    int cut;                         // where its inner run is cut off (cg_cut), as in a solve of its own
 };
 struct CGSeen {
     CGState s;

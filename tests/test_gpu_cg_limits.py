@@ -1,5 +1,6 @@
 """Where cg_maxiter cuts a solve off: the limit itself may be as large as an int
-holds."""
+holds, and a chain of a batch is cut off where its solve alone would be, however
+long the batch's rounds are."""
 import numpy as np
 import pytest
 import torch
@@ -33,3 +34,37 @@ def test_largest_limit(ctx, prec, recon, csw):
     for X, st in out[1:]:
         assert torch.equal(X, out[0][0]) and st["cg_iters"] == out[0][1]["cg_iters"] > 0
         assert st["max_rel_resid"] == out[0][1]["max_rel_resid"] <= 1e-11
+
+
+# the large kappas decay unevenly, so that a round's length misses their inner runs' ends
+MIX = [((4, 4, 4, 4), 0.25), ((6, 4, 4, 6), 0.12), ((2, 4, 2, 4), 0.2), ((4, 4, 6, 4), 0.3), ((4, 4, 4, 4), 0.157)]
+
+
+@pytest.mark.parametrize("cg_batch", [5, 8])
+@pytest.mark.parametrize("prec,recon", [("mp16", 12), ("mp32", 18), ("fp64", 18)])
+def test_batch_is_cut_off_as_single_solves(cg_batch, prec, recon):
+    """Chains whose inner runs end at different iterations, over every limit from
+    inside the first batch to where the slowest chain converges: links, momenta,
+    dH and the iterations counted, bitwise as alone."""
+    ctx = Context(0)
+    try:
+        ctx.set_option("cg_batch", cg_batch)
+        starts = [synth.hot_start(d, synth.SEED_BASE + 4720 + k) for k, (d, _) in enumerate(MIX)]
+        counts = []
+        for maxiter in range(3, 70):
+            kw = dict(cg_tol=1e-8, prec=prec, link_recon=recon, cg_maxiter=maxiter)
+            chains = [dict(dims=d, beta=5.6, kappa=k, U=dev(s[0]), P=dev(s[1]), eta=dev(s[2]))
+                      for (d, k), s in zip(MIX, starts)]
+            dHb, stb = ctx.trajectory_batched(chains, Action(beta=0.0, **kw), "PQP", 0.01, 1, allow_noconv=True)
+            its, most = 0, 0
+            for ch, s, dH in zip(chains, starts, dHb):
+                U, P = dev(s[0]), dev(s[1])
+                d1, st = ctx.trajectory(ch["dims"], Action(beta=5.6, kappa=ch["kappa"], **kw), "PQP", 0.01, 1, U, P,
+                                        dev(s[2]), allow_noconv=True)
+                assert torch.equal(U, ch["U"]) and torch.equal(P, ch["P"]) and d1 == dH, (maxiter, ch["dims"])
+                its, most = its + st["cg_iters"], max(most, st["cg_iters_max"])
+            assert stb["cg_iters"] == its and stb["cg_iters_max"] == most, maxiter
+            counts.append(its)
+        assert counts[0] < counts[-1]   # the limits do cut solves off
+    finally:
+        ctx.close()
