@@ -2371,14 +2371,19 @@ static void cg_batch_b(Ctx& c, const Batch& B, const FermionOp& ops, const CGVec
 //
 // A round is half as many iterations again as the slowest chain's inner run still
 // needs by its decay so far, one masked true residual for the chains that the
-// device finds at their end, and one wait.  A round that leaves chains unended is
-// held once (k_cg_hold_b) while those go on alone: without that they fall out of
-// step, and each goes through its iterations while the others wait.  A chain past
-// its end costs its blocks' exit.  Rounds of eight with the masks set by the host ->
-// by need, half as many again -> held (ms): 96 chains of 4^4 to 8^3x16 in FP16
-// storage 148 -> 124 -> 120, 12 of them 96 -> 60 -> 57, 24 in FP32 109 -> 61 -> 62,
-// in FP64 118 -> 82 -> 82, 2 chains of 16^3x32 98 -> 105 -> 94, 6 of them 265 -> 283
-// -> 255.  The iterates do not depend on the counts.
+// device finds at their end, and one wait.  While a chain's inner run goes on, all
+// true residuals are held back (k_cg_hold_b), so that the chains enter their next
+// inner runs together.  Out of step, a round ends for one chain or another every
+// time, and the launches past a chain's end cost its blocks' exit; holding back for
+// one round only lets large chains drift apart.  Rounds of a fixed batch with the
+// masks set by the host -> held for one round -> held:
+//   16^3x32 thermalised at beta 5.6, kappa 0.1575, FG n = 16 in FP16 storage with
+//   fixed-point links (s): 2 chains 2.17 -> 2.42 -> 2.05, 8 chains 8.33 -> 8.91 ->
+//   7.79, where one chain alone takes 1.05;
+//   links exp(0.45 X), kappa 0.15 to 0.157 (ms): 96 chains of 4^4 to 8^3x16 in FP16
+//   storage 158 -> 120 -> 119, 24 in FP32 117 -> 69.5 -> 63.8, 24 in FP64 118 -> 81.2
+//   -> 80.9, 12 with fixed-point links 96.6 -> 73.5 -> 73.4, 3 in FP16 45 -> 33.1 -> 32.2.
+// The iterates do not depend on the counts.
 template <int PP, int PX>
 static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& op64, const FermionOp& ops,
                                       const d2* phi, d2* X, double tol, int maxiter, bool guess) {
@@ -2442,7 +2447,6 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
                  v.q.v, v.t.v, (void*)v.p.norm, (void*)st, (void*)part, Bi, c.ds_bs, c.ds_xcd);
         ge = &cached_graph(c, key, [&] { cg_batch_b<PP, PX>(c, B, ops, v, Bi, st, ch); });
     }
-    bool hold = true;   // this round waits for chains that it leaves unended
     for (int n = std::min(Bi, 8); n > 0;) {
         for (int left = n; left > 0;) {
             const int m = std::min(left, Bi);
@@ -2450,7 +2454,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             else cg_batch_b<PP, PX>(c, B, ops, v, m, st, ch);
             left -= m;
         }
-        if (hold) hipLaunchKernelGGL(k_cg_hold_b, dim3(1), dim3(DBS), 0, c.stream, nc, st, (const CGChain*)ch);
+        hipLaunchKernelGGL(k_cg_hold_b, dim3(1), dim3(DBS), 0, c.stream, nc, st, (const CGChain*)ch);
         if (PX != P64) {
             FGI_B_LAUNCH((k_add_to64_b<PX>), B.nblk[GRID_VH]), B.cd, nc, st, v.x, sp(X));
             FGI_LAUNCH_CHECK();
@@ -2462,7 +2466,6 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
         FGI_HIP(hipStreamSynchronize(c.stream));
         n = 0;
         int room = INT_MAX;
-        bool held = false;
         for (int i = 0; i < nc; i++) {
             const CGState& s = c.host_bseen[i].s;
             const CGChain& e = c.host_bseen[i].h;
@@ -2470,10 +2473,7 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
                 throw Error(-4, guess && !e.iters ? "batched CG: non-finite residual of the starting point"
                                                   : "batched CG: non-finite residual");
             if (e.status != CH_RUNNING) continue;
-            if (s.stop_at <= s.base) {   // ended and held back
-                held = true;
-                continue;
-            }
+            if (s.stop_at <= s.base) continue;   // ended and held back
             const double now = s.rr[s.base & 1];
             if (!std::isfinite(now)) throw Error(-4, "batched CG: non-finite residual");
             const double need = std::log(s.rr_stop / now) / (std::log(now / e.rr0) / s.base);
@@ -2481,7 +2481,6 @@ static std::vector<CGResult> cg_run_b(Ctx& c, const Batch& B, const FermionOp& o
             room = std::min(room, e.cut - s.base);   // no chain past its cut-off
         }
         n = std::min(n, room);
-        hold = !held;
     }
     for (int i = 0; i < nc; i++) {
         const CGChain& e = c.host_bseen[i].h;
