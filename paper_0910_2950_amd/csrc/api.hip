@@ -1943,11 +1943,13 @@ struct BDriver {
 namespace {
 // Chain table and block counts of a batch (host side).  The Dslash grid
 // (GRID_DS) uses the context's current Dslash block size.
-void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<ChainDesc>& cd, Batch& B) {
+void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, double c1, std::vector<ChainDesc>& cd, Batch& B) {
     const bool ferm = chains[0].kappa != 0.0;
     cd.assign(nchains, ChainDesc{});
     B = Batch{};
     B.nc = nchains;
+    long total = 0;
+    for (int i = 0; i < nchains; i++) total += make_geom(chains[i].dims).V;
     for (int i = 0; i < nchains; i++) {
         const fgi_chain& ch = chains[i];
         if ((ch.kappa != 0.0) != ferm) throw Error(FGI_EINVAL, "all chains need fermions or none");
@@ -1965,10 +1967,11 @@ void describe_batch(Ctx& c, int nchains, const fgi_chain* chains, std::vector<Ch
         const int bsz[4] = {256, 256, 256, ds_sites(c, d.g.Vh)};
         for (int k = 0; k < 5; k++) {
             d.blk0[k] = B.nblk[k];
-            d.nblk[k] = k == GRID_GS ? (d.g.V <= GAUGE_SPLIT_MAX_V ? 8 * ((d.g.Vh + 63) / 64) : 0)
+            d.nblk[k] = k == GRID_GS ? (gauge_split(d.g, total, c1) ? 8 * ((d.g.Vh + 63) / 64) : 0)
                                      : (int)((n[k] + bsz[k] - 1) / bsz[k]);
             B.nblk[k] += d.nblk[k];
         }
+        B.gauge_plain = B.gauge_plain || d.nblk[GRID_GS] == 0;
         d.user_U = ch.U;
         d.user_P = ch.P;
         d.user_eta = ch.eta;
@@ -2025,7 +2028,7 @@ extern "C" int fgi_trajectory_batched(fgi_ctx* ctx, int nchains, const fgi_chain
         BFields f(c, *act);
         std::vector<ChainDesc> cd;
         Batch B;
-        describe_batch(c, nchains, chains, cd, B);
+        describe_batch(c, nchains, chains, act->c1, cd, B);
         upload_batch(c, cd, B);
         f.B = B;
         f.st = st;
@@ -2214,7 +2217,7 @@ int fgi_autotune_batched(fgi_ctx* ctx, int nchains, const fgi_chain* chains, con
         BFields f(c, *act), f64(c, a64);
         std::vector<ChainDesc> cd;
         Batch B;
-        describe_batch(c, nchains, chains, cd, B);
+        describe_batch(c, nchains, chains, act->c1, cd, B);
         upload_batch(c, cd, B);
         f.B = B;
         f.fermions = true;
@@ -2237,7 +2240,7 @@ int fgi_autotune_batched(fgi_ctx* ctx, int nchains, const fgi_chain* chains, con
         f64.X = f.X;
         f64.fermions = true;
         auto rebuild = [&] {  // the Dslash grid follows the block size
-            describe_batch(c, nchains, chains, cd, B);
+            describe_batch(c, nchains, chains, act->c1, cd, B);
             upload_batch(c, cd, B);
             f.B = B;
             f64.B = B;

@@ -196,6 +196,20 @@ inline double ru_drop(const Ctx& c, int prec) { return c.ru_delta > 0.0 ? c.ru_d
 // 56.8 -> 39.3.  Above the line every SIMD has its waves already: 13440 sites
 // 28.7 -> 31.2 (with the rectangles 68.0 -> 66.7), 16^4 73.0 -> 88.9 (203 -> 200).
 constexpr int GAUGE_SPLIT_MAX_V = 8192;
+// A batch fills the chip with its total volume, so a chain whose force has the same
+// bits either way (no rectangles) takes the six waves by that: up to the same line,
+// or, where its links per (mu, parity) are no multiple of a wave and one-thread waves
+// hold two directions, up to GAUGE_SPLIT_MAX_RAGGED.  One thread per link and split
+// (us, force and update): 4^4 chains of 4096, 8192, 12288 and 65536 sites in all 17.5,
+// 13.1; 19.9, 19.3; 21.8, 25.3; 68.8, 107.9; 8^4 of 8192, 12288 and 131072 21.5, 20.2;
+// 22.3, 25.4; 118, 197; 6^4 (648 links) of 20736, 41472 and 62208 43.2, 37.7; 71.1,
+// 66.8; 92.6, 99.2; 96 chains of 4^4 to 8^3x16 198, 300.  With rectangles the two
+// differ in the last bits, so the kernel stays the one of the chain alone.
+constexpr int GAUGE_SPLIT_MAX_RAGGED = 49152;
+inline bool gauge_split(const Geom& g, long total, double c1) {
+    if (g.V > GAUGE_SPLIT_MAX_V) return false;
+    return c1 != 0.0 || total <= (g.Vh % 64 ? GAUGE_SPLIT_MAX_RAGGED : GAUGE_SPLIT_MAX_V);
+}
 
 enum DsKind { DS_PLAIN = 0, DS_SPLIT = 1 };
 
@@ -207,6 +221,7 @@ struct Batch {
     int nblk[5] = {0, 0, 0, 0, 0};
     long sites = 0, vol = 0, links = 0;  // totals: sum Vh, sum V, sum 4V
     long min_vol = 0, max_vol = 0;       // smallest and largest chain
+    bool gauge_plain = false;            // some chain's gauge force is not split
     // Dslash-shaped launches, one per DsKind that has chains: block -> (chain,
     // block of the chain), then one (chain, its block count) per chain for the
     // reduction blocks

@@ -635,7 +635,7 @@ k_gauge_force_b(const ChainDesc* __restrict__ cd, int nc, const d2* __restrict__
                 double c1, int accumulate) {
     const int c = find_chain(cd, nc, blockIdx.x, GRID_4V);
     const ChainDesc& d = cd[c];
-    if (d.g.V <= GAUGE_SPLIT_MAX_V) return;
+    if (d.nblk[GRID_GS]) return;   // it has the split kernel
     gauge_force_body<IMP>(d.g, -d.beta / 6.0 * coef, ForceCoef{1.0 - 8.0 * c1, c1}, U + 9 * d.link0, F + 8 * d.link0,
                           accumulate, (blockIdx.x - d.blk0[GRID_4V]) * blockDim.x + threadIdx.x);
 }
@@ -1138,7 +1138,7 @@ static void launch_gauge_force_b(Ctx& c, const Batch& B, const d2* U, double* F,
     if (B.nblk[GRID_GS])
         hipLaunchKernelGGL(k_gauge_force_split_b<IMP>, dim3(B.nblk[GRID_GS]), dim3(384), 0, c.stream, B.cd, B.nc, U, F,
                            coef, c1, accumulate);
-    if (B.max_vol > GAUGE_SPLIT_MAX_V)
+    if (B.gauge_plain)
         hipLaunchKernelGGL(k_gauge_force_b<IMP>, dim3(B.nblk[GRID_4V]), dim3(BS), 0, c.stream, B.cd, B.nc, U, F, coef, c1,
                            accumulate);
     FGI_LAUNCH_CHECK();

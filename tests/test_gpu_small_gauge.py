@@ -52,3 +52,25 @@ def test_link_update(ctx, dims, h):
     U0, P0, _, _ = synth.hot_start(dims, synth.SEED_BASE + 4500, fermions=False)
     U = ctx.link_update(dims, h, dev(P0), dev(U0)).cpu().numpy()
     assert np.max(np.abs(U - orc.link_update(dims, h, P0, U0))) <= 2.5e-14
+
+
+@pytest.mark.parametrize("c1", [0.0, -1.0 / 12.0])
+@pytest.mark.parametrize("sizes", [[(4, 4, 4, 4)] * 32, [(4, 4, 4, 4)] * 33, [(2, 2, 2, 2), (8, 8, 8, 16), (8, 8, 8, 18)],
+                                   [(6, 6, 6, 6)] * 3 + [(8, 8, 8, 8)], [(6, 6, 6, 6)] * 38])
+def test_batch_equals_single_runs_whatever_its_volume(ctx, sizes, c1):
+    """A batch's total volume chooses between the force kernels (8192 sites, 49152
+    for ragged chains, from both sides and mixed): bitwise the chains' own runs."""
+    starts = {}
+    for d in sizes:
+        if d not in starts:
+            starts[d] = [synth.hot_start(d, synth.SEED_BASE + 4450 + k, fermions=False)[:2] for k in range(2)]
+    chains, single = [], []
+    for k, d in enumerate(sizes):
+        U0, P0 = starts[d][k % 2]
+        U, P = dev(U0), dev(P0)
+        dH, _ = ctx.trajectory(d, fgi.Action(beta=5.5 + 0.01 * k, c1=c1), "FG", 0.25, 2, U, P)
+        single.append((U, P, dH))
+        chains.append(dict(dims=d, beta=5.5 + 0.01 * k, kappa=0.0, U=dev(U0), P=dev(P0)))
+    dH, _ = ctx.trajectory_batched(chains, fgi.Action(beta=0.0, c1=c1), "FG", 0.25, 2)
+    for ch, d, (U, P, d1) in zip(chains, dH, single):
+        assert torch.equal(ch["U"], U) and torch.equal(ch["P"], P) and d == d1, ch["dims"]
