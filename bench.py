@@ -332,7 +332,7 @@ def dslash_roofline_large(R, U_therm, prec, recon):
         R.ctx.cg_solve(dims_b, act, Ub, phi, allow_noconv=True)
     ms, launches, sites = R.ctx.get_profile()
     R.ctx.set_option("profile", 0)
-    R.ctx.set_option("ru_delta", 0.1)
+    R.ctx.set_option("ru_delta", 0)   # by storage again
     del Ub, phi
     torch.cuda.empty_cache()
     bps = DSLASH_BYTES[(prec, recon)]

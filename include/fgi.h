@@ -209,8 +209,8 @@ const char* fgi_last_error(void);
  * an FG stage the solves of the displaced force start from the solutions at
  * the undisplaced links, which are a function of the stage's links alone, so
  * the stage stays reversible; 0: from zero), "graphs" (0: launch the batch
- * kernels one by one instead), "ru_delta" (reliable-update residual drop; until
- * set, 0.1 with 16-bit and 0.01 with FP32 inner storage),
+ * kernels one by one instead), "ru_delta" (reliable-update residual drop in
+ * (0, 1); 0, the default: 0.1 with 16-bit and 0.01 with FP32 inner storage),
  * "cg_form" (0, the default: the classic CG iteration, five launches; 1: the
  * Chronopoulos-Gear form, four launches, which applies the operator to the
  * residual and carries the direction's image by recurrence, with <p, A p>

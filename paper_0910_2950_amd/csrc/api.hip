@@ -474,7 +474,7 @@ int fgi_set_option(fgi_ctx* ctx, const char* name, double value) {
             if (value < 1 || value > 1024) throw Error(FGI_EINVAL, "cg_batch out of range");
             c.cg_batch = (int)value;
         } else if (n == "ru_delta") {
-            if (!(value > 0 && value < 1)) throw Error(FGI_EINVAL, "ru_delta must be in (0,1)");
+            if (!(value >= 0 && value < 1)) throw Error(FGI_EINVAL, "ru_delta must be in [0, 1)");
             c.ru_delta = value;
         } else if (n == "dslash_block") {
             if (!(value == 64 || value == 128 || value == 256))
