@@ -488,21 +488,24 @@ CGResult clover_cg(Ctx& c, const FermionOp& op, const d2* blk, const d2* phi, d2
 // Mixed precision: FP32 inner iterations on the FP32 links of op32 and an FP32
 // copy of the blocks, FP64 reliable updates, so the solution meets tol exactly
 // as the FP64 solver's does.  Where the FP32 iteration is not finite (a
-// right-hand side beyond the FP32 range, a broken recursion) FP64 takes over
-// from the start.
+// right-hand side beyond the FP32 range, a broken recursion) FP64 goes on from x
+// as the last reliable update left it, with what is left of maxiter; only where
+// the correction itself was not finite does it start from zero.
 CGResult clover_cg_mp(Ctx& c, const FermionOp& op, const FermionOp& op32, const d2* blk, const d2* phi, d2* x,
                       double tol, int maxiter, bool guess) {
     const size_t n = 72 * (size_t)op.g->V;
     f2* blk32 = (f2*)c.cl_blk32.get(sizeof(f2) * n);
     hipLaunchKernelGGL(k_blk_to_f32, dim3((unsigned)((n + CBS - 1) / CBS)), dim3(CBS), 0, c.stream, n, blk, blk32);
     FGI_LAUNCH_CHECK();
-    try {
-        return cg_solve(c, with_blocks(op, blk), with_blocks(op32, blk32), P32, phi, x, tol, maxiter, guess);
-    } catch (const Error& e) {
-        if (e.code != -4) throw;
+    const CGResult r32 = cg_solve(c, with_blocks(op, blk), with_blocks(op32, blk32), P32, phi, x, tol, maxiter, guess);
+    if (!r32.broke) return r32;
+    if (r32.iters >= maxiter) {
+        if (r32.broke == CG_BROKE_LOST) throw Error(-4, "CG: non-finite residual");
+        return r32;
     }
-    CGResult r = clover_cg(c, op, blk, phi, x, tol, maxiter, false);
-    r.reliable_updates++;
+    CGResult r = clover_cg(c, op, blk, phi, x, tol, maxiter - r32.iters, r32.broke == CG_BROKE_KEPT);
+    r.iters += r32.iters;
+    r.reliable_updates += r32.reliable_updates + 1;
     return r;
 }
 

@@ -2085,6 +2085,11 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
     int kcap = cg_cut(0, maxiter, whole);   // where an unfinished run is cut off
     int n = std::min(std::min(B, 8), kcap);
     double rr_first = 0.0;
+    const bool fp64_next = PX != P64 && op64.blk;   // the caller goes on in FP64 (clover_cg_mp)
+    auto broken = [&](CGBreak how) {
+        res.broke = how;
+        return res;
+    };
     for (;;) {
         for (int left = n; left > 0;) {
             const int m = std::min(left, B);
@@ -2095,8 +2100,10 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
         FGI_HIP(hipStreamSynchronize(c.stream));
         const CGState hs = *c.host_state;
         const double bb = c.host_scal[0], rr_true = c.host_scal[1], target = tol * tol * bb;
-        if (!std::isfinite(rr_true))
+        if (!std::isfinite(rr_true)) {
+            if (base0 && fp64_next) return broken(CG_BROKE_LOST);
             throw Error(-4, guess && !base0 ? "CG: non-finite residual of the starting point" : "CG: non-finite residual");
+        }
         if (bb == 0.0) {   // phi = 0: the solution is 0, whatever the start
             if (guess) zero_spinor(c, g, X, P64);
             res.converged = 1;
@@ -2114,7 +2121,12 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
         const bool inner_done = hs.stop_at <= kend;
         k = kend;
         const double now = hs.rr[kend & 1];
-        if (!std::isfinite(now)) throw Error(-4, "CG: non-finite residual");
+        if (!std::isfinite(now)) {
+            res.iters = kend;
+            res.rel_resid = std::sqrt(rr_true / bb);   // X is as the last true residual found it
+            if (fp64_next) return broken(CG_BROKE_KEPT);
+            throw Error(-4, "CG: non-finite residual");
+        }
         double stop = hs.rr_stop;
         if (inner_done || kend >= kcap) {
             if (PX != P64) {
@@ -2131,7 +2143,10 @@ static CGResult cg_run(Ctx& c, const FermionOp& op64, const FermionOp& ops, cons
                 FGI_HIP(hipStreamSynchronize(c.stream));
                 const double rr = c.host_scal[1];
                 res.rel_resid = std::sqrt(rr / bb);
-                if (!std::isfinite(rr)) throw Error(-4, "CG: non-finite residual");
+                if (!std::isfinite(rr)) {
+                    if (fp64_next) return broken(CG_BROKE_LOST);
+                    throw Error(-4, "CG: non-finite residual");
+                }
                 if (rr <= target) {
                     res.converged = 1;
                     break;

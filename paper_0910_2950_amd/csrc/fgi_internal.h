@@ -335,7 +335,10 @@ struct CGResult {
     int converged;
     double rel_resid;
     int reliable_updates;
+    int broke = 0;   // CGBreak: a clover solve's FP32 iteration stopped being finite (else 0)
 };
+// X as the break leaves it: the starting point with every reliable update since, or not finite
+enum CGBreak { CG_BROKE_KEPT = 1, CG_BROKE_LOST = 2 };
 // X = (Mhat^+ Mhat)^-1 phi from a zero start, or (guess) from the X given on
 // entry; FP64 op64 for the true residual, sloppy op for the inner iterations
 // (same op for FP64 mode)
@@ -400,7 +403,8 @@ void clover_mhat(Ctx&, const FermionOp& op64, const d2* blk, const d2* in_e, d2*
 CGResult clover_cg(Ctx&, const FermionOp& op64, const d2* blk, const d2* phi, d2* x, double tol, int maxiter,
                    bool guess);
 // the same solve with an FP32 inner CG on the FP32 links of op32 and FP32 blocks
-// (reliable updates: the FP64 true residual decides convergence)
+// (reliable updates: the FP64 true residual decides convergence; FP64 takes over
+// where FP32 is not finite)
 CGResult clover_cg_mp(Ctx&, const FermionOp& op64, const FermionOp& op32, const d2* blk, const d2* phi, d2* x,
                       double tol, int maxiter, bool guess);
 // F += coef (pf_scale F_pf(X_e) + det_scale F_det); Xe may be null when pf_scale == 0

@@ -1,11 +1,12 @@
 """Where cg_maxiter cuts a solve off: the limit itself may be as large as an int
 holds, and a chain of a batch is cut off where its solve alone would be, however
-long the batch's rounds are."""
+long the batch's rounds are.  The clover MP32 solver's turn to FP64 (right-hand
+sides beyond the FP32 range) keeps to the same limit and starting point."""
 import numpy as np
 import pytest
 import torch
 
-from paper_0910_2950_amd import synth
+from paper_0910_2950_amd import fgi, synth
 from paper_0910_2950_amd.fgi import Action, Context
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +69,41 @@ def test_batch_is_cut_off_as_single_solves(cg_batch, prec, recon):
         assert counts[0] < counts[-1]   # the limits do cut solves off
     finally:
         ctx.close()
+
+
+def test_clover_fp64_turn_counts_towards_the_limit(ctx):
+    """FP32 overflows in its first iterations: they count, and FP64 has what is left."""
+    U0, _, eta, _ = synth.hot_start(DIMS, synth.SEED_BASE + 4740)
+    U, phi = dev(U0), dev(eta * 1e39)
+
+    def solve(prec, maxiter):
+        act = Action(beta=5.6, kappa=0.15, csw=1.0, cg_tol=1e-10, cg_maxiter=maxiter, prec=prec)
+        return ctx.cg_solve(DIMS, act, U, phi)
+    X64, st64 = solve("fp64", 1000)
+    X, st = solve("mp32", 1000)
+    lost = st["cg_iters"] - st64["cg_iters"]
+    assert torch.equal(X, X64) and 1 <= lost <= 8 and st["reliable_updates"] == st64["reliable_updates"] + 1
+    solve("mp32", st["cg_iters"])
+    for maxiter in (st["cg_iters"] - 1, lost, 1):
+        with pytest.raises(fgi.FgiError) as e:
+            solve("mp32", maxiter)
+        assert e.value.code == fgi.FGI_ENOCONV
+
+
+def test_clover_fp64_turn_keeps_the_starting_point(ctx):
+    """phi ~ 1e41 and steps of 1e-42, so that the links move by their usual amounts
+    while every residual lies beyond FP32: the displaced solves go on in FP64 from
+    the undisplaced solution, bitwise as the FP64 solver does."""
+    scale = 1e41
+    U0, P0, eta, _ = synth.hot_start(DIMS, synth.SEED_BASE + 4741)
+    out = []
+    for prec in ("fp64", "mp32"):
+        U, P = dev(U0), dev(P0)
+        act = Action(beta=5.6, kappa=0.15, csw=1.0, cg_tol=1e-10, prec=prec)
+        dH, st = ctx.trajectory(DIMS, act, "FG", 0.2 / scale, 2, U, P, dev(eta * scale), pf_is_phi=True)
+        out.append((U, P, dH, st))
+    (U, P, dH, st64), (U2, P2, dH2, st) = out
+    assert float((U - dev(U0)).abs().max()) > 1e-4   # the links moved, so the guesses were only guesses
+    assert torch.equal(U, U2) and torch.equal(P, P2) and dH == dH2
+    assert st["solves"] == st64["solves"]
+    assert st64["cg_iters"] < st["cg_iters"] <= st64["cg_iters"] + 8 * st["solves"]
