@@ -1457,6 +1457,7 @@ static void launch_dslash(Ctx& c, const FermionOp& op, DArgs& a) {
     a.xcd = c.ds_xcd;
     if (op.blk) {
         if constexpr (PIN != P16 && MODE != M_CGS) {
+            if (MODE == M_HOP && a.p_out != 1) throw Error(-1, "a clover hop goes onto odd sites");   // A_ee there
             a.bstride = a.g.V;
             a.blk = (const char*)op.blk + (size_t)a.p_out * a.g.Vh * (op.prec == P64 ? sizeof(d2) : sizeof(f2));
             if constexpr (PIN == P64) {
