@@ -240,8 +240,10 @@ typedef struct {
 /* Autotuner: times every (block, order) schedule on a 64-iteration solve of
  * the caller's system (U, phi in the user layout, act's precision), then
  * every cg_batch on full solves at act->cg_tol, each candidate once untimed
- * first; leaves the fastest choices set in the context and reports all
- * timings in *out (may be NULL).  Results of later calls do not depend on
+ * first, then the best of three; leaves the fastest choices set in the context
+ * and reports all timings in *out (may be NULL).  Where no launch of the system
+ * depends on dslash_block it is left as it was and its timings are reported
+ * alike; cg_batch is left as it was unless another is 2 % faster.  Results of later calls do not depend on
  * the schedule beyond rounding of the reductions (the same schedule always
  * gives the same bits).  Synchronises the stream. */
 int fgi_autotune_cg(fgi_ctx* ctx, const fgi_geom* g, const fgi_action* act, const void* U, const void* phi,
