@@ -439,8 +439,10 @@ __global__ void __launch_bounds__(DBS) k_dslash(DArgs A) {
 // half-spinor products, with all its loads in flight together; the products
 // meet in LDS and wave w sums spin w of the eight hops and finishes it.  The sum
 // runs over the hops in the one-thread order with the same multiply-adds, so a
-// site's result has the same bits; only the block sums of the reductions are
-// grouped differently, and site_split makes that a property of the lattice.
+// site's result has the same bits in FP64 and FP32 (in FP16 the compiler fuses the
+// stored numbers' scaling into the projection differently in the two kernels, a few
+// FP32 roundings); the block sums of the reductions are grouped differently.
+// site_split makes both a property of the lattice and its storage.
 
 // element e = 3 spin + colour of the spinor at s (R the working precision)
 template <int P, typename R> __device__ __forceinline__ cx<R> load_elem(const SpinorPtr& f, int s, int Vh, int e, float n) {
