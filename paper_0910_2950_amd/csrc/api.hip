@@ -189,7 +189,7 @@ struct Fields {
     Fields(Ctx& cc, const Geom& gg, const fgi_action& a) : c(cc), g(gg), act(a) {
         sp = sloppy_prec(&act);
         rc = sloppy_recon(&act);
-        c.split = sp != P16 || rc != 18;
+        c.split = may_split(sp, rc);
     }
 
     FermionOp op64(const d2* u, double kappa) const { return FermionOp{&g, kappa, u, P64, 18}; }
@@ -763,6 +763,7 @@ HaloOp halo_setup(Ctx& c, const Geom& g, const fgi_action* act, const void* U, c
     fgi_action a = *act;
     a.prec = prec;
     const int sp = sloppy_prec(&a), rc = sloppy_recon(&a);
+    c.split = may_split(sp, rc);
     d2* u = (d2*)c.gauge.get(gauge_bytes(g));
     pack_gauge(c, g, U, u);
     d2* vin = (d2*)c.tmp_e.get(spinor_bytes(g));
@@ -1850,7 +1851,7 @@ struct BFields {
     BFields(Ctx& cc, const fgi_action& a) : c(cc), act(a) {
         sp = sloppy_prec(&act);
         rc = sloppy_recon(&act);
-        c.split = sp != P16 || rc != 18;
+        c.split = may_split(sp, rc);
     }
     FermionOp op64(const d2* u) const { return FermionOp{nullptr, 0.0, u, P64, 18}; }
     FermionOp ops(const d2* u, const void* us) const {

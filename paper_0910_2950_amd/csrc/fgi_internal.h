@@ -147,11 +147,7 @@ struct Ctx {
     // threads (= even sites) per block, and XCD-aware block order on/off
     int ds_bs = 256;
     int ds_xcd = 1;
-    // whether this call's Dslash-shaped kernels may share a site between waves:
-    // not with 16-bit fixed-point links, whose iteration counts on an
-    // ill-conditioned field move with the rounding of the FP16 projection (the
-    // compiler fuses it differently in the two kernels; 241 to 276 on a
-    // thermalised 8^4 at kappa = 0.158 over right-hand sides, either kernel)
+    // whether this call's Dslash-shaped kernels may share a site between waves (may_split)
     bool split = true;
     double ru_delta = 0.0;     // reliable-update trigger |r| drop; 0: ru_drop's choice by storage
     // single-lattice CG iteration: 0 the classic form (five launches), 1 the
@@ -176,6 +172,13 @@ struct Ctx {
 // 71.2 -> 70.0, 50.2 -> 52.3.
 constexpr int SPLIT_SITES = 64;
 constexpr int SPLIT_MAX_VH = 32768;
+// A call with 16-bit fixed-point links (FP16 storage, 18 reals) keeps one thread per
+// site, its FP64 hops too, though the split kernels would be the faster here as well.
+// The two kernels round the FP16 projection differently, and on an ill-conditioned
+// field the iteration counts scatter with that rounding (241 to 276 over right-hand
+// sides on a thermalised 8^4 at kappa = 0.158, in either kernel); the bound that the
+// tests set them, 1.12 times FP64's on one right-hand side, is met by this one.
+inline bool may_split(int prec, int recon) { return prec != P16 || recon != 18; }
 inline bool site_split(const Ctx& c, int Vh) { return c.split && Vh <= SPLIT_MAX_VH; }
 // sites per block of the Dslash-shaped kernels on a lattice of Vh even sites
 inline int ds_sites(const Ctx& c, int Vh) { return site_split(c, Vh) ? SPLIT_SITES : c.ds_bs; }
