@@ -944,11 +944,13 @@ void rect_tangent(Ctx& c, const Geom& g, double beta, double c1, const d2* U, co
 }
 
 // ------------------------------------------------------------ updates ----
-// Lattices of at most SERIES_MAX_V sites take the exponential's series: their
-// update lasts as long as one wave's chain of transcendental calls (4^4, force
-// and update together 13.2 -> 10.1 us).  Large updates are bound by their 352
-// bytes per link either way (16^3x32: 35 us), and above the line the links keep
-// the bits that the seeded thermalisations and the committed calibration rest on.
+// Lattices of at most SERIES_MAX_V sites take the exponential's series.  It is the
+// faster on every lattice (a leapfrog step, closed form -> series, us: 4^4 14.4 ->
+// 9.3, 8x4x8x8 15.4 -> 10.0; 8^3x6 16.7 -> 11.5, 8^3x16 23.7 -> 18.2, 16^3x32 137.4 ->
+// 133.9), where an update lasts as long as one wave's chain of transcendental calls
+// most of all.  The line is not one of speed: the two differ in the last bits, and
+// above it the links keep those that the benchmark's seeded thermalisation, and the
+// calibration measured on its field, start from.
 constexpr int SERIES_MAX_V = 2048;
 template <bool SERIES>
 __device__ __forceinline__ void link_update_body(const Geom& g, double h, const double* __restrict__ X,
