@@ -894,11 +894,9 @@ void rect_density_add(Ctx& c, const Geom& g, double bc1, const d2* U, double* h)
 
 // J += coef * (mode 0: J_V[F_R]; mode 1: -J_V[F_R] + [V, F_R] / 2) for the
 // rectangle part F_R = -(beta c1 / 6) TA(U A^R) of the force
-// two waves per SIMD: 1515 -> 1378 us at 16^3x32, 108 B a lane of scratch
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_rect_tangent(Geom g, double bc1, const d2* __restrict__ U,
-                                                     const double* __restrict__ Vd, double* __restrict__ J,
-                                                     double coef, int mode, int xcd) {
-    const int t = slab_thread(g.Vh, 8, xcd);
+__device__ __forceinline__ void rect_tangent_body(const Geom& g, double bc1, const d2* __restrict__ U,
+                                                  const double* __restrict__ Vd, double* __restrict__ J, double coef,
+                                                  int mode, int t) {
     if (t >= 4 * g.V) return;
     const int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
     const Coord c = cb_coords(g, p, s);
@@ -936,10 +934,29 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     for (int a = 0; a < 8; a++) o[(size_t)a * g.Vh] += coef * x[a];
 }
 
+// Up to one wave per SIMD (16384 sites) the kernel keeps its registers; above, two
+// waves per SIMD are held, for 108 B a lane of scratch.  Free -> two waves (us): 4^4
+// 151 -> 174, 8^4 160 -> 185, 12^3x8 190 -> 225, 8x8x16x16 184 -> 212; 12^4 335 -> 320,
+// 10x12x14x16 348 -> 335, 14^3x20 661 -> 643; from 16^4 on within 3 % either way.
+constexpr int RECT_TANGENT_ONE_WAVE_V = 16384;
+__global__ void __launch_bounds__(256) k_rect_tangent_small(Geom g, double bc1, const d2* __restrict__ U,
+                                                           const double* __restrict__ Vd, double* __restrict__ J,
+                                                           double coef, int mode, int xcd) {
+    rect_tangent_body(g, bc1, U, Vd, J, coef, mode, slab_thread(g.Vh, 8, xcd));
+}
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_rect_tangent(Geom g, double bc1, const d2* __restrict__ U, const double* __restrict__ Vd, double* __restrict__ J,
+               double coef, int mode, int xcd) {
+    rect_tangent_body(g, bc1, U, Vd, J, coef, mode, slab_thread(g.Vh, 8, xcd));
+}
+
 void rect_tangent(Ctx& c, const Geom& g, double beta, double c1, const d2* U, const double* Vd, double* J,
                   double coef, int mode) {
-    hipLaunchKernelGGL(k_rect_tangent, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g,
-                       beta * c1, U, Vd, J, coef, mode, c.ds_xcd);
+    const dim3 nb(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), bs(BS);
+    if (g.V <= RECT_TANGENT_ONE_WAVE_V)
+        hipLaunchKernelGGL(k_rect_tangent_small, nb, bs, 0, c.stream, g, beta * c1, U, Vd, J, coef, mode, c.ds_xcd);
+    else
+        hipLaunchKernelGGL(k_rect_tangent, nb, bs, 0, c.stream, g, beta * c1, U, Vd, J, coef, mode, c.ds_xcd);
     FGI_LAUNCH_CHECK();
 }
 
