@@ -440,7 +440,8 @@ void clover_build(Ctx& c, const Geom& g, double kappa, double csw, const d2* U, 
                   double* det_action) {
     d2* fh = (d2*)c.cl_fh.get(sizeof(d2) * 54 * (size_t)g.V);
     double* ld = (double*)c.cl_ld.get(sizeof(double) * 2 * (size_t)g.V);
-    hipLaunchKernelGGL(k_clover_fhat, dim3(slab_blocks(g.Vh, 2, CBS, c.ds_xcd)), dim3(CBS), 0, c.stream, g, U, fh, c.ds_xcd);
+    const int xcd = slab_order(c, g);
+    hipLaunchKernelGGL(k_clover_fhat, dim3(slab_blocks(g.Vh, 2, CBS, xcd)), dim3(CBS), 0, c.stream, g, U, fh, xcd);
     FGI_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_clover_blocks, dim3(nb_of(2L * g.V)), dim3(CBS), 0, c.stream, g, sigma_blocks(c),
                        kappa * csw, (const d2*)fh, blk, ld, invert_odd);
@@ -543,8 +544,9 @@ void clover_force(Ctx& c, const FermionOp& op, double csw, const d2* blk, const 
                        pf ? -2.0 * kc * pf_scale : 0.0, pf ? -2.0 * k * k * kc * pf_scale : 0.0,
                        -2.0 * kc * det_scale, (const d2*)Xe, (const d2*)xo, (const d2*)ye, (const d2*)yo, blk, kt);
     FGI_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_clover_force, dim3(slab_blocks(g.Vh, 8, CBS, c.ds_xcd)), dim3(CBS), 0, c.stream, g,
-                       (const d2*)op.links, (const d2*)kt, coef, F, c.ds_xcd);
+    const int xcd = slab_order(c, g);
+    hipLaunchKernelGGL(k_clover_force, dim3(slab_blocks(g.Vh, 8, CBS, xcd)), dim3(CBS), 0, c.stream, g,
+                       (const d2*)op.links, (const d2*)kt, coef, F, xcd);
     FGI_LAUNCH_CHECK();
 }
 

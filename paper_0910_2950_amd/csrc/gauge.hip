@@ -57,16 +57,47 @@ __device__ __forceinline__ void pack_records(const Geom& g, T* __restrict__ user
         }
     }
 }
+// The same by a thread per record of one parity, without the exchange.
+template <typename T, int NE>
+__device__ __forceinline__ void pack_record(const Geom& g, T* __restrict__ user, T* __restrict__ in, int to_internal,
+                                            int t) {
+    if (t >= 4 * g.V) return;
+    const int s = t % g.Vh, r = t / g.Vh, p = r & 1, mu = r >> 1;
+    const Coord c = cb_coords(g, p, s);
+    const int i = c.c[0] + g.L[0] * (c.c[1] + g.L[1] * (c.c[2] + g.L[2] * c.c[3]));
+    T* pl = in + (size_t)(r * NE) * g.Vh + s;
+    T* us = user + ((size_t)mu * g.V + i) * NE;
+    T v[NE];
+    if (to_internal) {
+#pragma unroll
+        for (int k = 0; k < NE; k++) v[k] = us[k];
+#pragma unroll
+        for (int k = 0; k < NE; k++) pl[(size_t)k * g.Vh] = v[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < NE; k++) v[k] = pl[(size_t)k * g.Vh];
+#pragma unroll
+        for (int k = 0; k < NE; k++) us[k] = v[k];
+    }
+}
+// One block's 256 records either way.
+template <bool EX, typename T, int NE, int PAD>
+__device__ __forceinline__ void pack_block(const Geom& g, T* user, T* in, int to_internal, int blk, T* lds) {
+    if (EX) pack_records<T, NE, PAD>(g, user, in, to_internal, blk, lds);
+    else pack_record<T, NE>(g, user, in, to_internal, blk * 256 + (int)threadIdx.x);
+}
 constexpr int PACK_LINK_LDS = 256 * 9, PACK_MOM_LDS = 256 * 9;   // elements; a momentum row is padded to 9
 
+template <bool EX>
 __global__ void __launch_bounds__(256) k_pack_gauge(Geom g, const d2* user, d2* U, int to_internal) {
-    __shared__ d2 lds[PACK_LINK_LDS];
-    pack_records<d2, 9, 0>(g, (d2*)user, U, to_internal, blockIdx.x, lds);
+    __shared__ d2 lds[EX ? PACK_LINK_LDS : 1];
+    pack_block<EX, d2, 9, 0>(g, (d2*)user, U, to_internal, blockIdx.x, lds);
 }
 
+template <bool EX>
 __global__ void __launch_bounds__(256) k_pack_mom(Geom g, const double* user, double* P, int to_internal) {
-    __shared__ double lds[PACK_MOM_LDS];
-    pack_records<double, 8, 1>(g, (double*)user, P, to_internal, blockIdx.x, lds);
+    __shared__ double lds[EX ? PACK_MOM_LDS : 1];
+    pack_block<EX, double, 8, 1>(g, (double*)user, P, to_internal, blockIdx.x, lds);
 }
 
 // user even spinor: entry k (= checkerboard index of the k-th even site) holds [4][3] complex
@@ -90,53 +121,76 @@ __global__ void k_pack_even(Geom g, const d2* __restrict__ user, d2* __restrict_
 // even spinor.  Small calls last as long as their launches: Mhat at 8^4, four
 // launches instead of five, 25 -> 21 us, the fermion force 52 -> 39 us (its split
 // hops included).
+template <bool EX>
 __global__ void __launch_bounds__(256) k_pack_inputs(Geom g, const d2* U, d2* u, const double* P, double* pm,
                                                      const d2* X, d2* x, int nl, int nm) {
-    __shared__ d2 lds[PACK_LINK_LDS];
+    __shared__ d2 lds[EX ? PACK_LINK_LDS : 1];
     const int b = blockIdx.x;
-    if (b < nl) pack_records<d2, 9, 0>(g, (d2*)U, u, 1, b, lds);
-    else if (b < nl + nm) pack_records<double, 8, 1>(g, (double*)P, pm, 1, b - nl, (double*)lds);
+    if (b < nl) pack_block<EX, d2, 9, 0>(g, (d2*)U, u, 1, b, lds);
+    else if (b < nl + nm) pack_block<EX, double, 8, 1>(g, (double*)P, pm, 1, b - nl, (double*)lds);
     else pack_even_body(g, X, x, 1, (b - nl - nm) * 256 + (int)threadIdx.x);
 }
 
 // batched: field 0 links, 1 momenta, 2 even spinor (the chain's user pointer)
+template <bool EX>
 __global__ void __launch_bounds__(256) k_pack_b(const ChainDesc* __restrict__ cd, int nc, void* internal, int field,
                                                 int to_internal) {
-    __shared__ d2 lds[PACK_LINK_LDS];
+    __shared__ d2 lds[EX ? PACK_LINK_LDS : 1];
     const int kind = field == 2 ? GRID_VH : GRID_4V;
     const int c = find_chain(cd, nc, blockIdx.x, kind);
     const ChainDesc& d = cd[c];
     const int b = blockIdx.x - d.blk0[kind];
-    if (field == 0) pack_records<d2, 9, 0>(d.g, (d2*)d.user_U, (d2*)internal + 9 * d.link0, to_internal, b, lds);
+    if (field == 0) pack_block<EX, d2, 9, 0>(d.g, (d2*)d.user_U, (d2*)internal + 9 * d.link0, to_internal, b, lds);
     else if (field == 1)
-        pack_records<double, 8, 1>(d.g, (double*)d.user_P, (double*)internal + 8 * d.link0, to_internal, b, (double*)lds);
+        pack_block<EX, double, 8, 1>(d.g, (double*)d.user_P, (double*)internal + 8 * d.link0, to_internal, b, (double*)lds);
     else
         pack_even_body(d.g, (const d2*)d.user_eta, (d2*)internal + 12 * d.site0, to_internal, b * 256 + (int)threadIdx.x);
 }
 
-void pack_gauge(Ctx& c, const Geom& g, const void* user, d2* U) {
-    hipLaunchKernelGGL(k_pack_gauge, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, (const d2*)user, U, 1);
+// Which way.  On a lattice that the L2s hold, a thread per record leaves each plane's
+// stretch in the L2 of the XCD whose block reads it next (blocks in linear order), and
+// waits for no barrier; above, every line's second fetch costs more.  Whole calls,
+// exchange -> direct (us): reunitarise 8^4 26.4 -> 24.6, 8x8x16x16 33.2 -> 29.0, 12^4 35.2 ->
+// 35.4, 12^3x24 40.5 -> 46.7; link update 8^3x16 37.9 -> 34.0, 12^4 43.1 -> 44.7, 16^4
+// 70.3 -> 76.1.  Momenta alone: kinetic term (in) 16^3x8 33.6 -> 31.3, 16^4 37.6 -> 33.5,
+// 10x14x22x26 39.7 -> 40.6; gauge force (out) 8^4 30.5 -> 29.5, 8^3x16 35.1 -> 36.3.
+// Links alone go direct up to twice the line where the planes are whole rounds of the
+// eight XCDs (2048 sites): action 16^3x8 46.5 -> 43.2.
+constexpr int PACK_DIRECT_MAX_V = 16384, PACK_MOM_IN_MAX_V = 65536, PACK_MOM_OUT_MAX_V = 4096;
+static bool whole_rounds(const Geom& g) { return g.Vh % 2048 == 0; }
+static bool exchange_links(const Geom& g, int to_internal) {
+    return g.V > (to_internal && whole_rounds(g) ? 2 * PACK_DIRECT_MAX_V : PACK_DIRECT_MAX_V);
+}
+static bool exchange_mom(const Geom& g, int to_internal) {
+    return g.V > (to_internal ? PACK_MOM_IN_MAX_V : PACK_MOM_OUT_MAX_V);
+}
+static void launch_pack_gauge(Ctx& c, const Geom& g, const void* user, d2* U, int to_internal) {
+    const dim3 nb(nblocks(4L * g.V, BS)), bs(BS);
+    if (exchange_links(g, to_internal)) hipLaunchKernelGGL(k_pack_gauge<true>, nb, bs, 0, c.stream, g, (const d2*)user, U, to_internal);
+    else hipLaunchKernelGGL(k_pack_gauge<false>, nb, bs, 0, c.stream, g, (const d2*)user, U, to_internal);
     FGI_LAUNCH_CHECK();
 }
+static void launch_pack_mom(Ctx& c, const Geom& g, const double* user, double* P, int to_internal) {
+    const dim3 nb(nblocks(4L * g.V, BS)), bs(BS);
+    if (exchange_mom(g, to_internal)) hipLaunchKernelGGL(k_pack_mom<true>, nb, bs, 0, c.stream, g, user, P, to_internal);
+    else hipLaunchKernelGGL(k_pack_mom<false>, nb, bs, 0, c.stream, g, user, P, to_internal);
+    FGI_LAUNCH_CHECK();
+}
+
+void pack_gauge(Ctx& c, const Geom& g, const void* user, d2* U) { launch_pack_gauge(c, g, user, U, 1); }
 // links, and where given momenta and an even spinor
 void pack_inputs(Ctx& c, const Geom& g, const void* U, d2* u, const double* P, double* pm, const void* X, d2* x) {
     const int nl = nblocks(4L * g.V, BS), nm = P ? nl : 0, nx = X ? nblocks(g.Vh, BS) : 0;
-    hipLaunchKernelGGL(k_pack_inputs, dim3(nl + nm + nx), dim3(BS), 0, c.stream, g, (const d2*)U, u, P, pm, (const d2*)X,
-                       x, nl, nm);
+    const dim3 nb(nl + nm + nx), bs(BS);
+    if (g.V > PACK_DIRECT_MAX_V)
+        hipLaunchKernelGGL(k_pack_inputs<true>, nb, bs, 0, c.stream, g, (const d2*)U, u, P, pm, (const d2*)X, x, nl, nm);
+    else
+        hipLaunchKernelGGL(k_pack_inputs<false>, nb, bs, 0, c.stream, g, (const d2*)U, u, P, pm, (const d2*)X, x, nl, nm);
     FGI_LAUNCH_CHECK();
 }
-void unpack_gauge(Ctx& c, const Geom& g, const d2* U, void* user) {
-    hipLaunchKernelGGL(k_pack_gauge, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, (const d2*)user, (d2*)U, 0);
-    FGI_LAUNCH_CHECK();
-}
-void pack_mom(Ctx& c, const Geom& g, const double* user, double* P) {
-    hipLaunchKernelGGL(k_pack_mom, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, user, P, 1);
-    FGI_LAUNCH_CHECK();
-}
-void unpack_mom(Ctx& c, const Geom& g, const double* P, double* user) {
-    hipLaunchKernelGGL(k_pack_mom, dim3(nblocks(4L * g.V, BS)), dim3(BS), 0, c.stream, g, (const double*)user, (double*)P, 0);
-    FGI_LAUNCH_CHECK();
-}
+void unpack_gauge(Ctx& c, const Geom& g, const d2* U, void* user) { launch_pack_gauge(c, g, user, (d2*)U, 0); }
+void pack_mom(Ctx& c, const Geom& g, const double* user, double* P) { launch_pack_mom(c, g, user, P, 1); }
+void unpack_mom(Ctx& c, const Geom& g, const double* P, double* user) { launch_pack_mom(c, g, user, (double*)P, 0); }
 void pack_even_spinor(Ctx& c, const Geom& g, const void* user, d2* X) {
     hipLaunchKernelGGL(k_pack_even, dim3(nblocks(g.Vh, BS)), dim3(BS), 0, c.stream, g, (const d2*)user, X, 1);
     FGI_LAUNCH_CHECK();
@@ -239,9 +293,20 @@ __global__ void __launch_bounds__(256) k_ham_density_b(const ChainDesc* __restri
 
 void rect_density_add(Ctx& c, const Geom& g, double bc1, const d2* U, double* h);
 
+// Order of the density kernel: linear where the fields lie in the L2s as the layout
+// kernels' blocks left them: the momenta up to 65536 sites, and links whose planes are
+// whole rounds of the XCDs unless the rectangles read them too.  Linear -> slabs (us): kinetic term 8x8x16x16 30.4 -> 31.8,
+// 16^3x8 31.3 -> 33.8, 12^3x24 34.8 -> 34.7; action 8^3x16 38.7 -> 39.6, 16^3x8 43.2 ->
+// 47.2, 16^4 52.6 -> 52.7, 16^3x32 91.9 -> 84.3; 12^3x8 45.2 -> 43.2, 12^3x24 51.5 -> 47.6.
+static int density_order(const Ctx& c, const Geom& g, const d2* U, double c1) {
+    if (g.V <= PACK_MOM_IN_MAX_V && (!U || (whole_rounds(g) && c1 == 0.0))) return 0;
+    return slab_order(c, g);
+}
+
 void ham_density(Ctx& c, const Geom& g, double beta, const d2* U, const double* P, double* h, double c1) {
-    hipLaunchKernelGGL(k_ham_density, dim3(slab_blocks(g.Vh, 2, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g,
-                       beta * (1.0 - 8.0 * c1), U, P, h, c.ds_xcd);
+    const int xcd = density_order(c, g, U, c1);
+    hipLaunchKernelGGL(k_ham_density, dim3(slab_blocks(g.Vh, 2, BS, xcd)), dim3(BS), 0, c.stream, g,
+                       beta * (1.0 - 8.0 * c1), U, P, h, xcd);
     FGI_LAUNCH_CHECK();
     if (c1 != 0.0 && U) rect_density_add(c, g, beta * c1, U, h);
 }
@@ -887,8 +952,8 @@ __global__ void __launch_bounds__(256) k_rect_density_b(const ChainDesc* __restr
 }
 
 void rect_density_add(Ctx& c, const Geom& g, double bc1, const d2* U, double* h) {
-    hipLaunchKernelGGL(k_rect_density, dim3(slab_blocks(g.Vh, 2, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, bc1, U, h,
-                       c.ds_xcd);
+    const int xcd = slab_order(c, g);
+    hipLaunchKernelGGL(k_rect_density, dim3(slab_blocks(g.Vh, 2, BS, xcd)), dim3(BS), 0, c.stream, g, bc1, U, h, xcd);
     FGI_LAUNCH_CHECK();
 }
 
@@ -1122,7 +1187,10 @@ void exp_su3_batch(Ctx& c, int n, const double* p, double h, void* out) {
 // ------------------------------------------------------ batched launchers ---
 void pack_b(Ctx& c, const Batch& B, void* internal, int field, int to_internal) {
     int nb = field == 2 ? B.nblk[GRID_VH] : B.nblk[GRID_4V];
-    hipLaunchKernelGGL(k_pack_b, dim3(nb), dim3(BS), 0, c.stream, B.cd, B.nc, internal, field, to_internal);
+    if (B.vol > PACK_DIRECT_MAX_V)
+        hipLaunchKernelGGL(k_pack_b<true>, dim3(nb), dim3(BS), 0, c.stream, B.cd, B.nc, internal, field, to_internal);
+    else
+        hipLaunchKernelGGL(k_pack_b<false>, dim3(nb), dim3(BS), 0, c.stream, B.cd, B.nc, internal, field, to_internal);
     FGI_LAUNCH_CHECK();
 }
 

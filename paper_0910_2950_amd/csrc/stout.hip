@@ -72,7 +72,7 @@ __device__ __forceinline__ void link_of(const Geom& g, int t, int& mu, int& p, i
 
 }  // namespace
 
-// Block order of the three kernels below: XCD-owned slabs (slab_thread), so the
+// Block order of the three kernels below: XCD-owned slabs (slab_order), so the
 // neighbour links (and M) of a block come from its own XCD's L2.  They are bound
 // by those loads and their register-held products at one or two waves per SIMD;
 // 16^3x32, linear -> slabs: level 161 -> 110 us, gamma 281 -> 225, gather 296 ->
@@ -231,11 +231,12 @@ __global__ void __launch_bounds__(256) k_stout_gather_b(const ChainDesc* __restr
 
 const d2* stout_smear(Ctx& c, const Geom& g, double rho, int n, const d2* U, d2* levels) {
     const size_t sz = (size_t)4 * 9 * g.V;
+    const int xcd = slab_order(c, g);
     const d2* in = U;
     for (int k = 0; k < n; k++) {
         d2* out = levels + k * sz;
-        hipLaunchKernelGGL(k_stout_level, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, rho, in,
-                           out, c.ds_xcd);
+        hipLaunchKernelGGL(k_stout_level, dim3(slab_blocks(g.Vh, 8, BS, xcd)), dim3(BS), 0, c.stream, g, rho, in,
+                           out, xcd);
         FGI_LAUNCH_CHECK();
         in = out;
     }
@@ -250,15 +251,16 @@ void stout_backprop(Ctx& c, const Geom& g, double rho, int n, const d2* U, const
     double* gb = (double*)c.stout_gb.get(mb);
     double* part = (double*)c.stout_part.get(mb);
     d2* M = (d2*)c.stout_M.get(sizeof(d2) * sz);
+    const int xcd = slab_order(c, g);
     const double* Gin = Fs;
     for (int k = n - 1; k >= 0; k--) {
         const d2* Uk = k == 0 ? U : levels + (k - 1) * sz;
-        hipLaunchKernelGGL(k_stout_gamma, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, rho, Uk,
-                           Gin, part, M, c.ds_xcd);
+        hipLaunchKernelGGL(k_stout_gamma, dim3(slab_blocks(g.Vh, 8, BS, xcd)), dim3(BS), 0, c.stream, g, rho, Uk,
+                           Gin, part, M, xcd);
         FGI_LAUNCH_CHECK();
         double* Gout = k == 0 ? F : ((n - 1 - k) % 2 == 0 ? ga : gb);
-        hipLaunchKernelGGL(k_stout_gather, dim3(slab_blocks(g.Vh, 8, BS, c.ds_xcd)), dim3(BS), 0, c.stream, g, Uk, M,
-                           part, Gout, k == 0 ? coef : 1.0, k == 0 ? accumulate : 0, c.ds_xcd);
+        hipLaunchKernelGGL(k_stout_gather, dim3(slab_blocks(g.Vh, 8, BS, xcd)), dim3(BS), 0, c.stream, g, Uk, M,
+                           part, Gout, k == 0 ? coef : 1.0, k == 0 ? accumulate : 0, xcd);
         FGI_LAUNCH_CHECK();
         Gin = Gout;
     }
