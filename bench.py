@@ -794,7 +794,7 @@ def clover_leg(R, U_therm, inputs, n, kappa=0.135, csw=1.0, reps=10):
     solves at the timed tolerance), and fgi_mhat with and without the clover
     term (HIP events around reps calls: pack, clover blocks, two hops and the
     site-local A_ee, A_oo^-1 products); the clover trajectory again with the
-    mixed-precision solver (FP32 inner CG, FP64 defect correction)."""
+    mixed-precision solver (FP32 iterations, FP64 reliable updates)."""
     torch = R.torch
     integ = R.fgi.integrator_builtin("FG", 0.1932)
     U = torch.empty_like(U_therm)
@@ -1307,7 +1307,7 @@ def main():
         k = min(args.improved_steps, args.steps)
         improved = improved_gauge_leg(R, U, inputs[args.warmup:args.warmup + k], n_fg)
         log("pure-gauge FG n=%d: Wilson %.4f s/traj, tree-level Symanzik %.4f s/traj; gauge force call "
-            "%.3f ms -> %.3f ms, rectangle kernel %.1f us = %.1f TFLOP/s FP64" %
+            "%.3f ms -> %.3f ms, the rectangles' part %.1f us = %.1f TFLOP/s FP64" %
             (n_fg, improved["wilson"]["s_per_traj"], improved["symanzik"]["s_per_traj"],
              improved["gauge_force_call_ms"]["wilson"], improved["gauge_force_call_ms"]["symanzik"],
              improved["rect_force_kernel"]["us"], improved["rect_force_kernel"]["achieved_TFLOPs"] or 0))
