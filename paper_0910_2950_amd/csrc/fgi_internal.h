@@ -185,10 +185,11 @@ inline int ds_sites(const Ctx& c, int Vh) { return site_split(c, Vh) ? SPLIT_SIT
 // |r| drop at which the true residual replaces an inner run's own: the caller's
 // (option "ru_delta"), or by storage.  FP32 loses nothing by a drop of 0.01: iterations
 // and us per solve to 1e-12, 0.1 against 0.01, 223, 14742 -> 223, 13885 on
-// 16^3x32 and 139, 4385 -> 139, 3960 on 12x10x14x18 (half the FP64 residuals);
-// near kappa_c on a thermalised 8^4 the iterations rise by 1 to 4 %, at 0.001 by
-// 4 to 7 %.  16-bit storage stays at 0.1: the rounding of its vectors drives the
-// recursion away there (fixed-point links, 0.03: 6 % at 223 iterations, a
+// 16^3x32 and 139, 4385 -> 139, 3960 on 12x10x14x18 (half the FP64 residuals); on
+// thermalised 8^4 to 12^4 up to kappa_c the iterations stay (222 -> 243 for one
+// right-hand side of 24) and the time falls by 3 to 14 %; at 0.001 they rise by 4 to
+// 7 % near kappa_c.  16-bit storage stays at 0.1: the rounding of its vectors drives
+// the recursion away there (fixed-point links, 0.03: 6 % at 223 iterations, a
 // quarter on a thermalised field near kappa_c).
 inline double ru_drop(const Ctx& c, int prec) { return c.ru_delta > 0.0 ? c.ru_delta : (prec == P32 ? 0.01 : 0.1); }
 
